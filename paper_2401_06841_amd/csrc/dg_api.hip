@@ -157,7 +157,21 @@ void build_tables(std::vector<double> &t)
         t[TL::LEND + 2 * n + 1] = lt(n, 1.0);
     }
     for (int p = 0; p <= K; ++p)
-        for (int a = 0; a <= K; ++a) t[TL::WLT + p * (K + 1) + a] = w[p] * lt(a, g[p]);
+        for (int a = 0; a <= K; ++a) {
+            t[TL::WLT + p * (K + 1) + a] = w[p] * lt(a, g[p]);
+            t[TL::P1 + p * (K + 1) + a] = lt(a, g[p]);
+        }
+    for (int ty = 0; ty < S::N1; ++ty)
+        for (int tx = 0; tx < S::N1; ++tx) {
+            const int r = tx + S::N1 * ty;
+            const double wr = w[tx] * w[ty];
+            for (int j = 0; j < S::NB2; ++j) {
+                const int a = M.p2[j][0], b = M.p2[j][1];
+                t[TL::LWP + r * S::NB2 + j] = wr * lt(a, g[tx]) * lt(b, g[ty]);
+                if (a >= 1) t[TL::LWX + r * TL::NL + line_dx(a, b)] = wr * dlt(a, g[tx]) * lt(b, g[ty]);
+                if (b >= 1) t[TL::LWY + r * TL::NL + line_dy(a, b)] = wr * lt(a, g[tx]) * dlt(b, g[ty]);
+            }
+        }
     // basis values on the faces: the face point r = r1 + (k+1) r2 has the tangential
     // coordinates (g[r1], g[r2]) along the axes tan1(d) < tan2(d), and xi_d = -1 or +1
     for (int d = 0; d < 3; ++d)
@@ -636,8 +650,6 @@ static int launch_rhs(dg_ctx *c, const void *u, const void *vh, void *out, doubl
     RhsArgs a;
     a.u = u;
     a.vh = vh;
-    a.vh_rho = nullptr;
-    a.pair_vstride = 0;
     a.out = out;
     a.tab = c->tab;
     a.ftab = c->wp(c->off.ftab);
@@ -678,19 +690,13 @@ static int launch_rhs(dg_ctx *c, const void *u, const void *vh, void *out, doubl
     }
     if constexpr (rhs_pair<T, K>()) {
         c->rhs_nblk = (c->nc + BLOCK / 2 - 1) / (BLOCK / 2);
-        // each lane loads only its own variables when two variable blocks and a cell offset fit
-        // a 32-bit buffer offset, and (projected traces) the density copy is in front of vh
-        const size_t vb = (size_t)c->nb * c->nc * 8;
-        const bool prim = c->cfg.flags & DG_PRIM_PROJ;
-        a.vh_rho = vh_rho_of(c, vh);
-        const bool lsel = 2 * vb + (size_t)c->nc * 8 < ((size_t)1 << 32) && (!prim || a.vh_rho);
-        a.pair_vstride = lsel ? (unsigned)(2 * vb) : 0u;
-        if (lsel) {
-            if (direct) hipLaunchKernelGGL((k_rhs_pair<K, true, true>), dim3(c->rhs_nblk), dim3(BLOCK), 0, c->stream, a);
-            else hipLaunchKernelGGL((k_rhs_pair<K, false, true>), dim3(c->rhs_nblk), dim3(BLOCK), 0, c->stream, a);
+        const dim3 gr(c->rhs_nblk), bl(BLOCK);
+        if (a.flags & DG_PRIM_PROJ) {
+            if (direct) hipLaunchKernelGGL((k_rhs_pair<K, true, true>), gr, bl, 0, c->stream, a);
+            else hipLaunchKernelGGL((k_rhs_pair<K, false, true>), gr, bl, 0, c->stream, a);
         } else {
-            if (direct) hipLaunchKernelGGL((k_rhs_pair<K, true, false>), dim3(c->rhs_nblk), dim3(BLOCK), 0, c->stream, a);
-            else hipLaunchKernelGGL((k_rhs_pair<K, false, false>), dim3(c->rhs_nblk), dim3(BLOCK), 0, c->stream, a);
+            if (direct) hipLaunchKernelGGL((k_rhs_pair<K, true, false>), gr, bl, 0, c->stream, a);
+            else hipLaunchKernelGGL((k_rhs_pair<K, false, false>), gr, bl, 0, c->stream, a);
         }
     } else {
         c->rhs_nblk = c->nblk;

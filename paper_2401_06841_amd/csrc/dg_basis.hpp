@@ -70,6 +70,11 @@ constexpr int idx3(int a, int b, int c)
     return n * (n + 1) * (n + 2) / 6 + (n - a) * (n - a + 1) / 2 + c;
 }
 
+// position among the 2D modes with a positive first exponent of the pair (p, q), p >= 1, and
+// among those with a positive second exponent, q >= 1 (the graded order of the reduced pair)
+constexpr int line_dx(int p, int q) { return idx2(p - 1, q); }
+constexpr int line_dy(int p, int q) { return idx2(p, q - 1); }
+
 // Derivative of a basis function along one axis in the basis itself: from
 // P_n' = sum over j = n-1, n-3, ... >= 0 of (2j+1) P_j it follows that
 // d/dxi Lt_n = sum_j sqrt((2n+1)(2j+1)) Lt_j, so d/dxi_d phi_e is a combination of the
@@ -120,7 +125,15 @@ struct TabLayout {
                                                             //   face (normal d, side s: 0 low, 1 high)
     static constexpr int WLT = PLIFT + 3 * 2 * S::NF * S::NB;  // [K+1][K+1] w_t Lt_a(xi_t): 1D weight times
                                                             //   the 1D basis of degree a at 1D point t
-    static constexpr int SIZE = WLT + (K + 1) * (K + 1);
+    static constexpr int P1 = WLT + (K + 1) * (K + 1);     // [K+1][K+1] Lt_a(xi_t) at 1D point t
+    // per line of volume points along z, r = t_x + (K+1) t_y: the weighted 2D basis
+    // w_r phi2_j (j < NB2; j = 0 is w_r itself), then w_r d/dx phi2_j and w_r d/dy phi2_j of the
+    // modes with a positive x (y) exponent, in the order of line_dx (line_dy)
+    static constexpr int NL = S::NB2 - (K + 1);             // 2D modes with a positive exponent along an axis
+    static constexpr int LWP = P1 + (K + 1) * (K + 1);      // [NF][NB2]
+    static constexpr int LWX = LWP + S::NF * S::NB2;        // [NF][NL]
+    static constexpr int LWY = LWX + S::NF * NL;            // [NF][NL]
+    static constexpr int SIZE = LWY + S::NF * NL;
 };
 
 }  // namespace dg

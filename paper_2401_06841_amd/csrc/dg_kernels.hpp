@@ -14,6 +14,7 @@
 #include <type_traits>
 
 #include "dg_basis.hpp"
+#include "dg_line.hpp"
 
 namespace dg {
 
@@ -249,12 +250,6 @@ struct RhsArgs {
     const double *dt_dev;   // the time step in device memory (a stage launched ahead), or NULL: dt
     int bpp, zt;            // block sweep order (plane_tiled): blocks per z-plane, planes per tile
     const float *mfma;      // A-operand tables of the matrix-core volume integral (MfmaTab), or NULL
-    // two-lane kernel: a copy of the density weights directly in front of vh (so that density
-    // and projected velocity form one [4][nb][nc] array), or NULL; and the byte distance of two
-    // variable blocks (2 nb nc 8) when every lane can reach its own variables through a 32-bit
-    // offset, else 0
-    const void *vh_rho;
-    unsigned pair_vstride;
 };
 
 // time-step bound inputs shared by the projection and stage kernels
@@ -447,48 +442,50 @@ __device__ __forceinline__ void project_first_with_speed(const T (&W)[4][Shape<K
 template <typename T>
 constexpr bool split_projection() { return sizeof(T) == 8; }
 
-// isothermal Rusanov flux across a face with normal +e_D between the low (L) and high
-// (R) states; u = (rho, m), v = velocity (Sec. 2.2 numerical flux)
-template <int D, typename T>
-__device__ __forceinline__ void rusanov(T cs, T cs2, const T (&uL)[4], const T (&vL)[3], const T (&uR)[4],
-                                        const T (&vR)[3], T (&F)[4])
+// The face flux at one point, in two parts, so that a face's tangential traces need not be held
+// beside the normal ones (Sec. 2.2 numerical flux; all values are twice the flux's): from the
+// density r and normal velocity v of the low (L) and high (R) side, the mass flux F0, the normal
+// momentum flux Fn, and the factors gL, gR that give each tangential momentum flux as
+// gL v_t,L + gR v_t,R.
+//
+// Isothermal Rusanov flux: m_j v_n +- lambda m_j of a side is r (v_n +- lambda) times v_j, so
+// the factors are g = r (v_n +- lambda); the mass flux keeps the difference form.
+template <typename T>
+__device__ __forceinline__ void rusanov2(T cs, T cs2, T rL, T vL, T rR, T vR, T &F0, T &Fn, T &gL, T &gR)
 {
     // every fused multiply-add written out and no other contraction left to the compiler:
     // the flux of a face is then the same bits whichever of its two cells computes it
 #pragma clang fp contract(off)
-    const T lam = fmax(fabs(vL[D]), fabs(vR[D])) + cs;
-    const T hl = T(0.5) * lam;
-    F[0] = fma(-hl, uR[0] - uL[0], T(0.5) * (uL[1 + D] + uR[1 + D]));
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-        F[1 + j] = fma(-hl, uR[1 + j] - uL[1 + j], T(0.5) * fma(uL[1 + D], vL[j], uR[1 + D] * vR[j]));
-    F[1 + D] = fma(T(0.5) * cs2, uL[0] + uR[0], F[1 + D]);
+    const T lam = fmax(fabs(vL), fabs(vR)) + cs;
+    F0 = fma(-lam, rR - rL, fma(rL, vL, rR * vR));
+    gL = rL * (vL + lam);
+    gR = rR * (vR - lam);
+    Fn = fma(cs2, rL + rR, fma(gL, vL, gR * vR));
 }
 
-// isothermal HLLC-type flux across a face with normal +e_D (the counterpart of the HLLC
-// solver of Sec. 2.2 for isothermal gas): wave speeds S_L = min(v_L, v_R) - cs and
-// S_R = max(v_L, v_R) + cs of the normal velocities; density and normal momentum take the
-// HLL flux, each tangential momentum is the mass flux times the upwind tangential velocity
-template <int D, typename T>
-__device__ __forceinline__ void hllc(T cs, T cs2, const T (&uL)[4], const T (&vL)[3], const T (&uR)[4],
-                                     const T (&vR)[3], T (&F)[4])
+// Isothermal HLLC-type flux (the counterpart of the HLLC solver of Sec. 2.2 for isothermal gas):
+// wave speeds S_L = min(v_L, v_R) - cs and S_R = max(v_L, v_R) + cs of the normal velocities;
+// density and normal momentum take the HLL flux, each tangential momentum is the mass flux times
+// the upwind tangential velocity
+template <typename T>
+__device__ __forceinline__ void hllc2(T cs, T cs2, T rL, T vL, T rR, T vR, T &F0, T &Fn, T &gL, T &gR)
 {
-    const T SL = fmin(vL[D], vR[D]) - cs;
-    const T SR = fmax(vL[D], vR[D]) + cs;
-    const T FL0 = uL[1 + D], FR0 = uR[1 + D];
-    const T FLn = uL[1 + D] * vL[D] + cs2 * uL[0];
-    const T FRn = uR[1 + D] * vR[D] + cs2 * uR[0];
+#pragma clang fp contract(off)
+    const T nL = rL * vL, nR = rR * vR;
+    const T SL = fmin(vL, vR) - cs;
+    const T SR = fmax(vL, vR) + cs;
+    const T FLn = fma(nL, vL, cs2 * rL);
+    const T FRn = fma(nR, vR, cs2 * rR);
     const T iw = rcp(SR - SL);
     const T sLR = SL * SR;
-    T F0 = (SR * FL0 - SL * FR0 + sLR * (uR[0] - uL[0])) * iw;
-    T Fn = (SR * FLn - SL * FRn + sLR * (uR[1 + D] - uL[1 + D])) * iw;
-    F0 = SL >= T(0) ? FL0 : (SR <= T(0) ? FR0 : F0);
-    Fn = SL >= T(0) ? FLn : (SR <= T(0) ? FRn : Fn);
-    F[0] = F0;
-    F[1 + D] = Fn;
-#pragma unroll
-    for (int t = 0; t < 3; ++t)
-        if (t != D) F[1 + t] = F0 * (F0 >= T(0) ? vL[t] : vR[t]);
+    T f0 = fma(sLR, rR - rL, fma(SR, nL, -(SL * nR))) * iw;
+    T fn = fma(sLR, nR - nL, fma(SR, FLn, -(SL * FRn))) * iw;
+    f0 = SL >= T(0) ? nL : (SR <= T(0) ? nR : f0);
+    fn = SL >= T(0) ? FLn : (SR <= T(0) ? FRn : fn);
+    F0 = f0 + f0;
+    Fn = fn + fn;
+    gL = F0 >= T(0) ? F0 : T(0);
+    gR = F0 >= T(0) ? T(0) : F0;
 }
 
 // von Neumann-Richtmyer viscous pressure at one point (Sec. 3.1)
@@ -503,115 +500,290 @@ __device__ __forceinline__ T vnr_pi(T rho, T divv, T hp, T alpha, T beta, T cs, 
 }
 
 // ---------------------------------------------------------------- face pass
-// Surface integral of one face (normal axis D, side s: 0 = low, 1 = high) from the point
-// fluxes in an LDS column (col: the column of the cell that stored them, [r][v] with stride
-// BLOCK): the flux moments against the 2D basis of the face, M_vj = sum_r w_r F_v(r) P2_j(r),
-// then per mode phi_l = Lt_{e_D}(+-1) P2_{d2(l)} on the face, so L_vl += Lt_{e_D}(+-1) M_v,d2(l)
-// (the lift of every point into all NB modes takes NB multiply-adds per point and variable,
-// the moments NB2).
+// Face moments of one cell in its LDS column (stride BLOCK): entry (t, v, i), t, i < N1, holds for
+// density and normal momentum the 1D moment p = i of the line t, and for the tangential momenta
+// the 2D moment j = N1 t + i (j < NB2), all of twice the flux
+template <typename T, int K>
+__device__ __forceinline__ int face_slot(int t, int v, int i)
+{
+    return ((t * 4 + v) * (K + 1) + i) * BLOCK;
+}
+
+// L_l += Lt_{e_D}(+-1) M_{d2(l)} (phi_l = Lt_{e_D}(+-1) P2_{d2(l)} on the face) with the sign of
+// the outward normal, from the 2D moments M of twice the flux of one variable
+template <typename T, int K, int D>
+__device__ __forceinline__ void lift_moments(const T (&M2)[Shape<K>::NB2], int s, ctab<T> *tab, T (&L)[Shape<K>::NB])
+{
+    constexpr Modes<K> M = make_modes<K>();
+    ctab<T> *lend = tab + TabLayout<K>::LEND;
+    const T sgn = s ? T(-0.5) : T(0.5);
+#pragma unroll
+    for (int l = 0; l < Shape<K>::NB; ++l) L[l] = fma(sgn * lend[2 * M.e[l][D] + s], M2[M.d2[D][l]], L[l]);
+}
+
+// adds a line's 1D moments m to the 2D moments: M_pq += w_t Lt_q(x_t) m_p (wl: the WLT row of t)
+template <typename T, int K>
+__device__ __forceinline__ void add_line(const T (&m)[K + 1], ctab<T> *wl, T (&M2)[Shape<K>::NB2])
+{
+#pragma unroll
+    for (int p = 0; p <= K; ++p)
+#pragma unroll
+        for (int q = 0; q <= K - p; ++q) M2[idx2(p, q)] = fma(m[p], wl[q], M2[idx2(p, q)]);
+}
+
+// the density and normal momentum part of a face's surface integral, from the column's line
+// moments
+template <typename T, int K, int D>
+__device__ __forceinline__ void lift_normal(const T *col, int s, ctab<T> *tab, T (&L)[4][Shape<K>::NB])
+{
+    using S = Shape<K>;
+    T M0[S::NB2], Mn[S::NB2];
+#pragma unroll
+    for (int j = 0; j < S::NB2; ++j) M0[j] = Mn[j] = T(0);
+#pragma unroll 1
+    for (int t = 0; t < S::N1; ++t) {
+        ctab<T> *wl = tab + TabLayout<K>::WLT + t * S::N1;
+        T m[S::N1];
+#pragma unroll
+        for (int p = 0; p < S::N1; ++p) m[p] = col[face_slot<T, K>(t, 0, p)];
+        add_line<T, K>(m, wl, M0);
+#pragma unroll
+        for (int p = 0; p < S::N1; ++p) m[p] = col[face_slot<T, K>(t, 1 + D, p)];
+        add_line<T, K>(m, wl, Mn);
+    }
+    lift_moments<T, K, D>(M0, s, tab, L[0]);
+    lift_moments<T, K, D>(Mn, s, tab, L[1 + D]);
+}
+
+// the whole surface integral of a face (normal axis D, side s: 0 = low, 1 = high) from the moments
+// in the LDS column of the cell that formed them
 template <typename T, int K, int D>
 __device__ __forceinline__ void lift(const T *col, int s, ctab<T> *tab, T (&L)[4][Shape<K>::NB])
 {
     using S = Shape<K>;
-    using TL = TabLayout<K>;
-    constexpr Modes<K> M = make_modes<K>();
-    T Mv[4][S::NB2];
+    lift_normal<T, K, D>(col, s, tab, L);
 #pragma unroll
-    for (int v = 0; v < 4; ++v)
+    for (int i = 0; i < 2; ++i) {
+        const int v = 1 + (i ? tan2(D) : tan1(D));
+        T M2[S::NB2];
 #pragma unroll
-        for (int j = 0; j < S::NB2; ++j) Mv[v][j] = T(0);
-#pragma unroll 1
-    for (int r = 0; r < S::NF; ++r) {
-        const T wr = s ? -tab[TL::FW + r] : tab[TL::FW + r];   // outward normal
-        ctab<T> *f2 = tab + TL::F2 + r * S::NB2;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const T g = wr * col[(r * 4 + v) * BLOCK];
-#pragma unroll
-            for (int j = 0; j < S::NB2; ++j) Mv[v][j] += g * f2[j];
-        }
-    }
-    ctab<T> *lend = tab + TL::LEND;
-#pragma unroll
-    for (int l = 0; l < S::NB; ++l) {
-        const T ls = lend[2 * M.e[l][D] + s];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) L[v][l] += ls * Mv[v][M.d2[D][l]];
+        for (int j = 0; j < S::NB2; ++j) M2[j] = col[face_slot<T, K>(j / S::N1, v, j % S::N1)];
+        lift_moments<T, K, D>(M2, s, tab, L[v]);
     }
 }
 
-// One face of the cell (normal axis D, side s): traces of the cell and its neighbour,
-// the numerical flux at every face point stored in the cell's LDS column col (where the
-// neighbour across a shared face reads it too), then lifted from there into L.
+// the weights of one variable of a trace field (its buffer r) in the cell at byte offset bo
+template <typename T, int K>
+__device__ __forceinline__ void load_modes(rsrc_t r, unsigned pstride, unsigned bo, T (&w)[Shape<K>::NB])
+{
+#pragma unroll
+    for (int l = 0; l < Shape<K>::NB; ++l) w[l] = bld<T>(r, bo, l * pstride);
+}
+
+// 2D face coefficients at the face (normal axis D, side s) of the cell with weights w: Lt_e(+-1)
+// along D, Lt_0 = 1 (the modes of e = 0 come first for every 2D mode)
 template <typename T, int K, int D>
-__device__ __forceinline__ void face(const Field<T, 4> &src, unsigned bo, unsigned bn, int s,
-                                     ctab<T> *tab, bool prim, bool use_hllc, T cs, T cs2,
-                                     T (&L)[4][Shape<K>::NB], T *col)
+__device__ __forceinline__ void collapse(const T (&w)[Shape<K>::NB], int s, ctab<T> *tab, T (&C)[Shape<K>::NB2])
+{
+    constexpr Modes<K> M = make_modes<K>();
+    ctab<T> *lend = tab + TabLayout<K>::LEND;
+#pragma unroll
+    for (int l = 0; l < Shape<K>::NB; ++l) {
+        const int e = M.e[l][D], j = M.d2[D][l];
+        C[j] = e == 0 ? w[l] : fma(w[l], lend[2 * e + s], C[j]);
+    }
+}
+
+// The normal part of one line of a face from the 2D coefficients of density and normal velocity
+// (prim off: momentum) of the cell (Co) and its neighbour (Cn): the line's values of twice the
+// mass and normal momentum flux, F0 and Fn, and the factors of the tangential velocities (of
+// the tangential momenta with prim off) of the two sides, go and gn.  s: 1 the cell is the low side.
+// p1: the basis values of the line's second tangential point.  PRIMSEL: prim when the caller's code
+// is compiled for one value of it (0, 1), or -1.
+template <typename T, int K, int PRIMSEL = -1, typename B>
+__device__ __forceinline__ void face_line_normal(const T (&Co)[2][Shape<K>::NB2], const T (&Cn)[2][Shape<K>::NB2],
+                                                 const B &p1, int s, bool prim, bool use_hllc, T cs, T cs2,
+                                                 T (&F0)[K + 1], T (&Fn)[K + 1], T (&go)[K + 1], T (&gn)[K + 1])
+{
+    constexpr int N1 = K + 1;
+    T ro[N1], rn[N1], vo[N1], vn[N1], c[N1];
+    face_line_coefficients<T, K>(Co[0], p1, c);
+    line_eval<K>(c, ro);
+    face_line_coefficients<T, K>(Cn[0], p1, c);
+    line_eval<K>(c, rn);
+    face_line_coefficients<T, K>(Co[1], p1, c);
+    line_eval<K>(c, vo);
+    face_line_coefficients<T, K>(Cn[1], p1, c);
+    line_eval<K>(c, vn);
+    // one branch per line and combination of options, each with its own straight code
+    auto fluxes = [&](auto pr, auto &&flux) {
+        auto point = [&](int r, auto low) {
+            T io, in;
+            if constexpr (!decltype(pr)::value) {
+                io = rcp(ro[r]);
+                in = rcp(rn[r]);
+                vo[r] *= io;
+                vn[r] *= in;
+            }
+            if constexpr (decltype(low)::value) flux(ro[r], vo[r], rn[r], vn[r], F0[r], Fn[r], go[r], gn[r]);
+            else flux(rn[r], vn[r], ro[r], vo[r], F0[r], Fn[r], gn[r], go[r]);
+            if constexpr (!decltype(pr)::value) {
+                go[r] *= io;
+                gn[r] *= in;
+            }
+            if constexpr (sizeof(T) == 8 && K == 3) __builtin_amdgcn_sched_barrier(0);
+        };
+        if (s)
+#pragma unroll
+            for (int r = 0; r < N1; ++r) point(r, std::true_type{});
+        else
+#pragma unroll
+            for (int r = 0; r < N1; ++r) point(r, std::false_type{});
+    };
+    auto solver = [&](auto pr) {
+        if (use_hllc)
+            fluxes(pr, [&](T rL, T vL, T rR, T vR, T &f0, T &fn, T &gL, T &gR) { hllc2(cs, cs2, rL, vL, rR, vR, f0, fn, gL, gR); });
+        else
+            fluxes(pr, [&](T rL, T vL, T rR, T vR, T &f0, T &fn, T &gL, T &gR) { rusanov2(cs, cs2, rL, vL, rR, vR, f0, fn, gL, gR); });
+    };
+    if constexpr (PRIMSEL >= 0) {
+        solver(std::integral_constant<bool, PRIMSEL == 1>{});
+    } else {
+        if (prim) solver(std::true_type{});
+        else solver(std::false_type{});
+    }
+}
+
+// The flux of one tangential momentum along a line from its 2D coefficients of both sides and
+// the line's factors
+template <typename T, int K, typename B>
+__device__ __forceinline__ void face_line_tangential(const T (&Co)[Shape<K>::NB2], const T (&Cn)[Shape<K>::NB2],
+                                                     const B &p1, int s, const T (&go)[K + 1], const T (&gn)[K + 1],
+                                                     T (&F)[K + 1])
+{
+    // the low side's product is the fused one, whichever side the cell is on
+#pragma clang fp contract(off)
+    T vn[K + 1], c[K + 1];
+    face_line_coefficients<T, K>(Co, p1, c);
+    line_eval<K>(c, F);
+    face_line_coefficients<T, K>(Cn, p1, c);
+    line_eval<K>(c, vn);
+    if (s)
+#pragma unroll
+        for (int r = 0; r <= K; ++r) F[r] = fma(go[r], F[r], gn[r] * vn[r]);
+    else
+#pragma unroll
+        for (int r = 0; r <= K; ++r) F[r] = fma(gn[r], vn[r], go[r] * F[r]);
+}
+
+// 2D moments M of one tangential momentum's flux from its 2D coefficients of both sides and the
+// factors in the column
+template <typename T, int K, int D>
+__device__ __forceinline__ void face_tangential(const T (&Co)[Shape<K>::NB2], const T (&Cn)[Shape<K>::NB2], int s,
+                                                ctab<T> *tab, const T *col, T (&M2)[Shape<K>::NB2])
 {
     using S = Shape<K>;
     using TL = TabLayout<K>;
-    constexpr Modes<K> M = make_modes<K>();
-    T Co[4][S::NB2], Cn[4][S::NB2];
+    constexpr int N1 = S::N1;
 #pragma unroll
-    for (int v = 0; v < 4; ++v)
+    for (int j = 0; j < S::NB2; ++j) M2[j] = T(0);
+#pragma unroll 1
+    for (int t = 0; t < N1; ++t) {
+        T go[N1], gn[N1], F[N1], m[N1];
 #pragma unroll
-        for (int j = 0; j < S::NB2; ++j) { Co[v][j] = T(0); Cn[v][j] = T(0); }
-    // collapse the 3D expansions onto the face: Lt_e(+-1) along D
-    ctab<T> *lend = tab + TL::LEND;
+        for (int r = 0; r < N1; ++r) {
+            go[r] = col[face_slot<T, K>(t, 1 + tan1(D), r)];
+            gn[r] = col[face_slot<T, K>(t, 1 + tan2(D), r)];
+        }
+        face_line_tangential<T, K>(Co, Cn, tab + TL::P1 + t * N1, s, go, gn, F);
+        line_moments<K>(F, m);
+        add_line<T, K>(m, tab + TL::WLT + t * N1, M2);
+    }
+}
+
+// One face of the cell (normal axis D, side s): traces of the cell and its neighbour, the
+// numerical flux at the points of one line of the face after the other, its moments in the
+// cell's LDS column col (where the neighbour across a shared face reads them too) and their lift
+// into L.  Line by line the traces cost 21 multiply-adds per variable and side at degree 2 (54
+// with the 2D basis at every point), the moments 39 per variable (63).  The density and the
+// normal velocity go first, then each tangential velocity (the tangential places of the column
+// hold the factors g of the points meanwhile): the 2D coefficients of all four variables of both
+// sides would not fit the registers beside the accumulators (FP64 at degree 2 spilled 13
+// accumulators, 0.74 -> 0.90 ms per 64^3 step).  What remains is the latency of the trace loads:
+// the density's and the normal velocity's go out together, each tangential velocity's while the
+// variables before it are worked on.
+template <typename T, int K, int D>
+__device__ __forceinline__ void face(const Field<T, 4> &src, unsigned bo, unsigned bn, int s, ctab<T> *tab, bool prim,
+                                     bool use_hllc, T cs, T cs2, T (&L)[4][Shape<K>::NB], T *col)
+{
+    using S = Shape<K>;
+    using TL = TabLayout<K>;
+    constexpr int N1 = S::N1, T1 = 1 + tan1(D), T2 = 1 + tan2(D);
+    // (the first tangential velocity's only where they fit beside both variables before it)
+    constexpr bool AHEAD = K != 2;
+    T wo[S::NB], wn[S::NB];
+    {
+        T Co[2][S::NB2], Cn[2][S::NB2];
+        T w[4][S::NB];
 #pragma unroll
-    for (int v = 0; v < 4; ++v)
+        for (int i = 0; i < 2; ++i) {
+            load_modes<T, K>(src.r[i ? 1 + D : 0], src.pstride, bo, w[2 * i]);
+            load_modes<T, K>(src.r[i ? 1 + D : 0], src.pstride, bn, w[2 * i + 1]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int l = 0; l < S::NB; ++l) {
-            const int e = M.e[l][D];
-            const T wo = src.get(v, l, bo);
-            const T wn = src.get(v, l, bn);
-            Co[v][M.d2[D][l]] += wo * lend[2 * e + s];
-            Cn[v][M.d2[D][l]] += wn * lend[2 * e + 1 - s];
-            // keep at most one variable's loads in flight (register pressure)
-            if (l == S::NB - 1) __builtin_amdgcn_sched_barrier(0);
+        for (int i = 0; i < 2; ++i) {
+            collapse<T, K, D>(w[2 * i], s, tab, Co[i]);
+            collapse<T, K, D>(w[2 * i + 1], 1 - s, tab, Cn[i]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (AHEAD) {
+            load_modes<T, K>(src.r[T1], src.pstride, bo, wo);
+            load_modes<T, K>(src.r[T1], src.pstride, bn, wn);
+            __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll 1
-    for (int r = 0; r < S::NF; ++r) {
-        ctab<T> *f2 = tab + TL::F2 + r * S::NB2;
-        T uo[4], un[4], vo[3], vn[3];
-        T ao[4] = {T(0), T(0), T(0), T(0)}, an[4] = {T(0), T(0), T(0), T(0)};
+        for (int t = 0; t < N1; ++t) {
+            T F0[N1], Fn[N1], go[N1], gn[N1], m[N1];
+            face_line_normal<T, K>(Co, Cn, tab + TL::P1 + t * N1, s, prim, use_hllc, cs, cs2, F0, Fn, go, gn);
+            line_moments<K>(F0, m);
 #pragma unroll
-        for (int j = 0; j < S::NB2; ++j) {
-            const T f = f2[j];
+            for (int p = 0; p < N1; ++p) col[face_slot<T, K>(t, 0, p)] = m[p];
+            line_moments<K>(Fn, m);
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                ao[v] += Co[v][j] * f;
-                an[v] += Cn[v][j] * f;
+            for (int p = 0; p < N1; ++p) col[face_slot<T, K>(t, 1 + D, p)] = m[p];
+#pragma unroll
+            for (int r = 0; r < N1; ++r) {
+                col[face_slot<T, K>(t, T1, r)] = go[r];
+                col[face_slot<T, K>(t, T2, r)] = gn[r];
             }
         }
-        uo[0] = ao[0];
-        un[0] = an[0];
-        if (prim) {
-#pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                vo[d] = ao[1 + d]; uo[1 + d] = ao[0] * ao[1 + d];
-                vn[d] = an[1 + d]; un[1 + d] = an[0] * an[1 + d];
-            }
-        } else {
-            const T io = rcp(ao[0]), in = rcp(an[0]);
-#pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                uo[1 + d] = ao[1 + d]; vo[d] = ao[1 + d] * io;
-                un[1 + d] = an[1 + d]; vn[d] = an[1 + d] * in;
-            }
-        }
-        T F[4];
-        if (use_hllc) {
-            if (s) hllc<D>(cs, cs2, uo, vo, un, vn, F);
-            else   hllc<D>(cs, cs2, un, vn, uo, vo, F);
-        } else {
-            if (s) rusanov<D>(cs, cs2, uo, vo, un, vn, F);
-            else   rusanov<D>(cs, cs2, un, vn, uo, vo, F);
-        }
-#pragma unroll
-        for (int v = 0; v < 4; ++v) col[(r * 4 + v) * BLOCK] = F[v];
     }
-    lift<T, K, D>(col, s, tab, L);
+    T Co[S::NB2], Cn[S::NB2], M1[S::NB2], M2[S::NB2];
+    if constexpr (!AHEAD) {
+        __builtin_amdgcn_sched_barrier(0);
+        load_modes<T, K>(src.r[T1], src.pstride, bo, wo);
+        load_modes<T, K>(src.r[T1], src.pstride, bn, wn);
+    }
+    collapse<T, K, D>(wo, s, tab, Co);
+    collapse<T, K, D>(wn, 1 - s, tab, Cn);
+    __builtin_amdgcn_sched_barrier(0);
+    load_modes<T, K>(src.r[T2], src.pstride, bo, wo);
+    load_modes<T, K>(src.r[T2], src.pstride, bn, wn);
+    __builtin_amdgcn_sched_barrier(0);
+    face_tangential<T, K, D>(Co, Cn, s, tab, col, M1);
+    lift_moments<T, K, D>(M1, s, tab, L[T1]);
+    collapse<T, K, D>(wo, s, tab, Co);
+    collapse<T, K, D>(wn, 1 - s, tab, Cn);
+    __builtin_amdgcn_sched_barrier(0);
+    face_tangential<T, K, D>(Co, Cn, s, tab, col, M2);
+    lift_moments<T, K, D>(M2, s, tab, L[T2]);
+#pragma unroll
+    for (int j = 0; j < S::NB2; ++j) {
+        col[face_slot<T, K>(j / N1, T1, j % N1)] = M1[j];
+        col[face_slot<T, K>(j / N1, T2, j % N1)] = M2[j];
+    }
+    lift_normal<T, K, D>(col, s, tab, L);
 }
 
 // ------------------------------------------------------------ driving field
@@ -672,6 +844,40 @@ __device__ __forceinline__ void pencil_accel(ctab<T> *ft, ctab<T> *g, int q, T p
 #pragma unroll
     for (int d = 0; d < 3; ++d)
         acc[d] = fma(-e[5 * d + 4], x2i, fma(e[5 * d + 3], x2r, fma(-e[5 * d + 2], xi, fma(e[5 * d + 1], xr, e[5 * d]))));
+}
+
+// the same for the points of a line along z, which share t_x: the phase X and its square once,
+// then a at the point pair tt = t_y + N1 t_z (sg = -1: the mirrored t_x, E_t conjugate)
+template <typename T, int K>
+__device__ __forceinline__ void line_phase(ctab<T> *ft, int tx, T pr, T pim, T sg, T &xr, T &xi, T &x2r, T &x2i)
+{
+#pragma clang fp contract(off)
+    const T er = ft[2 * tx], ei = sg * ft[2 * tx + 1];
+    xr = fma(pr, er, -(pim * ei));
+    xi = fma(pr, ei, pim * er);
+    x2r = fma(xr, xr, -(xi * xi));
+    x2i = (T(2) * xr) * xi;
+}
+
+template <typename T, int K>
+__device__ __forceinline__ void line_accel(ctab<T> *g, int tt, T xr, T xi, T x2r, T x2i, T (&acc)[3])
+{
+#pragma clang fp contract(off)
+    ctab<T> *e = g + tt * PencilLayout<K>::ENT;
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+        acc[d] = fma(-e[5 * d + 4], x2i, fma(e[5 * d + 3], x2r, fma(-e[5 * d + 2], xi, fma(e[5 * d + 1], xr, e[5 * d]))));
+}
+
+// the driving source of one volume point times h/2, s = (rho h/2) a, with its roundings fixed
+template <typename T>
+__device__ __forceinline__ void drive_source(T rho, T half_h, const T (&ac)[3], T &s0, T &s1, T &s2)
+{
+#pragma clang fp contract(off)
+    const T rh = rho * half_h;
+    s0 = rh * ac[0];
+    s1 = rh * ac[1];
+    s2 = rh * ac[2];
 }
 
 // a at the point with reference coordinates xi of cell (i, j, l), mode by mode (any table)
@@ -998,13 +1204,32 @@ __device__ __forceinline__ void volume_mfma(const RhsArgs &a, ctab<float> *tab, 
 // ------------------------------------------------------------------ RHS kernel
 // dw/dt = (1/(4h)) [ sum_q w_q grad_xi(phi) . F(q) - sum_faces +- sum_r w_r phi F*(r) ]
 //         + (1/8) sum_q w_q phi rho a (Sec. 2.2 weight evolution; Sec. 3.1; Sec. 4.2)
+// Line by line (dg_line.hpp) in the volume and on the faces: with the 3D basis tables at every point
+// the FP64 degree-2 kernel issued 12,700 vector instructions per wave and loaded 22 table values
+// per point.  Measured before and after, per step, with the two-lane kernel below in the same form:
+// 256^3 degree 2 FP64 38.7 -> 32.5 ms, 128^3 degree 3 FP32 9.41 -> 6.13 ms, 128^3 degree 2 FP32 with
+// the learned sensor 3.16 -> 2.75 ms, 64^3 degree 2 FP64 0.747 -> 0.616 ms, 128^3 degree 3 FP64 22.9
+// -> 21.5 ms, 33x20x27 degree 2 FP32 0.247 -> 0.191 ms, 16^3 degree 1 FP64 79 -> 68 us.
 // occupancy target (waves per SIMD) of the right-hand-side kernel: the register file
 // holds the 4 NB coefficients and 4 NB accumulators of a cell per lane, so FP64 fits two
-// waves and FP32 four (two at degree 3) without spilling.  FP64 at degree 3 (160 values
-// of coefficients and accumulators) cannot fit 256 VGPRs: one wave per SIMD lets the
-// compiler keep the overflow in accumulation registers instead of scratch memory.
+// waves and FP32 four (two at degree 3).  FP64 at degree 3 takes the two-lane kernel.
 template <typename T, int K, bool VMFMA = false>
 constexpr int rhs_waves() { return VMFMA ? MFMA_WAVES : (sizeof(T) == 8 ? (K <= 2 ? 2 : 1) : (K <= 2 ? 4 : 2)); }
+
+// Whether the momentum weights wait in the block's LDS (the face columns, unused until the surface
+// integral) during the volume integral instead of in registers: FP32 at degree 2, whose 4 waves
+// per SIMD leave 128 registers (33 spilled without it; 3 waves without spills measured 2.79
+// against 2.71 ms per 128^3 step, though 0.188 against 0.190 ms at 33x20x27).  FP64 at degree 2
+// and FP32 at degree 3 fit (605 against 600 us per 64^3 step, 6.24 against 6.14 ms at 128^3).
+template <typename T, int K>
+constexpr bool momentum_in_lds() { return sizeof(T) == 4 && K == 2; }
+
+// a lane's column of LDS values, stride ST
+template <typename T, int ST>
+struct LdsColumn {
+    const T *p;
+    __device__ __forceinline__ T operator[](int l) const { return p[l * ST]; }
+};
 
 template <typename T, int K, bool UNV>
 __device__ __forceinline__ void rhs_combination(const void *ui, T (&L)[4][Shape<K>::NB], T inv4h, double dt,
@@ -1021,9 +1246,10 @@ k_rhs(RhsArgs a, StageArgs st)
     using S = Shape<K>;
     using TL = TabLayout<K>;
     constexpr Modes<K> M = make_modes<K>();
-    constexpr int NB = S::NB, ND = S::ND;
+    constexpr int NB = S::NB;
+    constexpr bool MLDS = momentum_in_lds<T, K>() && !VMFMA;
     __shared__ double lds[4 * 4];
-    __shared__ T fsh[S::NF * 4 * BLOCK];        // point fluxes of the low faces, [r][v][thread]
+    __shared__ T fsh[S::NF * 4 * BLOCK];        // face moments, a column per cell (face_slot)
     ctab<T> *tab = as_tab<T>(a.tab);
     const int nc = a.g.nc;
     const int blk = plane_tiled(xcd_remap(blockIdx.x, gridDim.x), a.bpp, a.g.nz, a.zt);
@@ -1063,6 +1289,12 @@ k_rhs(RhsArgs a, StageArgs st)
         W[0][0] = U.get(0, 0, bo);
     }
 
+    if constexpr (MLDS)
+#pragma unroll
+        for (int v = 1; v < 4; ++v)
+#pragma unroll
+            for (int l = 0; l < NB; ++l) fsh[((v - 1) * NB + l) * BLOCK + threadIdx.x] = W[v][l];
+
     ctab<T> *ft = as_tab<T>(a.ftab);
 
     // divergence of the projected velocity (Sec. 3.1) as a degree-(K-1) polynomial:
@@ -1085,6 +1317,8 @@ k_rhs(RhsArgs a, StageArgs st)
                     for (int t = 0; t < DivMap<K>::MAXT; ++t)
                         if (DM.m[d][l][t] >= 0) Dv[DM.m[d][l][t]] += v * T(__builtin_sqrt(double(DM.f[d][l][t])));
                 }
+#pragma unroll
+        for (int m = 0; m < NDIV; ++m) Dv[m] *= two_h;
         if (a.flags & F_LEARNED) {
             learned = a.fb[c] == 0;
             nu = ((const T *)a.nu)[c];
@@ -1104,77 +1338,146 @@ k_rhs(RhsArgs a, StageArgs st)
     T pr = T(0), pim = T(0);
     if (force && !FDIRECT) cell_phase<T>(ft + PencilLayout<K>::phases(a.g.ny, a.g.nz), cijk[0], pr, pim);
 
-    // ---- volume integral
+    // ---- volume integral, line by line along z: the four variables at the points of a line, the
+    // momentum flux tensor there, and its moments along the line into the weights
     auto volume = [&](auto form, int pen) {
         constexpr int FM = decltype(form)::value;
+        constexpr int N1 = S::N1, NL = TL::NL;
         ctab<T> *g = ft + PencilLayout<K>::HDR + (size_t)pen * PencilLayout<K>::STRIDE;
 #pragma unroll 1
-        for (int q = 0; q < S::NQ; ++q) {
-            ctab<T> *ph = tab + TL::VPHI + q * NB;
-            ctab<T> *dph = tab + TL::VDPHI + q * 3 * ND;
-            const T wq = tab[TL::VW + q];
-            T rho = T(0), m[3] = {T(0), T(0), T(0)};
+        for (int r = 0; r < S::NF; ++r) {
+            ctab<T> *phi2 = tab + TL::F2 + r * S::NB2;
+            T x[4][N1], c[N1];
+            line_coefficients<T, K, K + 1>(W[0], phi2, c);
+            line_eval<K>(c, x[0]);
+            if constexpr (MLDS) {
+                // (the offset is opaque, or the compiler would keep the loop-invariant weights in
+                // registers after all)
+                int o = threadIdx.x;
+                asm volatile("" : "+v"(o));
 #pragma unroll
-            for (int l = 0; l < NB; ++l) {
-                const T p = ph[l];
-                rho += W[0][l] * p;
-                m[0] += W[1][l] * p;
-                m[1] += W[2][l] * p;
-                m[2] += W[3][l] * p;
+                for (int v = 1; v < 4; ++v) {
+                    line_coefficients<T, K, K + 1>(LdsColumn<T, BLOCK>{fsh + (v - 1) * NB * BLOCK + o}, phi2, c);
+                    line_eval<K>(c, x[v]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            } else {
+#pragma unroll
+                for (int v = 1; v < 4; ++v) {
+                    line_coefficients<T, K, K + 1>(W[v], phi2, c);
+                    line_eval<K>(c, x[v]);
+                }
             }
-            T pi = T(0);
+            T div[N1];
             if (av) {
-                T div = T(0);
-#pragma unroll
-                for (int mm = 0; mm < NDIV; ++mm) div += Dv[mm] * ph[mm];
-                div *= two_h;
-                const T pv = vnr_pi<T>(rho, div, hp, alpha, beta, cs, inv_dt);
-                // learned sensor: the cell's bulk viscosity nu in place of the vNR one,
-                // Pi = rho nu s at compressed points, with the Pi_max cap of the point
-                const T sq = -div;
-                T pl = fmin(rho * nu * sq, T(0.5) * rho * hp * hp * sq * inv_dt);
-                pl = (sq > T(0) && nu > T(0)) ? pl : T(0);
-                pi = learned ? pl : pv;
+                T cd[K];
+                line_coefficients<T, K, K>(Dv, phi2, cd);
+                line_eval<K>(cd, div);
             }
-            const T ir = rcp(rho);
-            const T pw = (cs2 * rho + pi) * wq;
+            ctab<T> *lw = tab + TL::LWP + r * S::NB2, *lx = tab + TL::LWX + r * NL, *ly = tab + TL::LWY + r * NL;
+            // the tensor's moments below degree K into the weights with an x or y exponent, and the
+            // z fluxes' derivative moments d
+            T d[3][N1];
+            {
+                // the tensor at a point: xx, xy, xz, yy, yz, zz
+                auto tensor = [&](int t, T (&F)[6]) {
+                    const T rho = x[0][t];
+                    T pi = T(0);
+                    if (av) {
+                        const T pv = vnr_pi<T>(rho, div[t], hp, alpha, beta, cs, inv_dt);
+                        // learned sensor: the cell's bulk viscosity nu in place of the vNR one,
+                        // Pi = rho nu s at compressed points, with the Pi_max cap of the point
+                        const T sq = -div[t];
+                        T pl = fmin(rho * nu * sq, T(0.5) * rho * hp * hp * sq * inv_dt);
+                        pl = (sq > T(0) && nu > T(0)) ? pl : T(0);
+                        pi = learned ? pl : pv;
+                    }
+                    const T ir = rcp(rho);
+                    const T pw = cs2 * rho + pi;
+                    const T vx = x[1][t] * ir, vy = x[2][t] * ir, vz = x[3][t] * ir;
+                    F[0] = x[1][t] * vx + pw;
+                    F[1] = x[1][t] * vy;
+                    F[2] = x[1][t] * vz;
+                    F[3] = x[2][t] * vy + pw;
+                    F[4] = x[2][t] * vz;
+                    F[5] = x[3][t] * vz + pw;
+                };
+                T m[6][K];
+                auto step = [&](auto ps) {
+                    constexpr int P = decltype(ps)::value;
+                    T lo[6], hi[6];
+                    if constexpr (2 * P < K) tensor(P, lo);
+                    tensor(K - P, hi);
 #pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                const T md = m[d] * wq;
-                const T mdr = md * ir;
-                T F[4];
-                F[0] = md;
-                F[1] = mdr * m[0];
-                F[2] = mdr * m[1];
-                F[3] = mdr * m[2];
-                F[1 + d] += pw;
+                    for (int j = 0; j < 6; ++j) line_moments_step<K, K, P>(lo[j], hi[j], m[j]);
+                    __builtin_amdgcn_sched_barrier(0);
+                };
+                step(std::integral_constant<int, 0>{});
+                if constexpr (K > 1) step(std::integral_constant<int, 1>{});
+                auto row = [&](T (&Lv)[NB], const T (&fx)[K], const T (&fy)[K]) {
 #pragma unroll
-                for (int l = 0; l < NB; ++l) {
-                    if (M.dj[d][l] < 0) continue;
-                    const T dp = dph[d * ND + M.dj[d][l]];
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) L[v][l] += dp * F[v];
-                }
+                    for (int l = 0; l < NB; ++l) {
+                        const int ea = M.e[l][0], eb = M.e[l][1], ec = M.e[l][2];
+                        if (ea) Lv[l] = fma(lx[line_dx(ea, eb)], fx[ec], Lv[l]);
+                        if (eb) Lv[l] = fma(ly[line_dy(ea, eb)], fy[ec], Lv[l]);
+                    }
+                };
+                row(L[1], m[0], m[1]);
+                row(L[2], m[1], m[3]);
+                row(L[3], m[2], m[4]);
+                line_derivative<K>(m[2], d[0]);
+                line_derivative<K>(m[4], d[1]);
+                line_derivative<K>(m[5], d[2]);
             }
+            __builtin_amdgcn_sched_barrier(0);
+            // the driving source's moments and d into the weights
             if (force) {
-                T ac[3];
-                if constexpr (FM == FM_DIRECT)
-                    direct_accel<T>(a.modes, a.nmodes, cijk, tab[TL::VXI + 3 * q], tab[TL::VXI + 3 * q + 1],
-                                    tab[TL::VXI + 3 * q + 2], a.h, ac);
-                else
-                    pencil_accel<T, K>(ft, g, q, pr, pim, ac);
-                T sp[3];
-                drive_point<T>(rho, wq, ac, sp, fs0, fs1, fs2);
-                const T t0 = sp[0] * half_h, t1 = sp[1] * half_h, t2 = sp[2] * half_h;
+                T sr[3][N1];
+                T xr = T(0), xi = T(0), x2r = T(0), x2i = T(0);
+                if constexpr (FM != FM_DIRECT) line_phase<T, K>(ft, r % N1, pr, pim, T(1), xr, xi, x2r, x2i);
 #pragma unroll
-                for (int l = 0; l < NB; ++l) {
-                    const T p = ph[l];
-                    L[1][l] += t0 * p;
-                    L[2][l] += t1 * p;
-                    L[3][l] += t2 * p;
+                for (int t = 0; t < N1; ++t) {
+                    const int q = r + S::NF * t;
+                    T ac[3];
+                    if constexpr (FM == FM_DIRECT)
+                        direct_accel<T>(a.modes, a.nmodes, cijk, tab[TL::VXI + 3 * q], tab[TL::VXI + 3 * q + 1],
+                                        tab[TL::VXI + 3 * q + 2], a.h, ac);
+                    else
+                        line_accel<T, K>(g, r / N1 + N1 * t, xr, xi, x2r, x2i, ac);
+                    drive_source<T>(x[0][t], half_h, ac, sr[0][t], sr[1][t], sr[2][t]);
                 }
+#pragma unroll
+                for (int v = 0; v < 3; ++v) {
+                    T z[N1];
+                    line_moments<K>(sr[v], z);
+                    T &fs = v == 0 ? fs0 : (v == 1 ? fs1 : fs2);
+                    fs = fma(lw[0], z[0], fs);
+#pragma unroll
+                    for (int n = 1; n < N1; ++n) z[n] += d[v][n];
+#pragma unroll
+                    for (int l = 0; l < NB; ++l) L[1 + v][l] = fma(lw[M.d2[2][l]], z[M.e[l][2]], L[1 + v][l]);
+                }
+            } else {
+#pragma unroll
+                for (int v = 0; v < 3; ++v)
+#pragma unroll
+                    for (int l = 0; l < NB; ++l)
+                        if (M.e[l][2]) L[1 + v][l] = fma(lw[M.d2[2][l]], d[v][M.e[l][2]], L[1 + v][l]);
             }
         }
+        // the density row, sum_q w_q d_d(phi_l) m_d, is linear in the momentum and the quadrature
+        // exact for it: 8 sum_t sqrt(f_t) W_{1+d, m_t} by the derivative identity
+#pragma unroll
+        for (int d = 0; d < 3; ++d)
+#pragma unroll
+            for (int l = 0; l < NB; ++l)
+#pragma unroll
+                for (int t = 0; t < DivMap<K>::MAXT; ++t)
+                    if (DM.m[d][l][t] >= 0) {
+                        const int m = DM.m[d][l][t];
+                        const T w = MLDS ? fsh[(d * NB + m) * BLOCK + threadIdx.x] : W[1 + d][m];
+                        L[0][l] = fma(T(8.0 * __builtin_sqrt(double(DM.f[d][l][t]))), w, L[0][l]);
+                    }
     };
     if constexpr (VMFMA) {
         static_assert(sizeof(T) == 4 && K == 2 && !FDIRECT, "matrix-core volume integral: FP32, degree 2");
@@ -1249,8 +1552,9 @@ k_rhs(RhsArgs a, StageArgs st)
         }
         if (force && a.part) {
             const bool fsok = active || VMFMA;     // the matrix-core sums are masked per tile cell
-            double acc[4] = {fsok ? 0.125 * (double)fs0 : 0.0, fsok ? 0.125 * (double)fs1 : 0.0,
-                             fsok ? 0.125 * (double)fs2 : 0.0, active ? (double)mass0 : 0.0};
+            const double fsc = VMFMA ? 0.125 : 0.125 / (double)half_h;   // the line sums carry h/2
+            double acc[4] = {fsok ? fsc * (double)fs0 : 0.0, fsok ? fsc * (double)fs1 : 0.0,
+                             fsok ? fsc * (double)fs2 : 0.0, active ? (double)mass0 : 0.0};
             block_sum<4>(acc, lds);
             if (threadIdx.x == 0)
 #pragma unroll
@@ -1260,16 +1564,11 @@ k_rhs(RhsArgs a, StageArgs st)
 }
 
 // ------------------------------------------- RHS kernel, FP64, two lanes per cell
-// The FP64 kernel above keeps all 4 NB coefficients and 4 NB accumulators of a cell in one
+// The FP64 kernel above keeps the 4 NB coefficients and 4 NB accumulators of a cell in one
 // lane, which at degree 3 fits only one wave per SIMD.  Here the lanes 2i and 2i+1 of a wave share
-// cell i: lane h owns variables 2h and 2h+1 (coefficients, accumulators, face traces), and
-// the partner's point values come across in registers (a DPP lane swap).  The flux at a
-// point, which needs all four variables, is formed in both lanes; each lane contracts and
-// lifts its own two variables.  Buffer resources are uniform over the wave: a lane reaches
-// its variable 2h+i through the buffer of variable i and a lane offset of two variable
-// blocks (LSEL: when that offset fits 32 bits, with the projected traces read from one
-// array that holds a copy of the density weights in front of the projected velocity);
-// otherwise it loads variables i and 2+i and keeps its own.
+// cell i: the cell's weights wait in LDS, the lanes share the lines of points of the volume and
+// of every face (lane 1 takes the mirror images of lane 0's lines), and lane h owns the rows of
+// the variables 2h and 2h+1 in the result.
 
 // the value held by the other lane of the pair (lane ^ 1)
 __device__ __forceinline__ double pair_swap(double x)
@@ -1280,20 +1579,9 @@ __device__ __forceinline__ double pair_swap(double x)
     return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
 }
 
-// all four variables from the own pair (a0, a1) and the partner's pair (b0, b1): lane 0
-// owns variables 0 and 1, lane 1 variables 2 and 3
-__device__ __forceinline__ void pair_assemble(int h, double a0, double a1, double b0, double b1, double (&x)[4])
-{
-    x[0] = h ? b0 : a0;
-    x[1] = h ? b1 : a1;
-    x[2] = h ? a0 : b0;
-    x[3] = h ? a1 : b1;
-}
-
-// Surface integral of one face (normal axis D, side s) from the point fluxes in an LDS column
-// (col: the column of the cell that stored them, [r][v] with stride CB): the flux moments
-// against the 2D basis of the face, M_j = sum_r w_r F(r) P2_j(r), then per mode
-// phi_l = Lt_{e_D}(+-1) P2_{d2(l)} on the face
+// Surface integral of one face (normal axis D, side s) for the lane's two variables from the
+// line moments in an LDS column, as lift does (col: the column of the cell that stored them,
+// [line][v][p] with stride CB, of twice the flux)
 template <int K, int D, int CB>
 __device__ __forceinline__ void lift_pair(const double *col, int h, int s, ctab<double> *tab,
                                           double (&L)[2][Shape<K>::NB])
@@ -1307,124 +1595,140 @@ __device__ __forceinline__ void lift_pair(const double *col, int h, int s, ctab<
 #pragma unroll
         for (int j = 0; j < S::NB2; ++j) M2[i][j] = 0.0;
 #pragma unroll 1
-    for (int r = 0; r < S::NF; ++r) {
-        const double wr = s ? -tab[TL::FW + r] : tab[TL::FW + r];   // outward normal
-        ctab<double> *f2 = tab + TL::F2 + r * S::NB2;
-        const double g0 = wr * col[(r * 4 + 2 * h) * CB];
-        const double g1 = wr * col[(r * 4 + 2 * h + 1) * CB];
+    for (int t = 0; t < S::N1; ++t) {
+        ctab<double> *wl = tab + TL::WLT + t * (K + 1);
 #pragma unroll
-        for (int j = 0; j < S::NB2; ++j) {
-            M2[0][j] += g0 * f2[j];
-            M2[1][j] += g1 * f2[j];
-        }
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int p = 0; p <= K; ++p) {
+                const double m = col[((t * 4 + 2 * h + i) * S::N1 + p) * CB];
+#pragma unroll
+                for (int q = 0; q <= K - p; ++q) M2[i][idx2(p, q)] += m * wl[q];
+            }
     }
     ctab<double> *lend = tab + TL::LEND;
+    const double sgn = s ? -0.5 : 0.5;
 #pragma unroll
     for (int l = 0; l < S::NB; ++l) {
-        const double ls = lend[2 * M.e[l][D] + s];
+        const double ls = sgn * lend[2 * M.e[l][D] + s];
         L[0][l] += ls * M2[0][M.d2[D][l]];
         L[1][l] += ls * M2[1][M.d2[D][l]];
     }
 }
 
-// one face of the cell for the lane's two variables; src[i] points at variable 2h+i of
-// the trace field (mode planes nc apart), c and cn the own and the neighbour cell
-template <int K, int D, int CB, bool LSEL>
+// 2D coefficients at the face of the variables v0 and v1 of the cell (bo) and its neighbour
+// (bn), one side's loads of one variable in flight at a time (register pressure)
+template <int K, int D>
+__device__ __forceinline__ void face_traces(const Field<double, 4> &src, int v0, int v1, unsigned bo, unsigned bn, int s,
+                                            ctab<double> *tab, double (&Co)[2][Shape<K>::NB2],
+                                            double (&Cn)[2][Shape<K>::NB2])
+{
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        double w[Shape<K>::NB];
+        load_modes<double, K>(src.r[i ? v1 : v0], src.pstride, bo, w);
+        collapse<double, K, D>(w, s, tab, Co[i]);
+        __builtin_amdgcn_sched_barrier(0);
+        load_modes<double, K>(src.r[i ? v1 : v0], src.pstride, bn, w);
+        collapse<double, K, D>(w, 1 - s, tab, Cn[i]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// One face of the cell by its two lanes, as face does.  The lanes share the lines of the face, not
+// the variables: line i of lane 1 is the mirror image of lane 0's line i (basis values with the
+// sign of the odd degrees flipped), and a lane forms all four fluxes of its lines, so nothing is
+// computed twice and nothing crosses lanes but through the column, from which each lane then
+// lifts its own two variables.  (With the variables split, every point value crossed lanes and
+// both lanes formed every flux.)
+template <int K, int D, int CB, bool PRIM>
 __device__ __forceinline__ void face_pair(const Field<double, 4> &src, unsigned bo, unsigned bn, int s, int h,
-                                          unsigned hoff, ctab<double> *tab, bool prim, bool use_hllc, double cs,
-                                          double cs2, double (&L)[2][Shape<K>::NB], double *col)
+                                          ctab<double> *tab, bool use_hllc, double cs, double cs2,
+                                          double (&L)[2][Shape<K>::NB], double *col)
 {
     using S = Shape<K>;
     using TL = TabLayout<K>;
-    constexpr Modes<K> M = make_modes<K>();
+    constexpr int N1 = S::N1, T1 = 1 + tan1(D), T2 = 1 + tan2(D);
+    static_assert(N1 % 2 == 0, "the two lanes share the lines");
     double Co[2][S::NB2], Cn[2][S::NB2];
+    auto line = [&](int i, double (&p1)[N1]) {
+        ctab<double> *row = tab + TL::P1 + i * N1;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < S::NB2; ++j) { Co[i][j] = 0.0; Cn[i][j] = 0.0; }
-    ctab<double> *lend = tab + TL::LEND;
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int l = 0; l < S::NB; ++l) {
-            const int e = M.e[l][D];
-            double wo, wn;
-            if constexpr (LSEL) {
-                // variable 2h+i: the buffer of variable i, two variable blocks further in lane 1
-                wo = src.get(i, l, bo + hoff);
-                wn = src.get(i, l, bn + hoff);
-            } else {
-                // through the uniform per-variable buffers: both candidates, then the lane's own
-                const double wo0 = src.get(i, l, bo), wo1 = src.get(2 + i, l, bo);
-                const double wn0 = src.get(i, l, bn), wn1 = src.get(2 + i, l, bn);
-                wo = h ? wo1 : wo0;
-                wn = h ? wn1 : wn0;
-            }
-            Co[i][M.d2[D][l]] += wo * lend[2 * e + s];
-            Cn[i][M.d2[D][l]] += wn * lend[2 * e + 1 - s];
-            // keep at most one variable's loads in flight (register pressure)
-            if (l == S::NB - 1) __builtin_amdgcn_sched_barrier(0);
-        }
+        for (int q = 0; q < N1; ++q) p1[q] = (q & 1) && h ? -row[q] : row[q];
+        return col + (h ? N1 - 1 - i : i) * (4 * N1 * CB);
+    };
+    face_traces<K, D>(src, 0, 1 + D, bo, bn, s, tab, Co, Cn);
 #pragma unroll 1
-    for (int r = 0; r < S::NF; ++r) {
-        ctab<double> *f2 = tab + TL::F2 + r * S::NB2;
-        double ao[2] = {0.0, 0.0}, an[2] = {0.0, 0.0};
+    for (int i = 0; i < N1 / 2; ++i) {
+        double p1[N1], F0[N1], Fn[N1], go[N1], gn[N1], m[N1];
+        double *o = line(i, p1);
+        face_line_normal<double, K, PRIM>(Co, Cn, p1, s, PRIM, use_hllc, cs, cs2, F0, Fn, go, gn);
+        line_moments<K>(F0, m);
 #pragma unroll
-        for (int j = 0; j < S::NB2; ++j) {
-            const double f = f2[j];
+        for (int p = 0; p < N1; ++p) o[p * CB] = m[p];
+        line_moments<K>(Fn, m);
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                ao[i] += Co[i][j] * f;
-                an[i] += Cn[i][j] * f;
-            }
+        for (int p = 0; p < N1; ++p) o[((1 + D) * N1 + p) * CB] = m[p];
+#pragma unroll
+        for (int r = 0; r < N1; ++r) {
+            o[(T1 * N1 + r) * CB] = go[r];
+            o[(T2 * N1 + r) * CB] = gn[r];
         }
-        double xo[4], xn[4];
-        pair_assemble(h, ao[0], ao[1], pair_swap(ao[0]), pair_swap(ao[1]), xo);
-        pair_assemble(h, an[0], an[1], pair_swap(an[0]), pair_swap(an[1]), xn);
-        double uo[4], un[4], vo[3], vn[3];
-        uo[0] = xo[0];
-        un[0] = xn[0];
-        if (prim) {
-#pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                vo[d] = xo[1 + d]; uo[1 + d] = xo[0] * xo[1 + d];
-                vn[d] = xn[1 + d]; un[1 + d] = xn[0] * xn[1 + d];
-            }
-        } else {
-            const double io = rcp(xo[0]), in = rcp(xn[0]);
-#pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                uo[1 + d] = xo[1 + d]; vo[d] = xo[1 + d] * io;
-                un[1 + d] = xn[1 + d]; vn[d] = xn[1 + d] * in;
-            }
-        }
-        double F[4];
-        if (use_hllc) {
-            if (s) hllc<D>(cs, cs2, uo, vo, un, vn, F);
-            else   hllc<D>(cs, cs2, un, vn, uo, vo, F);
-        } else {
-            if (s) rusanov<D>(cs, cs2, uo, vo, un, vn, F);
-            else   rusanov<D>(cs, cs2, un, vn, uo, vo, F);
-        }
-        col[(r * 4 + 2 * h) * CB] = h ? F[2] : F[0];
-        col[(r * 4 + 2 * h + 1) * CB] = h ? F[3] : F[1];
     }
+    face_traces<K, D>(src, T1, T2, bo, bn, s, tab, Co, Cn);
+#pragma unroll 1
+    for (int i = 0; i < N1 / 2; ++i) {
+        double p1[N1], go[N1], gn[N1];
+        double *o = line(i, p1);
+#pragma unroll
+        for (int r = 0; r < N1; ++r) {
+            go[r] = o[(T1 * N1 + r) * CB];
+            gn[r] = o[(T2 * N1 + r) * CB];
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            double F[N1], m[N1];
+            face_line_tangential<double, K>(Co[j], Cn[j], p1, s, go, gn, F);
+            line_moments<K>(F, m);
+#pragma unroll
+            for (int p = 0; p < N1; ++p) o[((j ? T2 : T1) * N1 + p) * CB] = m[p];
+        }
+    }
+    // the two lanes of a cell belong to one wave, whose LDS accesses are in order
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     lift_pair<K, D, CB>(col, h, s, tab, L);
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
 }
 
 template <int K>
-constexpr int rhs_pair_waves() { return K <= 2 ? 3 : 2; }   // at K = 3: 256 VGPRs, 14 of them spilled
+constexpr int rhs_pair_waves() { return K <= 2 ? 3 : 2; }
 
-template <int K, bool FDIRECT, bool LSEL>
+// a table row whose entries of odd first exponent change sign on the second lane's mirrored line
+template <int K>
+struct MirrorRow {
+    ctab<double> *row;
+    double sg;
+    __device__ __forceinline__ double operator[](int j) const
+    {
+        constexpr Modes<K> M = make_modes<K>();
+        return (M.p2[j][0] & 1) ? sg * row[j] : row[j];
+    }
+};
+
+// PRIM: F_PRIM (with the option read at run time the branches' joins cost registers)
+template <int K, bool FDIRECT, bool PRIM>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(rhs_pair_waves<K>()))) k_rhs_pair(RhsArgs a)
 {
     using S = Shape<K>;
     using TL = TabLayout<K>;
     constexpr Modes<K> M = make_modes<K>();
-    constexpr int NB = S::NB, ND = S::ND;
+    constexpr int NB = S::NB, N1 = S::N1, NL = TL::NL;
     constexpr int CB = BLOCK / 2;                  // cells per block
+    // LDS columns per cell: the cell's weights but the mean density during the volume integral,
+    // then the face moments ([line][v][p]).  Two blocks of 79 KiB and their sums fit a CU.
+    constexpr int NCOL = 4 * NB - 1 > S::NF * 4 ? 4 * NB - 1 : S::NF * 4;
     __shared__ double lds[4 * 4];
-    __shared__ double fsh[S::NF * 4 * CB];          // point fluxes of the low faces, [r][v][cell]
+    __shared__ double fsh[NCOL * CB];
     ctab<double> *tab = as_tab<double>(a.tab);
     const int nc = a.g.nc;
     const size_t ncs = (size_t)nc;
@@ -1436,7 +1740,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(rhs_
     const int c = active ? c0 : 0;
 
     const bool av = a.flags & F_AV;
-    const bool prim = a.flags & F_PRIM;
+    constexpr bool prim = PRIM;
     const bool force = a.flags & F_FORCE;
     const bool use_hllc = a.flags & F_HLLC;
     const double cs = a.cs, cs2 = a.cs * a.cs;
@@ -1448,22 +1752,22 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(rhs_
 
     const unsigned bo = (unsigned)c * 8u;
     const Field<double, 4> U(a.u, NB, nc);
-    const unsigned hoff = h ? a.pair_vstride : 0u;
-    double W[2][NB];
-    // with the projected velocity on the faces the momentum weights are read only here:
-    // non-temporal, like the right-hand side written at the end
+    double *col = fsh + cb;
+    const double mass0 = U.get(0, 0, bo);          // cell mean density
+    // the weights into the column, entry v NB + l - 1: lane h loads the modes 2j + h.  With the
+    // projected velocity on the faces the momentum weights are read only here (non-temporal)
+    {
+        const unsigned ho = bo + (h ? U.pstride : 0u);
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+        for (int v = 0; v < 4; ++v) {
+            double w[NB / 2];
 #pragma unroll
-        for (int l = 0; l < NB; ++l) {
-            if constexpr (LSEL) {
-                W[i][l] = (i && prim) ? U.get_nt(i, l, bo + hoff) : U.get(i, l, bo + hoff);
-            } else {
-                const double w0 = (i && prim) ? U.get_nt(i, l, bo) : U.get(i, l, bo);
-                const double w1 = prim ? U.get_nt(2 + i, l, bo) : U.get(2 + i, l, bo);
-                W[i][l] = h ? w1 : w0;
-            }
+            for (int j = 0; j < NB / 2; ++j) w[j] = v && prim ? U.get_nt(v, 2 * j, ho) : U.get(v, 2 * j, ho);
+#pragma unroll
+            for (int j = 0; j < NB / 2; ++j)
+                if (v + j > 0 || h) col[(v * NB + 2 * j + h - 1) * CB] = w[j];
         }
+    }
 
     constexpr DivMap<K> DM = make_divmap<K>();
     constexpr int NDIV = DivMap<K>::NDIV;
@@ -1484,20 +1788,14 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(rhs_
                     for (int t = 0; t < DivMap<K>::MAXT; ++t)
                         if (DM.m[d][l][t] >= 0) Dv[DM.m[d][l][t]] += v * __builtin_sqrt(double(DM.f[d][l][t]));
                 }
+#pragma unroll
+        for (int m = 0; m < NDIV; ++m) Dv[m] *= two_h;
         if (a.flags & F_LEARNED) {
             learned = a.fb[c] == 0;
             nu = ((const double *)a.nu)[c];
         }
     }
 
-    double L[2][NB];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int l = 0; l < NB; ++l) L[i][l] = 0.0;
-    // driving source sums of the lane's own momentum components: lane 0 the x one (fsa),
-    // lane 1 the y and z ones (fsa, fsb)
-    double fsa = 0.0, fsb = 0.0;
     const double half_h = 0.5 * a.h;
     const int pencil = c / a.g.nx;
     const int cijk[3] = {c % a.g.nx, pencil % a.g.ny, pencil / a.g.ny};
@@ -1505,73 +1803,162 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(rhs_
     ctab<double> *ft = as_tab<double>(a.ftab);
     if (force && !FDIRECT) cell_phase<double>(ft + PencilLayout<K>::phases(a.g.ny, a.g.nz), cijk[0], pr, pim);
 
-    // ---- volume integral
+    // the two lanes of a cell belong to one wave, whose LDS accesses are in order
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    // ---- volume integral, line by line as in the one-lane kernel: the lanes share the lines, not
+    // the variables.  Line (t_x, t_y) of lane 1 is the mirror image (K - t_x, t_y) of lane 0's
+    // (table entries of odd x parity change sign).  The line's moments cross to the other lane, and
+    // each lane adds both lines' to its own rows: lane 0 the x momentum, lane 1 the y and z
+    // momentum (with the variables split between the lanes both formed every flux; sums of all
+    // three rows in both lanes, added at the end, did not fit the registers).
+    const double sg = h ? -1.0 : 1.0;
+    double L[2][NB];       // lane 0: row 1 only until the density row is added below
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int l = 0; l < NB; ++l) L[i][l] = 0.0;
+    double fs0 = 0.0, fs1 = 0.0, fs2 = 0.0;   // driving source sums of the lane's lines, times h/2
     auto volume = [&](auto form, int pen) {
         constexpr int FM = decltype(form)::value;
         ctab<double> *g = ft + PencilLayout<K>::HDR + (size_t)pen * PencilLayout<K>::STRIDE;
 #pragma unroll 1
-        for (int q = 0; q < S::NQ; ++q) {
-            ctab<double> *ph = tab + TL::VPHI + q * NB;
-            ctab<double> *dph = tab + TL::VDPHI + q * 3 * ND;
-            const double wq = tab[TL::VW + q];
-            double x0 = 0.0, x1 = 0.0;
+        for (int i = 0; i < S::NF / 2; ++i) {
+            const int tx = i % (N1 / 2), ty = i / (N1 / 2), r = tx + N1 * ty;
+            const MirrorRow<K> phi2{tab + TL::F2 + r * S::NB2, sg};
+            double x[4][N1];
+            // (the offset is opaque, or the compiler would keep the loop-invariant weights in
+            // registers after all)
+            int o = cb - CB;
+            asm volatile("" : "+v"(o));
 #pragma unroll
-            for (int l = 0; l < NB; ++l) {
-                x0 += W[0][l] * ph[l];
-                x1 += W[1][l] * ph[l];
+            for (int v = 0; v < 4; ++v) {
+                double cf[N1];
+                if (v == 0) {
+                    // the mean density is not in the column
+                    struct {
+                        LdsColumn<double, CB> w;
+                        double mean;
+                        __device__ __forceinline__ double operator[](int l) const { return l ? w[l] : mean; }
+                    } w0{{fsh + o}, mass0};
+                    line_coefficients<double, K, K + 1>(w0, phi2, cf);
+                } else {
+                    line_coefficients<double, K, K + 1>(LdsColumn<double, CB>{fsh + v * NB * CB + o}, phi2, cf);
+                }
+                line_eval<K>(cf, x[v]);
+                __builtin_amdgcn_sched_barrier(0);
             }
-            double xv[4];
-            pair_assemble(h, x0, x1, pair_swap(x0), pair_swap(x1), xv);
-            const double rho = xv[0];
-            const double m[3] = {xv[1], xv[2], xv[3]};
-            double pi = 0.0;
+            double div[N1];
             if (av) {
-                double div = 0.0;
-#pragma unroll
-                for (int mm = 0; mm < NDIV; ++mm) div += Dv[mm] * ph[mm];
-                div *= two_h;
-                const double pv = vnr_pi<double>(rho, div, hp, alpha, beta, cs, inv_dt);
-                const double sq = -div;
-                double pl = fmin(rho * nu * sq, 0.5 * rho * hp * hp * sq * inv_dt);
-                pl = (sq > 0.0 && nu > 0.0) ? pl : 0.0;
-                pi = learned ? pl : pv;
+                double cd[K];
+                line_coefficients<double, K, K>(Dv, phi2, cd);
+                line_eval<K>(cd, div);
             }
-            const double ir = rcp(rho);
-            const double pw = (cs2 * rho + pi) * wq;
+            double d[3][N1];
+            {
+                // the tensor at a point: xx, xy, xz, yy, yz, zz
+                auto tensor = [&](int t, double (&F)[6]) {
+                    const double rho = x[0][t];
+                    double pi = double(0);
+                    if (av) {
+                        const double pv = vnr_pi<double>(rho, div[t], hp, alpha, beta, cs, inv_dt);
+                        // learned sensor: the cell's bulk viscosity nu in place of the vNR one,
+                        // Pi = rho nu s at compressed points, with the Pi_max cap of the point
+                        const double sq = -div[t];
+                        double pl = fmin(rho * nu * sq, double(0.5) * rho * hp * hp * sq * inv_dt);
+                        pl = (sq > double(0) && nu > double(0)) ? pl : double(0);
+                        pi = learned ? pl : pv;
+                    }
+                    const double ir = rcp(rho);
+                    const double pw = cs2 * rho + pi;
+                    const double vx = x[1][t] * ir, vy = x[2][t] * ir, vz = x[3][t] * ir;
+                    F[0] = x[1][t] * vx + pw;
+                    F[1] = x[1][t] * vy;
+                    F[2] = x[1][t] * vz;
+                    F[3] = x[2][t] * vy + pw;
+                    F[4] = x[2][t] * vz;
+                    F[5] = x[3][t] * vz + pw;
+                };
+                double m[6][K];
+                auto step = [&](auto ps) {
+                    constexpr int P = decltype(ps)::value;
+                    double lo[6], hi[6];
+                    if constexpr (2 * P < K) tensor(P, lo);
+                    tensor(K - P, hi);
 #pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                const double md = m[d] * wq;
-                const double mdr = md * ir;
-                // lane 0: (rho, m_x) fluxes; lane 1: (m_y, m_z)
-                const double fa = h ? mdr * m[1] + (d == 1 ? pw : 0.0) : md;
-                const double fb = h ? mdr * m[2] + (d == 2 ? pw : 0.0) : mdr * m[0] + (d == 0 ? pw : 0.0);
+                    for (int j = 0; j < 6; ++j) line_moments_step<K, K, P>(lo[j], hi[j], m[j]);
+                    __builtin_amdgcn_sched_barrier(0);
+                };
+                step(std::integral_constant<int, 0>{});
+                if constexpr (K > 1) step(std::integral_constant<int, 1>{});
+                ctab<double> *lx = tab + TL::LWX + r * NL, *ly = tab + TL::LWY + r * NL, *lw = tab + TL::LWP + r * S::NB2;
+                // the rows' fluxes along x, y, z: lane 0 (-; xx, xy, xz), lane 1 (xy, yy, yz; xz, yz, zz).
+                // Of the two lines' moments the sum and (lane 0's minus lane 1's) meet the table
+                // entries of even and odd x parity (line_dx and line_dy are the graded order of the
+                // reduced pair, whose first exponent has the entry's parity in both cases).
 #pragma unroll
-                for (int l = 0; l < NB; ++l) {
-                    if (M.dj[d][l] < 0) continue;
-                    const double dp = dph[d * ND + M.dj[d][l]];
-                    L[0][l] += dp * fa;
-                    L[1][l] += dp * fb;
+                for (int i = 0; i < 2; ++i) {
+                    constexpr int comp[2][3] = {{1, 3, 4}, {2, 4, 5}};
+                    double e[3][K], o[3][K], dz[2][N1];
+#pragma unroll
+                    for (int f = 0; f < 3; ++f)
+#pragma unroll
+                        for (int n = 0; n < K; ++n) {
+                            // lane 0's row 1 is x momentum: xx, xy, xz
+                            const double own = i && !h ? m[f][n] : m[comp[i][f]][n];
+                            const double give = i && h ? m[f][n] : m[comp[i][f]][n];
+                            const double other = pair_swap(give);
+                            e[f][n] = own + other;
+                            o[f][n] = sg * (own - other);
+                        }
+                    line_derivative<K>(e[2], dz[0]);
+                    line_derivative<K>(o[2], dz[1]);
+#pragma unroll
+                    for (int l = 0; l < NB; ++l) {
+                        const int ea = M.e[l][0], eb = M.e[l][1], ec = M.e[l][2];
+                        if (ea) L[i][l] = fma(lx[line_dx(ea, eb)], ((ea - 1) & 1) ? o[0][ec] : e[0][ec], L[i][l]);
+                        if (eb) L[i][l] = fma(ly[line_dy(ea, eb)], (ea & 1) ? o[1][ec] : e[1][ec], L[i][l]);
+                        if (ec) L[i][l] = fma(lw[M.d2[2][l]], dz[ea & 1][ec], L[i][l]);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
                 }
             }
             if (force) {
-                double ac[3];
-                if constexpr (FM == FM_DIRECT)
-                    direct_accel<double>(a.modes, a.nmodes, cijk, tab[TL::VXI + 3 * q], tab[TL::VXI + 3 * q + 1],
-                                         tab[TL::VXI + 3 * q + 2], a.h, ac);
-                else
-                    pencil_accel<double, K>(ft, g, q, pr, pim, ac);
-                const double rw = rho * wq;
-                const double sa = rw * (h ? ac[1] : ac[0]);
-                const double sb = h ? rw * ac[2] : 0.0;
-                fsa += sa;
-                fsb += sb;
-                const double ta = h ? sa * half_h : 0.0;
-                const double tb = h ? sb * half_h : sa * half_h;
+                ctab<double> *lw = tab + TL::LWP + r * S::NB2;
+                double sr[3][N1];
+                double xr = 0.0, xi = 0.0, x2r = 0.0, x2i = 0.0;
+                if constexpr (FM != FM_DIRECT) line_phase<double, K>(ft, tx, pr, pim, sg, xr, xi, x2r, x2i);
 #pragma unroll
-                for (int l = 0; l < NB; ++l) {
-                    const double p = ph[l];
-                    L[0][l] += ta * p;
-                    L[1][l] += tb * p;
+                for (int t = 0; t < N1; ++t) {
+                    const int q = r + S::NF * t;
+                    double ac[3];
+                    if constexpr (FM == FM_DIRECT)
+                        direct_accel<double>(a.modes, a.nmodes, cijk, sg * tab[TL::VXI + 3 * q], tab[TL::VXI + 3 * q + 1],
+                                             tab[TL::VXI + 3 * q + 2], a.h, ac);
+                    else
+                        line_accel<double, K>(g, ty + N1 * t, xr, xi, x2r, x2i, ac);
+                    drive_source<double>(x[0][t], half_h, ac, sr[0][t], sr[1][t], sr[2][t]);
+                }
+                double z[3][N1];
+#pragma unroll
+                for (int v = 0; v < 3; ++v) {
+                    line_moments<K>(sr[v], z[v]);
+                    double &fs = v == 0 ? fs0 : (v == 1 ? fs1 : fs2);
+                    fs = fma(lw[0], z[v][0], fs);
+                }
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    double e[N1], o[N1];
+#pragma unroll
+                    for (int n = 0; n < N1; ++n) {
+                        const double own = i && !h ? z[0][n] : z[1 + i][n];
+                        const double give = i && h ? z[0][n] : z[1 + i][n];
+                        const double other = pair_swap(give);
+                        e[n] = own + other;
+                        o[n] = sg * (own - other);
+                    }
+#pragma unroll
+                    for (int l = 0; l < NB; ++l)
+                        L[i][l] = fma(lw[M.d2[2][l]], (M.e[l][0] & 1) ? o[M.e[l][2]] : e[M.e[l][2]], L[i][l]);
                 }
             }
         }
@@ -1585,25 +1972,34 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(rhs_
         else
             volume(std::integral_constant<int, FM_LANE>{}, pencil);
     }
-    const double mass0 = W[0][0];                   // cell mean density (lane 0)
+    // lane 0's first row is the density's, linear as in the one-lane kernel (its sums so far are
+    // not used)
+#pragma unroll
+    for (int l = 0; l < NB; ++l) {
+        double dr = 0.0;
+#pragma unroll
+        for (int d = 0; d < 3; ++d)
+#pragma unroll
+            for (int t = 0; t < DivMap<K>::MAXT; ++t)
+                if (DM.m[d][l][t] >= 0)
+                    dr = fma(8.0 * __builtin_sqrt(double(DM.f[d][l][t])), col[((1 + d) * NB + DM.m[d][l][t] - 1) * CB], dr);
+        L[0][l] = h ? L[0][l] : dr;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
 
     // ---- surface integral, with the low x and y face fluxes shared through LDS as in the
     // one-lane kernel (cells of the block: CB consecutive cells)
     int nbr[6], ijk[3];
     neighbours(a.g, c, nbr, ijk);
-    // trace sources: density and projected velocity (one array when the density copy is
-    // there), or the weights
-    const Field<double, 4> SRC = !prim ? U
-                                 : (LSEL ? Field<double, 4>(a.vh_rho, NB, nc) : Field<double, 4>(a.u, a.vh, NB, nc));
+    const Field<double, 4> SRC = prim ? Field<double, 4>(a.u, a.vh, NB, nc) : U;
     const int base = blk * CB;
     const bool xsh = __all((unsigned)(nbr[1] - base) < (unsigned)CB);
     const bool ysh = __all((unsigned)(nbr[3] - base) < (unsigned)CB);
-    // Every face leaves its point fluxes in the cell's LDS column and lifts them from there.
-    // The low x and y faces are the high faces of the neighbours below: a wave whose
-    // neighbours above all lie in the block lifts theirs (between two barriers) instead of
-    // computing its high face; a high face that is computed is stored only after the second
-    // barrier, when no other wave reads the columns any more.
-    double *col = fsh + cb;
+    // Every face leaves its moments in the cell's LDS column and lifts them from there.  The low x
+    // and y faces are the high faces of the neighbours below: a wave whose neighbours above all
+    // lie in the block lifts theirs (between two barriers) instead of computing its high face; a
+    // high face that is computed is stored only after the second barrier, when no other wave
+    // reads the columns any more.  (The first barrier also separates the columns' two uses.)
 #pragma unroll 1
     for (int s = 0; s < 2; ++s) {
         if (s == 1) {
@@ -1612,8 +2008,8 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(rhs_
             __syncthreads();
             if (xsh) break;
         }
-        face_pair<K, 0, CB, LSEL>(SRC, bo, (unsigned)(s ? nbr[1] : nbr[0]) * 8u, s, h, hoff, tab, prim, use_hllc, cs,
-                                  cs2, L, col);
+        face_pair<K, 0, CB, PRIM>(SRC, bo, (unsigned)(s ? nbr[1] : nbr[0]) * 8u, s, h, tab, use_hllc, cs,
+                            cs2, L, col);
     }
 #pragma unroll 1
     for (int s = 0; s < 2; ++s) {
@@ -1623,13 +2019,13 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(rhs_
             __syncthreads();
             if (ysh) break;
         }
-        face_pair<K, 1, CB, LSEL>(SRC, bo, (unsigned)(s ? nbr[3] : nbr[2]) * 8u, s, h, hoff, tab, prim, use_hllc, cs,
-                                  cs2, L, col);
+        face_pair<K, 1, CB, PRIM>(SRC, bo, (unsigned)(s ? nbr[3] : nbr[2]) * 8u, s, h, tab, use_hllc, cs,
+                            cs2, L, col);
     }
 #pragma unroll 1
     for (int s = 0; s < 2; ++s)
-        face_pair<K, 2, CB, LSEL>(SRC, bo, (unsigned)(s ? nbr[5] : nbr[4]) * 8u, s, h, hoff, tab, prim, use_hllc, cs,
-                                  cs2, L, col);
+        face_pair<K, 2, CB, PRIM>(SRC, bo, (unsigned)(s ? nbr[5] : nbr[4]) * 8u, s, h, tab, use_hllc, cs,
+                            cs2, L, col);
 
     const double inv4h = 0.25 / a.h;
     if (active) {
@@ -1644,9 +2040,9 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(rhs_
     if (force && a.part) {
         double acc[4] = {0.0, 0.0, 0.0, 0.0};
         if (active) {
-            acc[0] = h ? 0.0 : 0.125 * fsa;
-            acc[1] = h ? 0.125 * fsa : 0.0;
-            acc[2] = h ? 0.125 * fsb : 0.0;
+            acc[0] = 0.125 / half_h * fs0;
+            acc[1] = 0.125 / half_h * fs1;
+            acc[2] = 0.125 / half_h * fs2;
             acc[3] = h ? 0.0 : mass0;
         }
         block_sum<4>(acc, lds);
@@ -1766,9 +2162,8 @@ __device__ __forceinline__ void project_and_bounds(const T (&W)[4][Shape<K>::NB]
 
 // The driving source of a cell summed over its volume points (times 1/8) and its mean
 // density, from its density weights W0, for tables off the driving shell (the field mode by
-// mode at each point), with the arithmetic of the right-hand side's volume loop: the point
-// densities summed mode by mode in the same order, the source through drive_point and
-// direct_accel.  acc[0..2]: source, acc[3]: mean density (all 0 for an inactive lane).
+// mode at each point), with the arithmetic of the right-hand side's volume loop: line by line,
+// the source through drive_source and direct_accel.  acc[0..2]: source, acc[3]: mean density (all 0 for an inactive lane).
 template <typename T, int K>
 __device__ __forceinline__ void drive_sums_direct(const T (&W0)[Shape<K>::NB], ctab<T> *tab, const double *modes,
                                                   int nmodes, const Mesh &g, double h, int c, bool active,
@@ -1780,23 +2175,32 @@ __device__ __forceinline__ void drive_sums_direct(const T (&W0)[Shape<K>::NB], c
     const int pencil = c / g.nx;
     const int cijk[3] = {c % g.nx, pencil % g.ny, pencil / g.ny};
     T fs0 = T(0), fs1 = T(0), fs2 = T(0);
-    // three points per loop step: their table loads in flight together (the same sums)
-#pragma unroll 3
-    for (int q = 0; q < S::NQ; ++q) {
-        ctab<T> *ph = tab + TL::VPHI + q * NB;
-        const T wq = tab[TL::VW + q];
-        T rho = T(0);
+    const T half_h = (T)(0.5 * h);
+#pragma unroll 1
+    for (int r = 0; r < S::NF; ++r) {
+        T c[S::N1], rho[S::N1], sx[S::N1], sy[S::N1], sz[S::N1], m[1];
+        line_coefficients<T, K, K + 1>(W0, tab + TL::F2 + r * S::NB2, c);
+        line_eval<K>(c, rho);
 #pragma unroll
-        for (int l = 0; l < NB; ++l) rho += W0[l] * ph[l];
-        T ac[3];
-        direct_accel<T>(modes, nmodes, cijk, tab[TL::VXI + 3 * q], tab[TL::VXI + 3 * q + 1], tab[TL::VXI + 3 * q + 2],
-                        h, ac);
-        T sp[3];
-        drive_point<T>(rho, wq, ac, sp, fs0, fs1, fs2);
+        for (int t = 0; t < S::N1; ++t) {
+            const int q = r + S::NF * t;
+            T ac[3];
+            direct_accel<T>(modes, nmodes, cijk, tab[TL::VXI + 3 * q], tab[TL::VXI + 3 * q + 1],
+                            tab[TL::VXI + 3 * q + 2], h, ac);
+            drive_source<T>(rho[t], half_h, ac, sx[t], sy[t], sz[t]);
+        }
+        const T w = tab[TL::LWP + r * S::NB2];
+        line_moments<K>(sx, m);
+        fs0 = fma(w, m[0], fs0);
+        line_moments<K>(sy, m);
+        fs1 = fma(w, m[0], fs1);
+        line_moments<K>(sz, m);
+        fs2 = fma(w, m[0], fs2);
     }
-    acc[0] = active ? 0.125 * (double)fs0 : 0.0;
-    acc[1] = active ? 0.125 * (double)fs1 : 0.0;
-    acc[2] = active ? 0.125 * (double)fs2 : 0.0;
+    const double fsc = 0.125 / (double)half_h;
+    acc[0] = active ? fsc * (double)fs0 : 0.0;
+    acc[1] = active ? fsc * (double)fs1 : 0.0;
+    acc[2] = active ? fsc * (double)fs2 : 0.0;
     acc[3] = active ? (double)W0[0] : 0.0;
 }
 

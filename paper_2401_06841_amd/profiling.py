@@ -31,7 +31,7 @@ import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 # the sources that define and launch the step kernels
-STEP_SOURCES = ("dg_api.hip", "dg_basis.hpp", "dg_ctx.hpp", "dg_kernels.hpp")
+STEP_SOURCES = ("dg_api.hip", "dg_basis.hpp", "dg_ctx.hpp", "dg_kernels.hpp", "dg_line.hpp")
 # bytes a plain device copy of the calibration moves per dispatch (bench.py --copy-calibration)
 COPY_BYTES = 4 * (1 << 27)
 
