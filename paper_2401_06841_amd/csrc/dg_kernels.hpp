@@ -337,104 +337,60 @@ __device__ __forceinline__ void store_field(const Field<T, NV> &f, unsigned bo, 
         for (int l = 0; l < Shape<K>::NB; ++l) f.put(v, l, bo, W[v][l]);
 }
 
-// projected velocity of one cell from its weights (Sec. 3.2): vh_{d,l} = 1/8 sum_q w_q phi_l v_d
-template <typename T, int K>
-__device__ __forceinline__ void project_cell(const T (&W)[4][Shape<K>::NB], ctab<T> *tab,
-                                             T (&V)[3][Shape<K>::NB], double *smax, double cs)
+// Projected velocity of a cell, components D0 .. D0 + ND - 1 (Sec. 3.2): vh_{d,l} = 1/8 sum_q w_q
+// phi_l v_d, line by line (dg_line.hpp) with fixed roundings: a component gets the same bits
+// whether it is projected alone (ND = 1, which keeps only NB accumulators live) or with the
+// others.  About half the vector instructions of point-by-point sums over all modes: k_limit_project
+// 2.07 -> 1.77 ms at 256^3 degree 2 FP64 (HBM-bound now), 0.70 -> 0.29 ms at 128^3 degree 3 FP32;
+// steps 616 -> 574 us at 64^3 FP64, 6.13 -> 5.06 ms at 128^3 degree 3 FP32.  SPEED: also the largest signal speed sum_d |v_d| + cs over the points (the time-step
+// bound) into sm.
+template <typename T, int K, int D0, int ND, bool SPEED>
+__device__ __forceinline__ void project_lines(const T (&W)[4][Shape<K>::NB], ctab<T> *tab, T (&V)[ND][Shape<K>::NB],
+                                              double cs, double &sm)
 {
+#pragma clang fp contract(off)
     using S = Shape<K>;
     using TL = TabLayout<K>;
+    constexpr Modes<K> M = make_modes<K>();
+    constexpr int N1 = S::N1;
 #pragma unroll
-    for (int d = 0; d < 3; ++d)
+    for (int d = 0; d < ND; ++d)
 #pragma unroll
         for (int l = 0; l < S::NB; ++l) V[d][l] = T(0);
-    double sm = 0.0;
-    for (int q = 0; q < S::NQ; ++q) {
-        ctab<T> *ph = tab + TL::VPHI + q * S::NB;
-        T rho = T(0), m0 = T(0), m1 = T(0), m2 = T(0);
-#pragma unroll
-        for (int l = 0; l < S::NB; ++l) {
-            const T p = ph[l];
-            rho += W[0][l] * p;
-            m0 += W[1][l] * p;
-            m1 += W[2][l] * p;
-            m2 += W[3][l] * p;
-        }
-        const T ir = rcp(rho);
-        const T v0 = m0 * ir, v1 = m1 * ir, v2 = m2 * ir;
-        if (smax) {
-            const double s = (double)fabs(v0) + (double)fabs(v1) + (double)fabs(v2) + 3.0 * cs;
-            sm = fmax(sm, s);
-        }
-        const T wq = T(0.125) * tab[TL::VW + q];
-        const T a0 = wq * v0, a1 = wq * v1, a2 = wq * v2;
-#pragma unroll
-        for (int l = 0; l < S::NB; ++l) {
-            const T p = ph[l];
-            V[0][l] += a0 * p;
-            V[1][l] += a1 * p;
-            V[2][l] += a2 * p;
-        }
-    }
-    if (smax) *smax = sm;
-}
-
-// Component d of the projected velocity of one cell (Sec. 3.2), same arithmetic as
-// project_cell for that component; working one component at a time keeps only NB
-// accumulators live.
-template <typename T, int K>
-__device__ __forceinline__ void project_component(const T (&W)[4][Shape<K>::NB], ctab<T> *tab, int d,
-                                                  T (&V)[Shape<K>::NB])
-{
-    using S = Shape<K>;
-    using TL = TabLayout<K>;
-#pragma unroll
-    for (int l = 0; l < S::NB; ++l) V[l] = T(0);
 #pragma unroll 1
-    for (int q = 0; q < S::NQ; ++q) {
-        ctab<T> *ph = tab + TL::VPHI + q * S::NB;
-        T rho = T(0), m = T(0);
+    for (int r = 0; r < S::NF; ++r) {
+        ctab<T> *phi2 = tab + TL::F2 + r * S::NB2, *lw = tab + TL::LWP + r * S::NB2;
+        T c[N1], ir[N1], v[N1], z[N1];
+        double sp[N1];
+        line_coefficients<T, K, K + 1>(W[0], phi2, c);
+        line_eval<K>(c, ir);
 #pragma unroll
-        for (int l = 0; l < S::NB; ++l) {
-            const T p = ph[l];
-            rho += W[0][l] * p;
-            m += W[1 + d][l] * p;
+        for (int t = 0; t < N1; ++t) ir[t] = rcp(ir[t]);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            const bool mine = d >= D0 && d < D0 + ND;
+            if (!mine && !SPEED) continue;
+            line_coefficients<T, K, K + 1>(W[1 + d], phi2, c);
+            line_eval<K>(c, v);
+#pragma unroll
+            for (int t = 0; t < N1; ++t) v[t] *= ir[t];
+            if (SPEED)
+#pragma unroll
+                for (int t = 0; t < N1; ++t) sp[t] = d == 0 ? (double)fabs(v[t]) : sp[t] + (double)fabs(v[t]);
+            if (mine) {
+                line_moments<K>(v, z);
+#pragma unroll
+                for (int l = 0; l < S::NB; ++l) V[d - D0][l] = fma(lw[M.d2[2][l]], z[M.e[l][2]], V[d - D0][l]);
+            }
         }
-        const T a = T(0.125) * tab[TL::VW + q] * (m * rcp(rho));
+        if (SPEED)
 #pragma unroll
-        for (int l = 0; l < S::NB; ++l) V[l] += a * ph[l];
+            for (int t = 0; t < N1; ++t) sm = fmax(sm, sp[t] + 3.0 * cs);
     }
-}
-
-// project_component for d = 0 that also takes the largest signal speed sum_d |v_d| + cs
-// over the points from the same point values (the time-step bound)
-template <typename T, int K>
-__device__ __forceinline__ void project_first_with_speed(const T (&W)[4][Shape<K>::NB], ctab<T> *tab,
-                                                         T (&V)[Shape<K>::NB], double cs, double &sm)
-{
-    using S = Shape<K>;
-    using TL = TabLayout<K>;
 #pragma unroll
-    for (int l = 0; l < S::NB; ++l) V[l] = T(0);
-#pragma unroll 1
-    for (int q = 0; q < S::NQ; ++q) {
-        ctab<T> *ph = tab + TL::VPHI + q * S::NB;
-        T rho = T(0), m0 = T(0), m1 = T(0), m2 = T(0);
+    for (int d = 0; d < ND; ++d)
 #pragma unroll
-        for (int l = 0; l < S::NB; ++l) {
-            const T p = ph[l];
-            rho += W[0][l] * p;
-            m0 += W[1][l] * p;
-            m1 += W[2][l] * p;
-            m2 += W[3][l] * p;
-        }
-        const T ir = rcp(rho);
-        const double sp = (double)fabs(m0 * ir) + (double)fabs(m1 * ir) + (double)fabs(m2 * ir) + 3.0 * cs;
-        sm = fmax(sm, sp);
-        const T a = T(0.125) * tab[TL::VW + q] * (m0 * ir);
-#pragma unroll
-        for (int l = 0; l < S::NB; ++l) V[l] += a * ph[l];
-    }
+        for (int l = 0; l < S::NB; ++l) V[d][l] *= T(0.125);
 }
 
 // FP64 kernels project one velocity component at a time (fewer live registers, four
@@ -2071,22 +2027,8 @@ __device__ __forceinline__ void project_and_bounds(const T (&W)[4][Shape<K>::NB]
     const bool speed_in_projection = vh || (part && pa.visc);
     if (part && !speed_in_projection) {
         // largest signal speed sum_d |v_d| + cs over the interior points
-#pragma unroll 1
-        for (int q = 0; q < S::NQ; ++q) {
-            ctab<T> *ph = tab + TL::VPHI + q * NB;
-            T rho = T(0), m0 = T(0), m1 = T(0), m2 = T(0);
-#pragma unroll
-            for (int l = 0; l < NB; ++l) {
-                const T p = ph[l];
-                rho += W[0][l] * p;
-                m0 += W[1][l] * p;
-                m1 += W[2][l] * p;
-                m2 += W[3][l] * p;
-            }
-            const T ir = rcp(rho);
-            const double s = (double)fabs(m0 * ir) + (double)fabs(m1 * ir) + (double)fabs(m2 * ir) + 3.0 * pa.cs;
-            sm = fmax(sm, s);
-        }
+        T none[1][NB];
+        project_lines<T, K, 3, 1, true>(W, tab, none, pa.cs, sm);
     }
     // projected velocity, component by component: stored, and folded into the modal
     // coefficients of its divergence (a degree-(K-1) polynomial) for the viscous bound
@@ -2107,24 +2049,25 @@ __device__ __forceinline__ void project_and_bounds(const T (&W)[4][Shape<K>::NB]
                         if (DM.m[d][l][t] >= 0) Dv[DM.m[d][l][t]] += V[l] * T(__builtin_sqrt(double(DM.f[d][l][t])));
         };
         if constexpr (SPLIT) {
-#pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                T V[NB];
-                if (d == 0 && part)
-                    project_first_with_speed<T, K>(W, tab, V, pa.cs, sm);
-                else
-                    project_component<T, K>(W, tab, d, V);
+            auto component = [&](auto dc, auto speed) {
+                constexpr int d = decltype(dc)::value;
+                T V[1][NB];
+                project_lines<T, K, d, 1, decltype(speed)::value>(W, tab, V, pa.cs, sm);
                 if (vh && active)
 #pragma unroll
-                    for (int l = 0; l < NB; ++l) VO.put(d, l, bo, V[l]);
-                if (visc) fold(d, V);
-            }
+                    for (int l = 0; l < NB; ++l) VO.put(d, l, bo, V[0][l]);
+                if (visc) fold(d, V[0]);
+            };
+            if (part) component(std::integral_constant<int, 0>{}, std::true_type{});
+            else component(std::integral_constant<int, 0>{}, std::false_type{});
+            component(std::integral_constant<int, 1>{}, std::false_type{});
+            component(std::integral_constant<int, 2>{}, std::false_type{});
         } else {
             T V[3][NB];
             if (part)   // two calls, so that sm stays in registers
-                project_cell<T, K>(W, tab, V, &sm, pa.cs);
+                project_lines<T, K, 0, 3, true>(W, tab, V, pa.cs, sm);
             else
-                project_cell<T, K>(W, tab, V, nullptr, pa.cs);
+                project_lines<T, K, 0, 3, false>(W, tab, V, pa.cs, sm);
             if (vh && active) store_field<T, K, 3>(VO, bo, V);
             if (visc)
 #pragma unroll
@@ -2138,12 +2081,12 @@ __device__ __forceinline__ void project_and_bounds(const T (&W)[4][Shape<K>::NB]
             const double hp = pa.h / (K + 1);
             double smin = 0.0;
 #pragma unroll 1
-            for (int q = 0; q < S::NQ; ++q) {
-                ctab<T> *ph = tab + TL::VPHI + q * NB;
-                T div = T(0);
+            for (int r = 0; r < S::NF; ++r) {
+                T cd[K], div[S::N1];
+                line_coefficients<T, K, K>(Dv, tab + TL::F2 + r * S::NB2, cd);
+                line_eval<K>(cd, div);
 #pragma unroll
-                for (int m = 0; m < NDIV; ++m) div += Dv[m] * ph[m];
-                smin = fmin(smin, (double)div);
+                for (int t = 0; t < S::N1; ++t) smin = fmin(smin, (double)div[t]);
             }
             const double s = -smin * (2.0 / pa.h);
             if (s > 0.0) nm = pa.alpha * hp * hp * s + pa.beta * pa.cs * hp;
@@ -2261,32 +2204,32 @@ __device__ __forceinline__ bool stage_limit(T (&U)[4][Shape<K>::NB], ctab<T> *ta
     T rmin = T(__builtin_huge_valf());
     if (!__all(clear)) {
 #pragma unroll 1
-        for (int q = 0; q < S::NQ; ++q) {
-            ctab<T> *ph = tab + TL::VPHI + q * NB;
-            T r = T(0);
+        for (int r = 0; r < S::NF; ++r) {
+            T c[S::N1], rho[S::N1];
+            line_coefficients<T, K, K + 1>(U[0], tab + TL::F2 + r * S::NB2, c);
+            line_eval<K>(c, rho);
 #pragma unroll
-            for (int l = 0; l < NB; ++l) r += U[0][l] * ph[l];
-            rmin = fmin(rmin, r);
+            for (int t = 0; t < S::N1; ++t) rmin = fmin(rmin, rho[t]);
         }
-        ctab<T> *lend = tab + TL::LEND;
-#pragma unroll
-        for (int d = 0; d < 3; ++d)
+        auto face_min = [&](auto dc) {
+            constexpr int D = decltype(dc)::value;
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
                 T C[S::NB2];
-#pragma unroll
-                for (int j = 0; j < S::NB2; ++j) C[j] = T(0);
-#pragma unroll
-                for (int l = 0; l < NB; ++l) C[M.d2[d][l]] += U[0][l] * lend[2 * M.e[l][d] + s];
+                collapse<T, K, D>(U[0], s, tab, C);
 #pragma unroll 1
-                for (int r = 0; r < S::NF; ++r) {
-                    ctab<T> *f2 = tab + TL::F2 + r * S::NB2;
-                    T val = T(0);
+                for (int t = 0; t < S::N1; ++t) {
+                    T c[S::N1], rho[S::N1];
+                    face_line_coefficients<T, K>(C, tab + TL::P1 + t * S::N1, c);
+                    line_eval<K>(c, rho);
 #pragma unroll
-                    for (int j = 0; j < S::NB2; ++j) val += C[j] * f2[j];
-                    rmin = fmin(rmin, val);
+                    for (int i = 0; i < S::N1; ++i) rmin = fmin(rmin, rho[i]);
                 }
             }
+        };
+        face_min(std::integral_constant<int, 0>{});
+        face_min(std::integral_constant<int, 1>{});
+        face_min(std::integral_constant<int, 2>{});
     }
     const double rm = (double)rmin;
     int bad = 0;
@@ -2502,7 +2445,7 @@ __device__ __forceinline__ void rhs_combination(const void *ui, T (&L)[4][Shape<
 
 // The rest of a stage whose combination the right-hand-side kernel has stored (a.out,
 // unlimited): the positivity limiter in place (a cell is written back only where it changes),
-// the projected velocity of the result (a.vh_out; project_cell's arithmetic, all three
+// the projected velocity of the result (a.vh_out; project_lines, all three
 // components in one pass over the points), and with DRIVE the mean-acceleration partials of the
 // result for the next stage (block b: cells b BLOCK + t), in the modal form the right-hand
 // side uses (driving table in the pencil form).
@@ -2539,34 +2482,8 @@ k_limit_project(StageArgs a)
         if (changed && active) store_field<T, K, 4>(UO, bo, U);
     }
     T V[3][NB];
-#pragma unroll
-    for (int d = 0; d < 3; ++d)
-#pragma unroll
-        for (int l = 0; l < NB; ++l) V[d][l] = T(0);
-#pragma unroll 1
-    for (int q = 0; q < S::NQ; ++q) {
-        ctab<T> *ph = tab + TL::VPHI + q * NB;
-        T rho = T(0), m0 = T(0), m1 = T(0), m2 = T(0);
-#pragma unroll
-        for (int l = 0; l < NB; ++l) {
-            const T p = ph[l];
-            rho += U[0][l] * p;
-            m0 += U[1][l] * p;
-            m1 += U[2][l] * p;
-            m2 += U[3][l] * p;
-        }
-        const T ir = rcp(rho);
-        const T v0 = m0 * ir, v1 = m1 * ir, v2 = m2 * ir;
-        const T wq = T(0.125) * tab[TL::VW + q];
-        const T a0 = wq * v0, a1 = wq * v1, a2 = wq * v2;
-#pragma unroll
-        for (int l = 0; l < NB; ++l) {
-            const T p = ph[l];
-            V[0][l] += a0 * p;
-            V[1][l] += a1 * p;
-            V[2][l] += a2 * p;
-        }
-    }
+    double sm = 0.0;
+    project_lines<T, K, 0, 3, false>(U, tab, V, 0.0, sm);
     if (active) store_field<T, K, 3>(Field<T, 3>(a.vh_out, NB, nc), bo, V);
     if constexpr (DRIVE) {
         double acc[4];

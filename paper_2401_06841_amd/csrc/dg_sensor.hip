@@ -375,7 +375,7 @@ __global__ void __launch_bounds__(256) k_mlp_adam(float *__restrict__ P, const f
 //            D_1 = 3 sqrt(5) V_x,(200) + 3 V_y,(110) + 3 V_z,(101) (and cyclic), times 2/h,
 //            scaled by (h/3)/cs
 //   [19]     |mean velocity|/cs
-// vhat: the projected velocity of u already at hand (same arithmetic as project_cell), used
+// vhat: the projected velocity of u already at hand (same arithmetic as project_lines), used
 // unless *fail is raised (then u is not the state vhat belongs to); NULL: project here.
 template <typename T>
 __global__ void __launch_bounds__(BLOCK) k_features(const void *u_, float *__restrict__ x, const void *tab_, Mesh g,
@@ -395,7 +395,8 @@ __global__ void __launch_bounds__(BLOCK) k_features(const void *u_, float *__res
         load_field<T, K, 3>(Field<T, 3>(vhat, NB, nc), bo, V);
     } else {
         load_field<T, K, 4>(Field<T, 4>(u_, NB, nc), bo, W);
-        project_cell<T, K>(W, as_tab<T>(tab_), V, nullptr, 0.0);
+        double sm = 0.0;
+        project_lines<T, K, 0, 3, false>(W, as_tab<T>(tab_), V, 0.0, sm);
     }
     if (!active) return;
     const double r0 = (double)W[0][0];
@@ -428,8 +429,7 @@ __global__ void __launch_bounds__(BLOCK) k_labels(const void *u_, OUT *__restric
 {
     using S = Shape<K>;
     using TL = TabLayout<K>;
-    constexpr Modes<K> M = make_modes<K>();
-    constexpr int NB = S::NB, ND = S::ND;
+    constexpr int NB = S::NB;
     const int nc = g.nc;
     const int c0 = blockIdx.x * BLOCK + threadIdx.x;
     const bool active = c0 < nc;
@@ -439,22 +439,34 @@ __global__ void __launch_bounds__(BLOCK) k_labels(const void *u_, OUT *__restric
     T W[4][NB];
     load_field<T, K, 4>(Field<T, 4>(u_, NB, nc), bo, W);
     T V[3][NB];
-    project_cell<T, K>(W, tab, V, nullptr, 0.0);
+    double sm = 0.0;
+    project_lines<T, K, 0, 3, false>(W, tab, V, 0.0, sm);
+    // modal coefficients of the divergence of the projected velocity, then its values line by line
+    constexpr DivMap<K> DM = make_divmap<K>();
+    T Dv[DivMap<K>::NDIV];
+#pragma unroll
+    for (int m = 0; m < DivMap<K>::NDIV; ++m) Dv[m] = T(0);
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+#pragma unroll
+        for (int l = 0; l < NB; ++l)
+#pragma unroll
+            for (int t = 0; t < DivMap<K>::MAXT; ++t)
+                if (DM.m[d][l][t] >= 0) Dv[DM.m[d][l][t]] += V[d][l] * T(__builtin_sqrt(double(DM.f[d][l][t])));
     double s1 = 0.0, s2 = 0.0;
 #pragma unroll 1
-    for (int q = 0; q < S::NQ; ++q) {
-        ctab<T> *dph = tab + TL::VDPHI + q * 3 * ND;
-        T div = T(0);
+    for (int r = 0; r < S::NF; ++r) {
+        T cd[K], div[S::N1];
+        line_coefficients<T, K, K>(Dv, tab + TL::F2 + r * S::NB2, cd);
+        line_eval<K>(cd, div);
 #pragma unroll
-        for (int d = 0; d < 3; ++d)
-#pragma unroll
-            for (int l = 0; l < NB; ++l)
-                if (M.dj[d][l] >= 0) div += V[d][l] * dph[d * ND + M.dj[d][l]];
-        const double sq = -(double)div * (2.0 / h);
-        if (sq > 0.0) {
-            const double w = (double)tab[TL::VW + q];
-            s1 += w * sq;
-            s2 += w * sq * sq;
+        for (int t = 0; t < S::N1; ++t) {
+            const double sq = -(double)div[t] * (2.0 / h);
+            if (sq > 0.0) {
+                const double w = (double)tab[TL::VW + r + S::NF * t];
+                s1 += w * sq;
+                s2 += w * sq * sq;
+            }
         }
     }
     if (!active) return;
