@@ -79,8 +79,8 @@ enum dg_flags {
                                   combination unless a cell failed).  The same results as DG_SEPARATE_STAGE (bit for bit, or to rounding
                                   with mean-free driving on the driving shell, whose mean the split path
                                   sums in modal form).  With neither flag the split is used where it
-                                  measured faster (meshes of at least 2^21 cells); the two-lane FP64
-                                  degree-3 kernel and DG_VOLUME_MFMA never split.  Both flags together:
+                                  measured faster (meshes of at least 2^21 cells); FP64 at degree 3
+                                  and DG_VOLUME_MFMA never split.  Both flags together:
                                   DG_EINVAL */
 };
 

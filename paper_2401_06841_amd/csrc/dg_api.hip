@@ -243,12 +243,8 @@ static void layout(dg_ctx *c, size_t *total)
     // a third stage buffer for the five-stage scheme (degree 3 with DG_RK_BY_ORDER)
     c->off.stC = o; o += ((c->cfg.flags & DG_RK_BY_ORDER) && c->k == 3) ? state : 0;
     c->off.L = o; o += state;
-    // with the two-lane right-hand side (FP64, degree 3) each projection buffer is preceded by
-    // a copy of the density weights, so that density and projected velocity form one
-    // [4][nb][nc] array (vh_rho_of)
-    const size_t rho_blk = (c->es == 8 && c->k == 3) ? align_up((size_t)c->nb * nc * es) : 0;
-    c->off.vh0 = o + rho_blk; o = c->off.vh0 + vh;
-    c->off.vh1 = o + rho_blk; o = c->off.vh1 + vh;
+    c->off.vh0 = o; o += vh;
+    c->off.vh1 = o; o += vh;
     // driving field in pencil form: header, (k+1)^2 entries of 16 values per y-z pencil, and
     // the x phases (PencilLayout)
     c->off.ftab = o;
@@ -264,9 +260,8 @@ static void layout(dg_ctx *c, size_t *total)
     c->off.feat = o; o += learned ? align_up(nc * DG_MLP_NIN * 4) : 0;
     c->off.lab = o; o += learned ? align_up(nc * 8) : 0;
     c->off.mlp = o; o += align_up((size_t)MLP_PART_ROWS * (DG_MLP_NPARAM + 1) * 4);   // per-wave network gradients
-    // per-block partials: the FP64 degree-3 right-hand side runs two lanes per cell (twice
-    // the blocks)
-    c->off.part = o; o += align_up((size_t)c->nblk * 2 * 4 * 8);
+    // per-block partials
+    c->off.part = o; o += align_up((size_t)c->nblk * 4 * 8);
     // the step's last stage: per-block time-step maxima (apart from the right-hand side's
     // partials, which the same stage reads)
     c->off.spart = o; o += align_up((size_t)c->nblk * 2 * 8);
@@ -596,39 +591,28 @@ static ProjArgs proj_args(const dg_ctx *c)
     return pa;
 }
 
-// the density copy in front of a workspace projection buffer (two-lane configuration), or
-// NULL for any other buffer or configuration
-static void *vh_rho_of(const dg_ctx *c, const void *vh)
-{
-    if (!(c->es == 8 && c->k == 3) || !vh) return nullptr;
-    if (vh != c->wp(c->off.vh0) && vh != c->wp(c->off.vh1)) return nullptr;
-    return (char *)const_cast<void *>(vh) - (size_t)c->nb * c->nc * c->es;
-}
-
 template <typename T, int K>
 static int launch_project(dg_ctx *c, const void *u, void *vh, double *part, int *fail)
 {
     const Mesh g{c->cfg.nx, c->cfg.ny, c->cfg.nz, c->nc};
     const ProjArgs pa = proj_args(c);
     hipLaunchKernelGGL((k_project<T, K>), dim3(c->nblk), dim3(BLOCK), 0, c->stream, u, vh, c->tab, g, pa,
-                       part, fail, vh_rho_of(c, vh));
+                       part, fail);
     LAUNCHCHK(c);
     return DG_OK;
 }
-
-// The FP64 right-hand side at degree 3 runs two lanes per cell (k_rhs_pair): one lane per
-// cell fits only one wave per SIMD there, two lanes fit two (measured 15 % faster at 64^3).
-// At degrees 1 and 2 the one-lane kernel is faster (the pair costs twice the loads and a
-// lane swap per point value, 194 -> 265 us at 64^3 degree 2).
-template <typename T, int K>
-constexpr bool rhs_pair() { return sizeof(T) == 8 && K == 3; }
-
 
 // failure prediction of a last stage (RhsArgs::pred_fail): its u^n operand and coefficients
 struct StagePred {
     const void *un;
     const double *coef;
 };
+
+// Configurations whose stages may be split: all but FP64 at degree 3, whose right-hand side runs one
+// wave per SIMD (512 registers): its stages stay separate whatever the flags (12.9 ms per 128^3
+// step against 14.7 ms split).
+template <typename T, int K>
+constexpr bool may_split() { return !(sizeof(T) == 8 && K == 3); }
 
 // planes per tile of the right-hand-side kernels' block order (plane_tiled); measured on
 // driven states, alternated on one MI355X: 256^3 degree 2 FP64 step 50.9 ms with the plain
@@ -683,27 +667,14 @@ static int launch_rhs(dg_ctx *c, const void *u, const void *vh, void *out, doubl
     if (st) a.part = nullptr;   // a split stage's kernel reads the partials of its input
     // sweep order: tiles of planes when whole blocks make up a plane
     {
-        const int cpb = rhs_pair<T, K>() ? BLOCK / 2 : BLOCK;
         const long long plane = (long long)c->cfg.nx * c->cfg.ny;
-        a.bpp = plane % cpb == 0 ? (int)(plane / cpb) : 0;
+        a.bpp = plane % BLOCK == 0 ? (int)(plane / BLOCK) : 0;
         a.zt = RHS_ZTILE;
     }
-    if constexpr (rhs_pair<T, K>()) {
-        c->rhs_nblk = (c->nc + BLOCK / 2 - 1) / (BLOCK / 2);
-        const dim3 gr(c->rhs_nblk), bl(BLOCK);
-        if (a.flags & DG_PRIM_PROJ) {
-            if (direct) hipLaunchKernelGGL((k_rhs_pair<K, true, true>), gr, bl, 0, c->stream, a);
-            else hipLaunchKernelGGL((k_rhs_pair<K, false, true>), gr, bl, 0, c->stream, a);
-        } else {
-            if (direct) hipLaunchKernelGGL((k_rhs_pair<K, true, false>), gr, bl, 0, c->stream, a);
-            else hipLaunchKernelGGL((k_rhs_pair<K, false, false>), gr, bl, 0, c->stream, a);
-        }
-    } else {
-        c->rhs_nblk = c->nblk;
-        bool done = false;
+    const dim3 gr(c->nblk), bl(BLOCK);
+    if constexpr (may_split<T, K>()) {
         if (st) {
             // u^n enters the combination when its coefficient is not zero
-            const dim3 gr(c->nblk), bl(BLOCK);
             if (st->ca != 0.0) {
                 if (direct) hipLaunchKernelGGL((k_rhs<T, K, true, false, 2>), gr, bl, 0, c->stream, a, *st);
                 else hipLaunchKernelGGL((k_rhs<T, K, false, false, 2>), gr, bl, 0, c->stream, a, *st);
@@ -711,19 +682,21 @@ static int launch_rhs(dg_ctx *c, const void *u, const void *vh, void *out, doubl
                 if (direct) hipLaunchKernelGGL((k_rhs<T, K, true, false, 1>), gr, bl, 0, c->stream, a, *st);
                 else hipLaunchKernelGGL((k_rhs<T, K, false, false, 1>), gr, bl, 0, c->stream, a, *st);
             }
+            LAUNCHCHK(c);
+            return prof_mark(c, 0, 1);
+        }
+    }
+    bool done = false;
+    if constexpr (sizeof(T) == 4 && K == 2) {
+        // volume integral on the matrix cores (tables in the pencil form or no driving)
+        if ((c->cfg.flags & DG_VOLUME_MFMA) && !direct) {
+            hipLaunchKernelGGL((k_rhs<T, K, false, true>), gr, bl, 0, c->stream, a, st0);
             done = true;
         }
-        if constexpr (sizeof(T) == 4 && K == 2) {
-            // volume integral on the matrix cores (tables in the pencil form or no driving)
-            if (!done && (c->cfg.flags & DG_VOLUME_MFMA) && !direct) {
-                hipLaunchKernelGGL((k_rhs<T, K, false, true>), dim3(c->nblk), dim3(BLOCK), 0, c->stream, a, st0);
-                done = true;
-            }
-        }
-        if (!done) {
-            if (direct) hipLaunchKernelGGL((k_rhs<T, K, true>), dim3(c->nblk), dim3(BLOCK), 0, c->stream, a, st0);
-            else hipLaunchKernelGGL((k_rhs<T, K, false>), dim3(c->nblk), dim3(BLOCK), 0, c->stream, a, st0);
-        }
+    }
+    if (!done) {
+        if (direct) hipLaunchKernelGGL((k_rhs<T, K, true>), gr, bl, 0, c->stream, a, st0);
+        else hipLaunchKernelGGL((k_rhs<T, K, false>), gr, bl, 0, c->stream, a, st0);
     }
     LAUNCHCHK(c);
     return prof_mark(c, 0, 1);
@@ -742,7 +715,7 @@ static int launch_abar(dg_ctx *c, const double *part = nullptr, int np = 0)
 {
     if (!part) {
         part = (const double *)c->wp(c->off.part);
-        np = c->rhs_nblk;
+        np = c->nblk;
     }
     hipLaunchKernelGGL(k_final, dim3(1), dim3(BLOCK), 0, c->stream, part, np, 1, 1.0, 0.0, c->abar(),
                        (const int *)nullptr, (volatile long long *)nullptr, 0LL, (const double *)nullptr, 0);
@@ -762,7 +735,6 @@ static StageArgs stage_args(dg_ctx *c, const void *ui, const void *un, const voi
     a.L = L;
     a.out = out;
     a.vh_out = vh_out;
-    a.rho_out = vh_rho_of(c, vh_out);
     a.skip_flag = skip_if_failed ? c->fail() : nullptr;
     a.tab = c->tab;
     // abar_in_stage: every block reduces the right-hand side's partials to the removed mean
@@ -772,7 +744,7 @@ static StageArgs stage_args(dg_ctx *c, const void *ui, const void *un, const voi
     const bool mf = (L || split) && use_meanfree(c);
     a.abar = mf && !c->abar_in_stage ? c->abar() : nullptr;
     a.abar_part = mf && c->abar_in_stage ? (const double *)c->wp(split ? c->off.dpart : c->off.part) : nullptr;
-    a.abar_np = split ? c->nblk : c->rhs_nblk;
+    a.abar_np = c->nblk;
     a.fail = c->fail();
     a.nlim = nlim;
     a.part = part;
@@ -964,7 +936,7 @@ static int free_stage_buffer(const dg_ctx *c, const StageSpec &g)
 template <typename T, int K>
 static bool split_stage(const dg_ctx *c, const StageSpec &g, bool last)
 {
-    if (rhs_pair<T, K>() || g.w || g.out == g.in) return false;
+    if (!may_split<T, K>() || g.w || g.out == g.in) return false;
     if (last ? free_stage_buffer(c, g) == 0 : g.out == 0) return false;
     if (c->cfg.flags & (DG_SEPARATE_STAGE | DG_VOLUME_MFMA)) return false;
     if (c->cfg.flags & DG_SPLIT_STAGE) return true;
@@ -1019,7 +991,7 @@ static int launch_step_stage(dg_ctx *c, void *u, int s, double dt, bool reset_fa
     void *buf[4] = {u, c->wp(c->off.stA), c->wp(c->off.stB), c->wp(c->off.stC)};
     const StageSpec &g = S.s[s];
     const bool last = s == S.stages - 1;
-    if constexpr (!rhs_pair<T, K>()) if (split_stage<T, K>(c, g, last)) {
+    if constexpr (may_split<T, K>()) if (split_stage<T, K>(c, g, last)) {
         int rc = DG_OK;
         int *reset = reset_fail ? c->fail() : nullptr;
         const bool mf = use_meanfree(c);
@@ -1085,7 +1057,7 @@ static int launch_step_stage(dg_ctx *c, void *u, int s, double dt, bool reset_fa
     // mean-free driving: with few right-hand-side blocks every stage block reduces their
     // partials itself (at most 32 KB of reads per block, no reduction kernel); with more, one
     // k_final reduces them once, as the repeated reads would grow with the square of the mesh
-    const bool in_stage = c->rhs_nblk <= ABAR_IN_STAGE_BLOCKS;
+    const bool in_stage = c->nblk <= ABAR_IN_STAGE_BLOCKS;
     if (use_meanfree(c) && !in_stage) {
         rc = launch_abar(c);
         if (rc) return rc;

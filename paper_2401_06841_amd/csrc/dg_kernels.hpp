@@ -268,7 +268,6 @@ struct StageArgs {
     const void *L;          // right-hand side of u^(i) (NULL: plain copy/limit of ui)
     void *out;              // u^(i+1) (may alias un)
     void *vh_out;           // projection of u^(i+1) for the next stage, or NULL
-    void *rho_out;          // with vh_out: a copy of the density weights of u^(i+1), or NULL
     const int *skip_flag;   // the last stage: the failure flag (write nothing when raised), or NULL
     const void *tab;
     const double *abar;     // removed mean acceleration (3), or NULL
@@ -554,9 +553,8 @@ __device__ __forceinline__ void collapse(const T (&w)[Shape<K>::NB], int s, ctab
 // (prim off: momentum) of the cell (Co) and its neighbour (Cn): the line's values of twice the
 // mass and normal momentum flux, F0 and Fn, and the factors of the tangential velocities (of
 // the tangential momenta with prim off) of the two sides, go and gn.  s: 1 the cell is the low side.
-// p1: the basis values of the line's second tangential point.  PRIMSEL: prim when the caller's code
-// is compiled for one value of it (0, 1), or -1.
-template <typename T, int K, int PRIMSEL = -1, typename B>
+// p1: the basis values of the line's second tangential point.
+template <typename T, int K, typename B>
 __device__ __forceinline__ void face_line_normal(const T (&Co)[2][Shape<K>::NB2], const T (&Cn)[2][Shape<K>::NB2],
                                                  const B &p1, int s, bool prim, bool use_hllc, T cs, T cs2,
                                                  T (&F0)[K + 1], T (&Fn)[K + 1], T (&go)[K + 1], T (&gn)[K + 1])
@@ -602,12 +600,8 @@ __device__ __forceinline__ void face_line_normal(const T (&Co)[2][Shape<K>::NB2]
         else
             fluxes(pr, [&](T rL, T vL, T rR, T vR, T &f0, T &fn, T &gL, T &gR) { rusanov2(cs, cs2, rL, vL, rR, vR, f0, fn, gL, gR); });
     };
-    if constexpr (PRIMSEL >= 0) {
-        solver(std::integral_constant<bool, PRIMSEL == 1>{});
-    } else {
-        if (prim) solver(std::true_type{});
-        else solver(std::false_type{});
-    }
+    if (prim) solver(std::true_type{});
+    else solver(std::false_type{});
 }
 
 // The flux of one tangential momentum along a line from its 2D coefficients of both sides and
@@ -803,12 +797,12 @@ __device__ __forceinline__ void pencil_accel(ctab<T> *ft, ctab<T> *g, int q, T p
 }
 
 // the same for the points of a line along z, which share t_x: the phase X and its square once,
-// then a at the point pair tt = t_y + N1 t_z (sg = -1: the mirrored t_x, E_t conjugate)
+// then a at the point pair tt = t_y + N1 t_z
 template <typename T, int K>
-__device__ __forceinline__ void line_phase(ctab<T> *ft, int tx, T pr, T pim, T sg, T &xr, T &xi, T &x2r, T &x2i)
+__device__ __forceinline__ void line_phase(ctab<T> *ft, int tx, T pr, T pim, T &xr, T &xi, T &x2r, T &x2i)
 {
 #pragma clang fp contract(off)
-    const T er = ft[2 * tx], ei = sg * ft[2 * tx + 1];
+    const T er = ft[2 * tx], ei = ft[2 * tx + 1];
     xr = fma(pr, er, -(pim * ei));
     xi = fma(pr, ei, pim * er);
     x2r = fma(xr, xr, -(xi * xi));
@@ -1162,13 +1156,17 @@ __device__ __forceinline__ void volume_mfma(const RhsArgs &a, ctab<float> *tab, 
 //         + (1/8) sum_q w_q phi rho a (Sec. 2.2 weight evolution; Sec. 3.1; Sec. 4.2)
 // Line by line (dg_line.hpp) in the volume and on the faces: with the 3D basis tables at every point
 // the FP64 degree-2 kernel issued 12,700 vector instructions per wave and loaded 22 table values
-// per point.  Measured before and after, per step, with the two-lane kernel below in the same form:
+// per point.  Measured before and after, per step:
 // 256^3 degree 2 FP64 38.7 -> 32.5 ms, 128^3 degree 3 FP32 9.41 -> 6.13 ms, 128^3 degree 2 FP32 with
-// the learned sensor 3.16 -> 2.75 ms, 64^3 degree 2 FP64 0.747 -> 0.616 ms, 128^3 degree 3 FP64 22.9
-// -> 21.5 ms, 33x20x27 degree 2 FP32 0.247 -> 0.191 ms, 16^3 degree 1 FP64 79 -> 68 us.
+// the learned sensor 3.16 -> 2.75 ms, 64^3 degree 2 FP64 0.747 -> 0.616 ms, 33x20x27 degree 2 FP32
+// 0.247 -> 0.191 ms, 16^3 degree 1 FP64 79 -> 68 us.
 // occupancy target (waves per SIMD) of the right-hand-side kernel: the register file
 // holds the 4 NB coefficients and 4 NB accumulators of a cell per lane, so FP64 fits two
-// waves and FP32 four (two at degree 3).  FP64 at degree 3 takes the two-lane kernel.
+// waves and FP32 four (two at degree 3).  FP64 at degree 3 takes the whole register file, one wave
+// per SIMD, with the accumulators it is not working on in the accumulation registers: 3.2 ms per
+// 128^3 right-hand side.  Two lanes per cell at two waves per SIMD, which was the better form while
+// every point was evaluated from all modes (5.9 ms), took 5.4 ms line by line (256 registers and
+// spills, every line's moments swapped between the lanes).
 template <typename T, int K, bool VMFMA = false>
 constexpr int rhs_waves() { return VMFMA ? MFMA_WAVES : (sizeof(T) == 8 ? (K <= 2 ? 2 : 1) : (K <= 2 ? 4 : 2)); }
 
@@ -1390,7 +1388,7 @@ k_rhs(RhsArgs a, StageArgs st)
             if (force) {
                 T sr[3][N1];
                 T xr = T(0), xi = T(0), x2r = T(0), x2i = T(0);
-                if constexpr (FM != FM_DIRECT) line_phase<T, K>(ft, r % N1, pr, pim, T(1), xr, xi, x2r, x2i);
+                if constexpr (FM != FM_DIRECT) line_phase<T, K>(ft, r % N1, pr, pim, xr, xi, x2r, x2i);
 #pragma unroll
                 for (int t = 0; t < N1; ++t) {
                     const int q = r + S::NF * t;
@@ -1516,495 +1514,6 @@ k_rhs(RhsArgs a, StageArgs st)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) a.part[blk * 4 + i] = acc[i];
         }
-    }
-}
-
-// ------------------------------------------- RHS kernel, FP64, two lanes per cell
-// The FP64 kernel above keeps the 4 NB coefficients and 4 NB accumulators of a cell in one
-// lane, which at degree 3 fits only one wave per SIMD.  Here the lanes 2i and 2i+1 of a wave share
-// cell i: the cell's weights wait in LDS, the lanes share the lines of points of the volume and
-// of every face (lane 1 takes the mirror images of lane 0's lines), and lane h owns the rows of
-// the variables 2h and 2h+1 in the result.
-
-// the value held by the other lane of the pair (lane ^ 1)
-__device__ __forceinline__ double pair_swap(double x)
-{
-    const unsigned long long b = (unsigned long long)__double_as_longlong(x);
-    const int lo = __builtin_amdgcn_mov_dpp((int)(unsigned)(b & 0xffffffffull), 0xB1, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_mov_dpp((int)(unsigned)(b >> 32), 0xB1, 0xF, 0xF, false);
-    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
-}
-
-// Surface integral of one face (normal axis D, side s) for the lane's two variables from the
-// line moments in an LDS column, as lift does (col: the column of the cell that stored them,
-// [line][v][p] with stride CB, of twice the flux)
-template <int K, int D, int CB>
-__device__ __forceinline__ void lift_pair(const double *col, int h, int s, ctab<double> *tab,
-                                          double (&L)[2][Shape<K>::NB])
-{
-    using S = Shape<K>;
-    using TL = TabLayout<K>;
-    constexpr Modes<K> M = make_modes<K>();
-    double M2[2][S::NB2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < S::NB2; ++j) M2[i][j] = 0.0;
-#pragma unroll 1
-    for (int t = 0; t < S::N1; ++t) {
-        ctab<double> *wl = tab + TL::WLT + t * (K + 1);
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int p = 0; p <= K; ++p) {
-                const double m = col[((t * 4 + 2 * h + i) * S::N1 + p) * CB];
-#pragma unroll
-                for (int q = 0; q <= K - p; ++q) M2[i][idx2(p, q)] += m * wl[q];
-            }
-    }
-    ctab<double> *lend = tab + TL::LEND;
-    const double sgn = s ? -0.5 : 0.5;
-#pragma unroll
-    for (int l = 0; l < S::NB; ++l) {
-        const double ls = sgn * lend[2 * M.e[l][D] + s];
-        L[0][l] += ls * M2[0][M.d2[D][l]];
-        L[1][l] += ls * M2[1][M.d2[D][l]];
-    }
-}
-
-// 2D coefficients at the face of the variables v0 and v1 of the cell (bo) and its neighbour
-// (bn), one side's loads of one variable in flight at a time (register pressure)
-template <int K, int D>
-__device__ __forceinline__ void face_traces(const Field<double, 4> &src, int v0, int v1, unsigned bo, unsigned bn, int s,
-                                            ctab<double> *tab, double (&Co)[2][Shape<K>::NB2],
-                                            double (&Cn)[2][Shape<K>::NB2])
-{
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        double w[Shape<K>::NB];
-        load_modes<double, K>(src.r[i ? v1 : v0], src.pstride, bo, w);
-        collapse<double, K, D>(w, s, tab, Co[i]);
-        __builtin_amdgcn_sched_barrier(0);
-        load_modes<double, K>(src.r[i ? v1 : v0], src.pstride, bn, w);
-        collapse<double, K, D>(w, 1 - s, tab, Cn[i]);
-        __builtin_amdgcn_sched_barrier(0);
-    }
-}
-
-// One face of the cell by its two lanes, as face does.  The lanes share the lines of the face, not
-// the variables: line i of lane 1 is the mirror image of lane 0's line i (basis values with the
-// sign of the odd degrees flipped), and a lane forms all four fluxes of its lines, so nothing is
-// computed twice and nothing crosses lanes but through the column, from which each lane then
-// lifts its own two variables.  (With the variables split, every point value crossed lanes and
-// both lanes formed every flux.)
-template <int K, int D, int CB, bool PRIM>
-__device__ __forceinline__ void face_pair(const Field<double, 4> &src, unsigned bo, unsigned bn, int s, int h,
-                                          ctab<double> *tab, bool use_hllc, double cs, double cs2,
-                                          double (&L)[2][Shape<K>::NB], double *col)
-{
-    using S = Shape<K>;
-    using TL = TabLayout<K>;
-    constexpr int N1 = S::N1, T1 = 1 + tan1(D), T2 = 1 + tan2(D);
-    static_assert(N1 % 2 == 0, "the two lanes share the lines");
-    double Co[2][S::NB2], Cn[2][S::NB2];
-    auto line = [&](int i, double (&p1)[N1]) {
-        ctab<double> *row = tab + TL::P1 + i * N1;
-#pragma unroll
-        for (int q = 0; q < N1; ++q) p1[q] = (q & 1) && h ? -row[q] : row[q];
-        return col + (h ? N1 - 1 - i : i) * (4 * N1 * CB);
-    };
-    face_traces<K, D>(src, 0, 1 + D, bo, bn, s, tab, Co, Cn);
-#pragma unroll 1
-    for (int i = 0; i < N1 / 2; ++i) {
-        double p1[N1], F0[N1], Fn[N1], go[N1], gn[N1], m[N1];
-        double *o = line(i, p1);
-        face_line_normal<double, K, PRIM>(Co, Cn, p1, s, PRIM, use_hllc, cs, cs2, F0, Fn, go, gn);
-        line_moments<K>(F0, m);
-#pragma unroll
-        for (int p = 0; p < N1; ++p) o[p * CB] = m[p];
-        line_moments<K>(Fn, m);
-#pragma unroll
-        for (int p = 0; p < N1; ++p) o[((1 + D) * N1 + p) * CB] = m[p];
-#pragma unroll
-        for (int r = 0; r < N1; ++r) {
-            o[(T1 * N1 + r) * CB] = go[r];
-            o[(T2 * N1 + r) * CB] = gn[r];
-        }
-    }
-    face_traces<K, D>(src, T1, T2, bo, bn, s, tab, Co, Cn);
-#pragma unroll 1
-    for (int i = 0; i < N1 / 2; ++i) {
-        double p1[N1], go[N1], gn[N1];
-        double *o = line(i, p1);
-#pragma unroll
-        for (int r = 0; r < N1; ++r) {
-            go[r] = o[(T1 * N1 + r) * CB];
-            gn[r] = o[(T2 * N1 + r) * CB];
-        }
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            double F[N1], m[N1];
-            face_line_tangential<double, K>(Co[j], Cn[j], p1, s, go, gn, F);
-            line_moments<K>(F, m);
-#pragma unroll
-            for (int p = 0; p < N1; ++p) o[((j ? T2 : T1) * N1 + p) * CB] = m[p];
-        }
-    }
-    // the two lanes of a cell belong to one wave, whose LDS accesses are in order
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    lift_pair<K, D, CB>(col, h, s, tab, L);
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-}
-
-template <int K>
-constexpr int rhs_pair_waves() { return K <= 2 ? 3 : 2; }
-
-// a table row whose entries of odd first exponent change sign on the second lane's mirrored line
-template <int K>
-struct MirrorRow {
-    ctab<double> *row;
-    double sg;
-    __device__ __forceinline__ double operator[](int j) const
-    {
-        constexpr Modes<K> M = make_modes<K>();
-        return (M.p2[j][0] & 1) ? sg * row[j] : row[j];
-    }
-};
-
-// PRIM: F_PRIM (with the option read at run time the branches' joins cost registers)
-template <int K, bool FDIRECT, bool PRIM>
-__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(rhs_pair_waves<K>()))) k_rhs_pair(RhsArgs a)
-{
-    using S = Shape<K>;
-    using TL = TabLayout<K>;
-    constexpr Modes<K> M = make_modes<K>();
-    constexpr int NB = S::NB, N1 = S::N1, NL = TL::NL;
-    constexpr int CB = BLOCK / 2;                  // cells per block
-    // LDS columns per cell: the cell's weights but the mean density during the volume integral,
-    // then the face moments ([line][v][p]).  Two blocks of 79 KiB and their sums fit a CU.
-    constexpr int NCOL = 4 * NB - 1 > S::NF * 4 ? 4 * NB - 1 : S::NF * 4;
-    __shared__ double lds[4 * 4];
-    __shared__ double fsh[NCOL * CB];
-    ctab<double> *tab = as_tab<double>(a.tab);
-    const int nc = a.g.nc;
-    const size_t ncs = (size_t)nc;
-    const int blk = plane_tiled(xcd_remap(blockIdx.x, gridDim.x), a.bpp, a.g.nz, a.zt);
-    const int h = threadIdx.x & 1;                 // variables 2h and 2h+1
-    const int cb = threadIdx.x >> 1;
-    const int c0 = blk * CB + cb;
-    const bool active = c0 < nc;
-    const int c = active ? c0 : 0;
-
-    const bool av = a.flags & F_AV;
-    constexpr bool prim = PRIM;
-    const bool force = a.flags & F_FORCE;
-    const bool use_hllc = a.flags & F_HLLC;
-    const double cs = a.cs, cs2 = a.cs * a.cs;
-    const double hp = a.h / (K + 1);
-    const double dt = a.dt_dev ? *a.dt_dev : a.dt;
-    const double inv_dt = dt > 0.0 ? 1.0 / dt : 1e300;
-    const double alpha = a.alpha, beta = a.beta;
-    const double two_h = 2.0 / a.h;
-
-    const unsigned bo = (unsigned)c * 8u;
-    const Field<double, 4> U(a.u, NB, nc);
-    double *col = fsh + cb;
-    const double mass0 = U.get(0, 0, bo);          // cell mean density
-    // the weights into the column, entry v NB + l - 1: lane h loads the modes 2j + h.  With the
-    // projected velocity on the faces the momentum weights are read only here (non-temporal)
-    {
-        const unsigned ho = bo + (h ? U.pstride : 0u);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            double w[NB / 2];
-#pragma unroll
-            for (int j = 0; j < NB / 2; ++j) w[j] = v && prim ? U.get_nt(v, 2 * j, ho) : U.get(v, 2 * j, ho);
-#pragma unroll
-            for (int j = 0; j < NB / 2; ++j)
-                if (v + j > 0 || h) col[(v * NB + 2 * j + h - 1) * CB] = w[j];
-        }
-    }
-
-    constexpr DivMap<K> DM = make_divmap<K>();
-    constexpr int NDIV = DivMap<K>::NDIV;
-    double Dv[NDIV];
-#pragma unroll
-    for (int m = 0; m < NDIV; ++m) Dv[m] = 0.0;
-    bool learned = false;
-    double nu = 0.0;
-    const Field<double, 3> VH(a.vh, NB, nc);
-    if (av) {
-#pragma unroll
-        for (int d = 0; d < 3; ++d)
-#pragma unroll
-            for (int l = 0; l < NB; ++l)
-                if (M.e[l][d] >= 1) {
-                    const double v = VH.get(d, l, bo);
-#pragma unroll
-                    for (int t = 0; t < DivMap<K>::MAXT; ++t)
-                        if (DM.m[d][l][t] >= 0) Dv[DM.m[d][l][t]] += v * __builtin_sqrt(double(DM.f[d][l][t]));
-                }
-#pragma unroll
-        for (int m = 0; m < NDIV; ++m) Dv[m] *= two_h;
-        if (a.flags & F_LEARNED) {
-            learned = a.fb[c] == 0;
-            nu = ((const double *)a.nu)[c];
-        }
-    }
-
-    const double half_h = 0.5 * a.h;
-    const int pencil = c / a.g.nx;
-    const int cijk[3] = {c % a.g.nx, pencil % a.g.ny, pencil / a.g.ny};
-    double pr = 0.0, pim = 0.0;
-    ctab<double> *ft = as_tab<double>(a.ftab);
-    if (force && !FDIRECT) cell_phase<double>(ft + PencilLayout<K>::phases(a.g.ny, a.g.nz), cijk[0], pr, pim);
-
-    // the two lanes of a cell belong to one wave, whose LDS accesses are in order
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    // ---- volume integral, line by line as in the one-lane kernel: the lanes share the lines, not
-    // the variables.  Line (t_x, t_y) of lane 1 is the mirror image (K - t_x, t_y) of lane 0's
-    // (table entries of odd x parity change sign).  The line's moments cross to the other lane, and
-    // each lane adds both lines' to its own rows: lane 0 the x momentum, lane 1 the y and z
-    // momentum (with the variables split between the lanes both formed every flux; sums of all
-    // three rows in both lanes, added at the end, did not fit the registers).
-    const double sg = h ? -1.0 : 1.0;
-    double L[2][NB];       // lane 0: row 1 only until the density row is added below
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int l = 0; l < NB; ++l) L[i][l] = 0.0;
-    double fs0 = 0.0, fs1 = 0.0, fs2 = 0.0;   // driving source sums of the lane's lines, times h/2
-    auto volume = [&](auto form, int pen) {
-        constexpr int FM = decltype(form)::value;
-        ctab<double> *g = ft + PencilLayout<K>::HDR + (size_t)pen * PencilLayout<K>::STRIDE;
-#pragma unroll 1
-        for (int i = 0; i < S::NF / 2; ++i) {
-            const int tx = i % (N1 / 2), ty = i / (N1 / 2), r = tx + N1 * ty;
-            const MirrorRow<K> phi2{tab + TL::F2 + r * S::NB2, sg};
-            double x[4][N1];
-            // (the offset is opaque, or the compiler would keep the loop-invariant weights in
-            // registers after all)
-            int o = cb - CB;
-            asm volatile("" : "+v"(o));
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                double cf[N1];
-                if (v == 0) {
-                    // the mean density is not in the column
-                    struct {
-                        LdsColumn<double, CB> w;
-                        double mean;
-                        __device__ __forceinline__ double operator[](int l) const { return l ? w[l] : mean; }
-                    } w0{{fsh + o}, mass0};
-                    line_coefficients<double, K, K + 1>(w0, phi2, cf);
-                } else {
-                    line_coefficients<double, K, K + 1>(LdsColumn<double, CB>{fsh + v * NB * CB + o}, phi2, cf);
-                }
-                line_eval<K>(cf, x[v]);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            double div[N1];
-            if (av) {
-                double cd[K];
-                line_coefficients<double, K, K>(Dv, phi2, cd);
-                line_eval<K>(cd, div);
-            }
-            double d[3][N1];
-            {
-                // the tensor at a point: xx, xy, xz, yy, yz, zz
-                auto tensor = [&](int t, double (&F)[6]) {
-                    const double rho = x[0][t];
-                    double pi = double(0);
-                    if (av) {
-                        const double pv = vnr_pi<double>(rho, div[t], hp, alpha, beta, cs, inv_dt);
-                        // learned sensor: the cell's bulk viscosity nu in place of the vNR one,
-                        // Pi = rho nu s at compressed points, with the Pi_max cap of the point
-                        const double sq = -div[t];
-                        double pl = fmin(rho * nu * sq, double(0.5) * rho * hp * hp * sq * inv_dt);
-                        pl = (sq > double(0) && nu > double(0)) ? pl : double(0);
-                        pi = learned ? pl : pv;
-                    }
-                    const double ir = rcp(rho);
-                    const double pw = cs2 * rho + pi;
-                    const double vx = x[1][t] * ir, vy = x[2][t] * ir, vz = x[3][t] * ir;
-                    F[0] = x[1][t] * vx + pw;
-                    F[1] = x[1][t] * vy;
-                    F[2] = x[1][t] * vz;
-                    F[3] = x[2][t] * vy + pw;
-                    F[4] = x[2][t] * vz;
-                    F[5] = x[3][t] * vz + pw;
-                };
-                double m[6][K];
-                auto step = [&](auto ps) {
-                    constexpr int P = decltype(ps)::value;
-                    double lo[6], hi[6];
-                    if constexpr (2 * P < K) tensor(P, lo);
-                    tensor(K - P, hi);
-#pragma unroll
-                    for (int j = 0; j < 6; ++j) line_moments_step<K, K, P>(lo[j], hi[j], m[j]);
-                    __builtin_amdgcn_sched_barrier(0);
-                };
-                step(std::integral_constant<int, 0>{});
-                if constexpr (K > 1) step(std::integral_constant<int, 1>{});
-                ctab<double> *lx = tab + TL::LWX + r * NL, *ly = tab + TL::LWY + r * NL, *lw = tab + TL::LWP + r * S::NB2;
-                // the rows' fluxes along x, y, z: lane 0 (-; xx, xy, xz), lane 1 (xy, yy, yz; xz, yz, zz).
-                // Of the two lines' moments the sum and (lane 0's minus lane 1's) meet the table
-                // entries of even and odd x parity (line_dx and line_dy are the graded order of the
-                // reduced pair, whose first exponent has the entry's parity in both cases).
-#pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    constexpr int comp[2][3] = {{1, 3, 4}, {2, 4, 5}};
-                    double e[3][K], o[3][K], dz[2][N1];
-#pragma unroll
-                    for (int f = 0; f < 3; ++f)
-#pragma unroll
-                        for (int n = 0; n < K; ++n) {
-                            // lane 0's row 1 is x momentum: xx, xy, xz
-                            const double own = i && !h ? m[f][n] : m[comp[i][f]][n];
-                            const double give = i && h ? m[f][n] : m[comp[i][f]][n];
-                            const double other = pair_swap(give);
-                            e[f][n] = own + other;
-                            o[f][n] = sg * (own - other);
-                        }
-                    line_derivative<K>(e[2], dz[0]);
-                    line_derivative<K>(o[2], dz[1]);
-#pragma unroll
-                    for (int l = 0; l < NB; ++l) {
-                        const int ea = M.e[l][0], eb = M.e[l][1], ec = M.e[l][2];
-                        if (ea) L[i][l] = fma(lx[line_dx(ea, eb)], ((ea - 1) & 1) ? o[0][ec] : e[0][ec], L[i][l]);
-                        if (eb) L[i][l] = fma(ly[line_dy(ea, eb)], (ea & 1) ? o[1][ec] : e[1][ec], L[i][l]);
-                        if (ec) L[i][l] = fma(lw[M.d2[2][l]], dz[ea & 1][ec], L[i][l]);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-            if (force) {
-                ctab<double> *lw = tab + TL::LWP + r * S::NB2;
-                double sr[3][N1];
-                double xr = 0.0, xi = 0.0, x2r = 0.0, x2i = 0.0;
-                if constexpr (FM != FM_DIRECT) line_phase<double, K>(ft, tx, pr, pim, sg, xr, xi, x2r, x2i);
-#pragma unroll
-                for (int t = 0; t < N1; ++t) {
-                    const int q = r + S::NF * t;
-                    double ac[3];
-                    if constexpr (FM == FM_DIRECT)
-                        direct_accel<double>(a.modes, a.nmodes, cijk, sg * tab[TL::VXI + 3 * q], tab[TL::VXI + 3 * q + 1],
-                                             tab[TL::VXI + 3 * q + 2], a.h, ac);
-                    else
-                        line_accel<double, K>(g, ty + N1 * t, xr, xi, x2r, x2i, ac);
-                    drive_source<double>(x[0][t], half_h, ac, sr[0][t], sr[1][t], sr[2][t]);
-                }
-                double z[3][N1];
-#pragma unroll
-                for (int v = 0; v < 3; ++v) {
-                    line_moments<K>(sr[v], z[v]);
-                    double &fs = v == 0 ? fs0 : (v == 1 ? fs1 : fs2);
-                    fs = fma(lw[0], z[v][0], fs);
-                }
-#pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    double e[N1], o[N1];
-#pragma unroll
-                    for (int n = 0; n < N1; ++n) {
-                        const double own = i && !h ? z[0][n] : z[1 + i][n];
-                        const double give = i && h ? z[0][n] : z[1 + i][n];
-                        const double other = pair_swap(give);
-                        e[n] = own + other;
-                        o[n] = sg * (own - other);
-                    }
-#pragma unroll
-                    for (int l = 0; l < NB; ++l)
-                        L[i][l] = fma(lw[M.d2[2][l]], (M.e[l][0] & 1) ? o[M.e[l][2]] : e[M.e[l][2]], L[i][l]);
-                }
-            }
-        }
-    };
-    if constexpr (FDIRECT) {
-        volume(std::integral_constant<int, FM_DIRECT>{}, 0);
-    } else {
-        const int p0 = __shfl(pencil, 0, 64);
-        if (force && __all(!active || pencil == p0))
-            volume(std::integral_constant<int, FM_UNIFORM>{}, __builtin_amdgcn_readfirstlane(p0));
-        else
-            volume(std::integral_constant<int, FM_LANE>{}, pencil);
-    }
-    // lane 0's first row is the density's, linear as in the one-lane kernel (its sums so far are
-    // not used)
-#pragma unroll
-    for (int l = 0; l < NB; ++l) {
-        double dr = 0.0;
-#pragma unroll
-        for (int d = 0; d < 3; ++d)
-#pragma unroll
-            for (int t = 0; t < DivMap<K>::MAXT; ++t)
-                if (DM.m[d][l][t] >= 0)
-                    dr = fma(8.0 * __builtin_sqrt(double(DM.f[d][l][t])), col[((1 + d) * NB + DM.m[d][l][t] - 1) * CB], dr);
-        L[0][l] = h ? L[0][l] : dr;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-
-    // ---- surface integral, with the low x and y face fluxes shared through LDS as in the
-    // one-lane kernel (cells of the block: CB consecutive cells)
-    int nbr[6], ijk[3];
-    neighbours(a.g, c, nbr, ijk);
-    const Field<double, 4> SRC = prim ? Field<double, 4>(a.u, a.vh, NB, nc) : U;
-    const int base = blk * CB;
-    const bool xsh = __all((unsigned)(nbr[1] - base) < (unsigned)CB);
-    const bool ysh = __all((unsigned)(nbr[3] - base) < (unsigned)CB);
-    // Every face leaves its moments in the cell's LDS column and lifts them from there.  The low x
-    // and y faces are the high faces of the neighbours below: a wave whose neighbours above all
-    // lie in the block lifts theirs (between two barriers) instead of computing its high face; a
-    // high face that is computed is stored only after the second barrier, when no other wave
-    // reads the columns any more.  (The first barrier also separates the columns' two uses.)
-#pragma unroll 1
-    for (int s = 0; s < 2; ++s) {
-        if (s == 1) {
-            __syncthreads();
-            if (xsh) lift_pair<K, 0, CB>(fsh + (nbr[1] - base), h, 1, tab, L);
-            __syncthreads();
-            if (xsh) break;
-        }
-        face_pair<K, 0, CB, PRIM>(SRC, bo, (unsigned)(s ? nbr[1] : nbr[0]) * 8u, s, h, tab, use_hllc, cs,
-                            cs2, L, col);
-    }
-#pragma unroll 1
-    for (int s = 0; s < 2; ++s) {
-        if (s == 1) {
-            __syncthreads();
-            if (ysh) lift_pair<K, 1, CB>(fsh + (nbr[3] - base), h, 1, tab, L);
-            __syncthreads();
-            if (ysh) break;
-        }
-        face_pair<K, 1, CB, PRIM>(SRC, bo, (unsigned)(s ? nbr[3] : nbr[2]) * 8u, s, h, tab, use_hllc, cs,
-                            cs2, L, col);
-    }
-#pragma unroll 1
-    for (int s = 0; s < 2; ++s)
-        face_pair<K, 2, CB, PRIM>(SRC, bo, (unsigned)(s ? nbr[5] : nbr[4]) * 8u, s, h, tab, use_hllc, cs,
-                            cs2, L, col);
-
-    const double inv4h = 0.25 / a.h;
-    if (active) {
-        double *ob = (double *)a.out;
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int l = 0; l < NB; ++l)
-                __builtin_nontemporal_store(L[i][l] * inv4h, &ob[((size_t)(2 * h + i) * NB + l) * ncs + c]);
-        if (a.pred_fail && h == 0) predict_failure<double>(a, dt, c, mass0, L[0][0] * inv4h);
-    }
-    if (force && a.part) {
-        double acc[4] = {0.0, 0.0, 0.0, 0.0};
-        if (active) {
-            acc[0] = 0.125 / half_h * fs0;
-            acc[1] = 0.125 / half_h * fs1;
-            acc[2] = 0.125 / half_h * fs2;
-            acc[3] = h ? 0.0 : mass0;
-        }
-        block_sum<4>(acc, lds);
-        if (threadIdx.x == 0)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a.part[blk * 4 + i] = acc[i];
     }
 }
 
@@ -2264,9 +1773,6 @@ __device__ __forceinline__ void stage_finish(T (&U)[4][Shape<K>::NB], ctab<T> *t
     const int nc = a.g.nc;
     if (a.flags & F_LIMIT) stage_limit<T, K>(U, tab, a, active, lds);
     if (active) store_field<T, K, 4>(Field<T, 4>(a.out, NB, nc), bo, U);
-    if (a.rho_out && active)
-#pragma unroll
-        for (int l = 0; l < NB; ++l) ((T *)a.rho_out)[(size_t)l * nc + c] = U[0][l];
     if (a.vh_out) project_and_bounds<T, K, SPLIT>(U, tab, a.vh_out, nc, bo, c, active, a.pa, a.part, blk, lds);
 }
 
@@ -2540,7 +2046,7 @@ __global__ void __launch_bounds__(BLOCK) k_drive_parts(RhsArgs a)
 // vhat of u and, optionally, the per-block time-step maxima and a reset of the failure flag
 template <typename T, int K>
 __global__ void __launch_bounds__(BLOCK) k_project(const void *u_, void *vh_, const void *tab_, Mesh g, ProjArgs pa,
-                                                   double *part, int *fail, void *rho_out)
+                                                   double *part, int *fail)
 {
     using S = Shape<K>;
     constexpr int NB = S::NB;
@@ -2555,9 +2061,6 @@ __global__ void __launch_bounds__(BLOCK) k_project(const void *u_, void *vh_, co
     ctab<T> *tab = as_tab<T>(tab_);
     T W[4][NB];
     load_field<T, K, 4>(Field<T, 4>(u_, NB, nc), bo, W);
-    if (rho_out && active)
-#pragma unroll
-        for (int l = 0; l < NB; ++l) ((T *)rho_out)[(size_t)l * nc + c] = W[0][l];
     project_and_bounds<T, K>(W, tab, vh_, nc, bo, c, active, pa, part, blk, lds);
 }
 
