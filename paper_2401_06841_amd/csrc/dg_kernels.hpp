@@ -399,48 +399,48 @@ constexpr bool split_projection() { return sizeof(T) == 8; }
 
 // The face flux at one point, in two parts, so that a face's tangential traces need not be held
 // beside the normal ones (Sec. 2.2 numerical flux; all values are twice the flux's): from the
-// density r and normal velocity v of the low (L) and high (R) side, the mass flux F0, the normal
-// momentum flux Fn, and the factors gL, gR that give each tangential momentum flux as
-// gL v_t,L + gR v_t,R.
+// density r and normal velocity v of the cell (o) and its neighbour (n), the mass flux F0, the
+// normal momentum flux Fn, and the factors go, gn that give each tangential momentum flux as
+// go v_t,o + gn v_t,n.  sg = 1 when the cell is the low side of the face, else -1: written in the
+// cell and its neighbour, with no choice of a low and a high side (the compiler turned that branch
+// into moves, a quarter of a face's instructions).
 //
 // Isothermal Rusanov flux: m_j v_n +- lambda m_j of a side is r (v_n +- lambda) times v_j, so
 // the factors are g = r (v_n +- lambda); the mass flux keeps the difference form.
 template <typename T>
-__device__ __forceinline__ void rusanov2(T cs, T cs2, T rL, T vL, T rR, T vR, T &F0, T &Fn, T &gL, T &gR)
+__device__ __forceinline__ void rusanov2(T cs, T cs2, T sg, T ro, T vo, T rn, T vn, T &F0, T &Fn, T &go, T &gn)
 {
-    // every fused multiply-add written out and no other contraction left to the compiler:
-    // the flux of a face is then the same bits whichever of its two cells computes it
+    // products of the two sides rounded alike and no contraction left to the compiler: the flux of a
+    // face is then the same bits whichever of its two cells computes it
 #pragma clang fp contract(off)
-    const T lam = fmax(fabs(vL), fabs(vR)) + cs;
-    F0 = fma(-lam, rR - rL, fma(rL, vL, rR * vR));
-    gL = rL * (vL + lam);
-    gR = rR * (vR - lam);
-    Fn = fma(cs2, rL + rR, fma(gL, vL, gR * vR));
+    const T lam = sg * (fmax(fabs(vo), fabs(vn)) + cs);
+    F0 = fma(lam, ro - rn, ro * vo + rn * vn);
+    go = ro * (vo + lam);
+    gn = rn * (vn - lam);
+    Fn = fma(cs2, ro + rn, go * vo + gn * vn);
 }
 
 // Isothermal HLLC-type flux (the counterpart of the HLLC solver of Sec. 2.2 for isothermal gas):
 // wave speeds S_L = min(v_L, v_R) - cs and S_R = max(v_L, v_R) + cs of the normal velocities;
 // density and normal momentum take the HLL flux, each tangential momentum is the mass flux times
-// the upwind tangential velocity
+// the upwind tangential velocity.  With S_L clipped to at most 0 and S_R to at least 0 the HLL
+// flux is the low (high) side's where all waves move one way.  In the cell and its neighbour: with
+// a = S_R and b = S_L when the cell is the low side, else a = S_L and b = S_R, it is
+// (a f_o - b f_n + a b (u_n - u_o)) / (a - b) either way.
 template <typename T>
-__device__ __forceinline__ void hllc2(T cs, T cs2, T rL, T vL, T rR, T vR, T &F0, T &Fn, T &gL, T &gR)
+__device__ __forceinline__ void hllc2(T cs, T cs2, T sg, T ro, T vo, T rn, T vn, T &F0, T &Fn, T &go, T &gn)
 {
 #pragma clang fp contract(off)
-    const T nL = rL * vL, nR = rR * vR;
-    const T SL = fmin(vL, vR) - cs;
-    const T SR = fmax(vL, vR) + cs;
-    const T FLn = fma(nL, vL, cs2 * rL);
-    const T FRn = fma(nR, vR, cs2 * rR);
-    const T iw = rcp(SR - SL);
-    const T sLR = SL * SR;
-    T f0 = fma(sLR, rR - rL, fma(SR, nL, -(SL * nR))) * iw;
-    T fn = fma(sLR, nR - nL, fma(SR, FLn, -(SL * FRn))) * iw;
-    f0 = SL >= T(0) ? nL : (SR <= T(0) ? nR : f0);
-    fn = SL >= T(0) ? FLn : (SR <= T(0) ? FRn : fn);
-    F0 = f0 + f0;
-    Fn = fn + fn;
-    gL = F0 >= T(0) ? F0 : T(0);
-    gR = F0 >= T(0) ? T(0) : F0;
+    const T no = ro * vo, nn = rn * vn;
+    const T SL = fmin(fmin(vo, vn) - cs, T(0)), SR = fmax(fmax(vo, vn) + cs, T(0));
+    const bool low = sg > T(0);
+    const T a = low ? SR : SL, b = low ? SL : SR;
+    const T iw = (sg + sg) * rcp(SR - SL), ab = SL * SR;
+    F0 = fma(ab, rn - ro, a * no - b * nn) * iw;
+    Fn = fma(ab, nn - no, a * fma(no, vo, cs2 * ro) - b * fma(nn, vn, cs2 * rn)) * iw;
+    const bool up = (F0 >= T(0)) == low;   // the cell is upwind
+    go = up ? F0 : T(0);
+    gn = up ? T(0) : F0;
 }
 
 // von Neumann-Richtmyer viscous pressure at one point (Sec. 3.1)
@@ -570,8 +570,10 @@ __device__ __forceinline__ void face_line_normal(const T (&Co)[2][Shape<K>::NB2]
     face_line_coefficients<T, K>(Cn[1], p1, c);
     line_eval<K>(c, vn);
     // one branch per line and combination of options, each with its own straight code
-    auto fluxes = [&](auto pr, auto &&flux) {
-        auto point = [&](int r, auto low) {
+    const T sg = s ? T(1) : T(-1);
+    auto fluxes = [&](auto pr, auto hl) {
+#pragma unroll
+        for (int r = 0; r < N1; ++r) {
             T io, in;
             if constexpr (!decltype(pr)::value) {
                 io = rcp(ro[r]);
@@ -579,57 +581,44 @@ __device__ __forceinline__ void face_line_normal(const T (&Co)[2][Shape<K>::NB2]
                 vo[r] *= io;
                 vn[r] *= in;
             }
-            if constexpr (decltype(low)::value) flux(ro[r], vo[r], rn[r], vn[r], F0[r], Fn[r], go[r], gn[r]);
-            else flux(rn[r], vn[r], ro[r], vo[r], F0[r], Fn[r], gn[r], go[r]);
+            if constexpr (decltype(hl)::value) hllc2(cs, cs2, sg, ro[r], vo[r], rn[r], vn[r], F0[r], Fn[r], go[r], gn[r]);
+            else rusanov2(cs, cs2, sg, ro[r], vo[r], rn[r], vn[r], F0[r], Fn[r], go[r], gn[r]);
             if constexpr (!decltype(pr)::value) {
                 go[r] *= io;
                 gn[r] *= in;
             }
-            if constexpr (sizeof(T) == 8 && K == 3) __builtin_amdgcn_sched_barrier(0);
-        };
-        if (s)
-#pragma unroll
-            for (int r = 0; r < N1; ++r) point(r, std::true_type{});
-        else
-#pragma unroll
-            for (int r = 0; r < N1; ++r) point(r, std::false_type{});
+        }
     };
-    auto solver = [&](auto pr) {
-        if (use_hllc)
-            fluxes(pr, [&](T rL, T vL, T rR, T vR, T &f0, T &fn, T &gL, T &gR) { hllc2(cs, cs2, rL, vL, rR, vR, f0, fn, gL, gR); });
-        else
-            fluxes(pr, [&](T rL, T vL, T rR, T vR, T &f0, T &fn, T &gL, T &gR) { rusanov2(cs, cs2, rL, vL, rR, vR, f0, fn, gL, gR); });
-    };
-    if (prim) solver(std::true_type{});
-    else solver(std::false_type{});
+    if (prim) {
+        if (use_hllc) fluxes(std::true_type{}, std::true_type{});
+        else fluxes(std::true_type{}, std::false_type{});
+    } else {
+        if (use_hllc) fluxes(std::false_type{}, std::true_type{});
+        else fluxes(std::false_type{}, std::false_type{});
+    }
 }
 
 // The flux of one tangential momentum along a line from its 2D coefficients of both sides and
 // the line's factors
 template <typename T, int K, typename B>
 __device__ __forceinline__ void face_line_tangential(const T (&Co)[Shape<K>::NB2], const T (&Cn)[Shape<K>::NB2],
-                                                     const B &p1, int s, const T (&go)[K + 1], const T (&gn)[K + 1],
+                                                     const B &p1, const T (&go)[K + 1], const T (&gn)[K + 1],
                                                      T (&F)[K + 1])
 {
-    // the low side's product is the fused one, whichever side the cell is on
 #pragma clang fp contract(off)
     T vn[K + 1], c[K + 1];
     face_line_coefficients<T, K>(Co, p1, c);
     line_eval<K>(c, F);
     face_line_coefficients<T, K>(Cn, p1, c);
     line_eval<K>(c, vn);
-    if (s)
 #pragma unroll
-        for (int r = 0; r <= K; ++r) F[r] = fma(go[r], F[r], gn[r] * vn[r]);
-    else
-#pragma unroll
-        for (int r = 0; r <= K; ++r) F[r] = fma(gn[r], vn[r], go[r] * F[r]);
+    for (int r = 0; r <= K; ++r) F[r] = go[r] * F[r] + gn[r] * vn[r];
 }
 
 // 2D moments M of one tangential momentum's flux from its 2D coefficients of both sides and the
 // factors in the column
 template <typename T, int K, int D>
-__device__ __forceinline__ void face_tangential(const T (&Co)[Shape<K>::NB2], const T (&Cn)[Shape<K>::NB2], int s,
+__device__ __forceinline__ void face_tangential(const T (&Co)[Shape<K>::NB2], const T (&Cn)[Shape<K>::NB2],
                                                 ctab<T> *tab, const T *col, T (&M2)[Shape<K>::NB2])
 {
     using S = Shape<K>;
@@ -645,7 +634,7 @@ __device__ __forceinline__ void face_tangential(const T (&Co)[Shape<K>::NB2], co
             go[r] = col[face_slot<T, K>(t, 1 + tan1(D), r)];
             gn[r] = col[face_slot<T, K>(t, 1 + tan2(D), r)];
         }
-        face_line_tangential<T, K>(Co, Cn, tab + TL::P1 + t * N1, s, go, gn, F);
+        face_line_tangential<T, K>(Co, Cn, tab + TL::P1 + t * N1, go, gn, F);
         line_moments<K>(F, m);
         add_line<T, K>(m, tab + TL::WLT + t * N1, M2);
     }
@@ -721,18 +710,20 @@ __device__ __forceinline__ void face(const Field<T, 4> &src, unsigned bo, unsign
     load_modes<T, K>(src.r[T2], src.pstride, bo, wo);
     load_modes<T, K>(src.r[T2], src.pstride, bn, wn);
     __builtin_amdgcn_sched_barrier(0);
-    face_tangential<T, K, D>(Co, Cn, s, tab, col, M1);
+    face_tangential<T, K, D>(Co, Cn, tab, col, M1);
     lift_moments<T, K, D>(M1, s, tab, L[T1]);
     collapse<T, K, D>(wo, s, tab, Co);
     collapse<T, K, D>(wn, 1 - s, tab, Cn);
     __builtin_amdgcn_sched_barrier(0);
-    face_tangential<T, K, D>(Co, Cn, s, tab, col, M2);
+    face_tangential<T, K, D>(Co, Cn, tab, col, M2);
     lift_moments<T, K, D>(M2, s, tab, L[T2]);
+    // (only the low x and y faces are read by a neighbour)
+    if constexpr (D < 2)
 #pragma unroll
-    for (int j = 0; j < S::NB2; ++j) {
-        col[face_slot<T, K>(j / N1, T1, j % N1)] = M1[j];
-        col[face_slot<T, K>(j / N1, T2, j % N1)] = M2[j];
-    }
+        for (int j = 0; j < S::NB2; ++j) {
+            col[face_slot<T, K>(j / N1, T1, j % N1)] = M1[j];
+            col[face_slot<T, K>(j / N1, T2, j % N1)] = M2[j];
+        }
     lift_normal<T, K, D>(col, s, tab, L);
 }
 
@@ -1170,13 +1161,13 @@ __device__ __forceinline__ void volume_mfma(const RhsArgs &a, ctab<float> *tab, 
 template <typename T, int K, bool VMFMA = false>
 constexpr int rhs_waves() { return VMFMA ? MFMA_WAVES : (sizeof(T) == 8 ? (K <= 2 ? 2 : 1) : (K <= 2 ? 4 : 2)); }
 
-// Whether the momentum weights wait in the block's LDS (the face columns, unused until the surface
-// integral) during the volume integral instead of in registers: FP32 at degree 2, whose 4 waves
-// per SIMD leave 128 registers (33 spilled without it; 3 waves without spills measured 2.79
-// against 2.71 ms per 128^3 step, though 0.188 against 0.190 ms at 33x20x27).  FP64 at degree 2
-// and FP32 at degree 3 fit (605 against 600 us per 64^3 step, 6.24 against 6.14 ms at 128^3).
+// How many variables' weights (the last ones) wait in the block's LDS (the face columns, unused
+// until the surface integral) during the volume integral instead of in registers: at degree 2 one
+// in FP64 (256 registers for 2 waves; 9 spilled without, 567 -> 552 us per 64^3 step; two: 560 us)
+// and three in FP32 (128 registers for 4 waves; 2.58 ms per 128^3 learned step against 2.64 ms
+// with two; 3 waves without spills 2.79 against 2.71 ms in an earlier form); the others fit.
 template <typename T, int K>
-constexpr bool momentum_in_lds() { return sizeof(T) == 4 && K == 2; }
+constexpr int volume_lds_vars() { return K == 2 ? (sizeof(T) == 8 ? 1 : 3) : 0; }
 
 // a lane's column of LDS values, stride ST
 template <typename T, int ST>
@@ -1201,7 +1192,7 @@ k_rhs(RhsArgs a, StageArgs st)
     using TL = TabLayout<K>;
     constexpr Modes<K> M = make_modes<K>();
     constexpr int NB = S::NB;
-    constexpr bool MLDS = momentum_in_lds<T, K>() && !VMFMA;
+    constexpr int LV0 = VMFMA ? 4 : 4 - volume_lds_vars<T, K>();    // variables LV0.. wait in LDS
     __shared__ double lds[4 * 4];
     __shared__ T fsh[S::NF * 4 * BLOCK];        // face moments, a column per cell (face_slot)
     ctab<T> *tab = as_tab<T>(a.tab);
@@ -1243,11 +1234,11 @@ k_rhs(RhsArgs a, StageArgs st)
         W[0][0] = U.get(0, 0, bo);
     }
 
-    if constexpr (MLDS)
+    if constexpr (LV0 < 4)
 #pragma unroll
-        for (int v = 1; v < 4; ++v)
+        for (int v = LV0; v < 4; ++v)
 #pragma unroll
-            for (int l = 0; l < NB; ++l) fsh[((v - 1) * NB + l) * BLOCK + threadIdx.x] = W[v][l];
+            for (int l = 0; l < NB; ++l) fsh[((v - LV0) * NB + l) * BLOCK + threadIdx.x] = W[v][l];
 
     ctab<T> *ft = as_tab<T>(a.ftab);
 
@@ -1258,8 +1249,9 @@ k_rhs(RhsArgs a, StageArgs st)
     T Dv[NDIV];
 #pragma unroll
     for (int m = 0; m < NDIV; ++m) Dv[m] = T(0);
-    bool learned = false;
-    T nu = T(0);
+    // viscosity of a compressed point, nu0 + nu1 s capped at numax (Sec. 3.1)
+    T nu1 = alpha * hp * hp, nu0 = beta * cs * hp;
+    const T numax = T(0.5) * hp * hp * inv_dt;
     if (av && !VMFMA) {
 #pragma unroll
         for (int d = 0; d < 3; ++d)
@@ -1273,9 +1265,10 @@ k_rhs(RhsArgs a, StageArgs st)
                 }
 #pragma unroll
         for (int m = 0; m < NDIV; ++m) Dv[m] *= two_h;
-        if (a.flags & F_LEARNED) {
-            learned = a.fb[c] == 0;
-            nu = ((const T *)a.nu)[c];
+        if ((a.flags & F_LEARNED) && a.fb[c] == 0) {
+            // learned sensor: the cell's bulk viscosity in place of the vNR one
+            nu1 = T(0);
+            nu0 = fmax(((const T *)a.nu)[c], T(0));
         }
     }
 
@@ -1302,24 +1295,19 @@ k_rhs(RhsArgs a, StageArgs st)
         for (int r = 0; r < S::NF; ++r) {
             ctab<T> *phi2 = tab + TL::F2 + r * S::NB2;
             T x[4][N1], c[N1];
-            line_coefficients<T, K, K + 1>(W[0], phi2, c);
-            line_eval<K>(c, x[0]);
-            if constexpr (MLDS) {
-                // (the offset is opaque, or the compiler would keep the loop-invariant weights in
-                // registers after all)
-                int o = threadIdx.x;
-                asm volatile("" : "+v"(o));
+            // (the offset is opaque, or the compiler would keep the loop-invariant weights in
+            // registers after all)
+            int o = threadIdx.x;
+            if constexpr (LV0 < 4) asm volatile("" : "+v"(o));
 #pragma unroll
-                for (int v = 1; v < 4; ++v) {
-                    line_coefficients<T, K, K + 1>(LdsColumn<T, BLOCK>{fsh + (v - 1) * NB * BLOCK + o}, phi2, c);
-                    line_eval<K>(c, x[v]);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            } else {
-#pragma unroll
-                for (int v = 1; v < 4; ++v) {
+            for (int v = 0; v < 4; ++v) {
+                if (v < LV0) {
                     line_coefficients<T, K, K + 1>(W[v], phi2, c);
                     line_eval<K>(c, x[v]);
+                } else {
+                    line_coefficients<T, K, K + 1>(LdsColumn<T, BLOCK>{fsh + (v - LV0) * NB * BLOCK + o}, phi2, c);
+                    line_eval<K>(c, x[v]);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
             }
             T div[N1];
@@ -1338,16 +1326,13 @@ k_rhs(RhsArgs a, StageArgs st)
                     const T rho = x[0][t];
                     T pi = T(0);
                     if (av) {
-                        const T pv = vnr_pi<T>(rho, div[t], hp, alpha, beta, cs, inv_dt);
-                        // learned sensor: the cell's bulk viscosity nu in place of the vNR one,
-                        // Pi = rho nu s at compressed points, with the Pi_max cap of the point
-                        const T sq = -div[t];
-                        T pl = fmin(rho * nu * sq, T(0.5) * rho * hp * hp * sq * inv_dt);
-                        pl = (sq > T(0) && nu > T(0)) ? pl : T(0);
-                        pi = learned ? pl : pv;
+                        // Pi = rho nu(s) s at compressed points (s = -div v > 0), nu(s) = alpha hp^2 s + beta cs hp
+                        // (a learned cell: its viscosity), at most rho hp^2 s / (2 dt) (Sec. 3.1)
+                        const T sq = fmax(-div[t], T(0));
+                        pi = rho * sq * fmin(fma(nu1, sq, nu0), numax);
                     }
                     const T ir = rcp(rho);
-                    const T pw = cs2 * rho + pi;
+                    const T pw = fma(cs2, rho, pi);
                     const T vx = x[1][t] * ir, vy = x[2][t] * ir, vz = x[3][t] * ir;
                     F[0] = x[1][t] * vx + pw;
                     F[1] = x[1][t] * vy;
@@ -1429,7 +1414,7 @@ k_rhs(RhsArgs a, StageArgs st)
                 for (int t = 0; t < DivMap<K>::MAXT; ++t)
                     if (DM.m[d][l][t] >= 0) {
                         const int m = DM.m[d][l][t];
-                        const T w = MLDS ? fsh[(d * NB + m) * BLOCK + threadIdx.x] : W[1 + d][m];
+                        const T w = 1 + d >= LV0 ? fsh[((1 + d - LV0) * NB + m) * BLOCK + threadIdx.x] : W[1 + d][m];
                         L[0][l] = fma(T(8.0 * __builtin_sqrt(double(DM.f[d][l][t]))), w, L[0][l]);
                     }
     };
