@@ -7,7 +7,7 @@
 // 16 g + i holds A[i][8g .. 8g+7], B[8g .. 8g+7][i] and accumulates D[4g .. 4g+3][i].
 // Activations are rounded to bf16 only where they feed a matrix instruction; bias, GELU,
 // the last layer and all accumulations are FP32.  Gradients are reduced per wave, then
-// summed over waves in a fixed order (deterministic).
+// summed over waves and blocks in a fixed order (deterministic).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -22,7 +22,7 @@ namespace dg {
 constexpr int NIN = DG_MLP_NIN, NH = DG_MLP_NHID, NPARAM = DG_MLP_NPARAM;
 constexpr int OFF_W1 = 0, OFF_B1 = NH * NIN, OFF_W2 = OFF_B1 + NH, OFF_B2 = OFF_W2 + NH * NH,
               OFF_W3 = OFF_B2 + NH, OFF_B3 = OFF_W3 + NH;
-constexpr int MLP_WAVES = MLP_PART_ROWS;  // waves of the gradient kernel: one per SIMD at its occupancy of 1
+constexpr int MLP_BLOCKS = MLP_PART_ROWS / 4;   // blocks of the gradient kernel: its 4 waves are one per SIMD
 constexpr double NU0 = 1e-3;            // nu scale of the target t = log(1 + nu/nu0)
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -30,10 +30,31 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ float gelu(float z) { return 0.5f * z * (1.0f + erff(z * 0.70710678118654752f)); }
 
-__device__ __forceinline__ float gelu_d(float z)
+// GELU and its derivative from one exponential: gelu = z Phi(z), gelu' = Phi(z) + z phi(z).  The
+// tail q = Phi(-|z|) = exp(-z^2/2) erfcx(|z|/sqrt 2)/2 is the same exponential times a polynomial
+// of degree 9 in t = 1/(1 + 0.33 |z|) (no constant term: q ~ t for large |z|), a weighted
+// least-squares fit of that quotient on 0 <= |z| <= 14 whose largest relative error is 5.5e-8.
+// Against 64 bits over |z| <= 8 the largest errors are 3.8e-7 (gelu) and 2.0e-7 (gelu'); with the
+// library's erff and expf 4.5e-7 and 1.4e-7, at three times the instructions, and the relative
+// error of gelu's negative tail (2.7e-6) there is 1, from 1 + erf.
+__device__ __forceinline__ void gelu_both(float z, float &f, float &d)
 {
-    const float cdf = 0.5f * (1.0f + erff(z * 0.70710678118654752f));
-    return cdf + z * 0.39894228040143268f * expf(-0.5f * z * z);
+    const float a = fabsf(z);
+    const float e = __builtin_amdgcn_exp2f(z * z * -0.72134752044448170f);
+    const float t = rcp(fmaf(0.33f, a, 1.0f));
+    float p = -0.0208073827f;
+    p = fmaf(p, t, 0.123079021f);
+    p = fmaf(p, t, -0.267184559f);
+    p = fmaf(p, t, 0.224629068f);
+    p = fmaf(p, t, -0.0565259163f);
+    p = fmaf(p, t, 0.121818947f);
+    p = fmaf(p, t, 0.111065914f);
+    p = fmaf(p, t, 0.132302778f);
+    p = fmaf(p, t, 0.131622159f);
+    const float q = p * t * e;
+    const float cdf = z < 0.0f ? q : 1.0f - q;
+    f = z * cdf;
+    d = fmaf(z, 0.39894228040143268f * e, cdf);
 }
 
 __device__ __forceinline__ f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c)
@@ -41,13 +62,31 @@ __device__ __forceinline__ f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c)
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
+// the 16-slot form: lane 16 g + i holds A[i][4g .. 4g+3], B[4g .. 4g+3][i]
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ f32x4 mfma(bf16x4 a, bf16x4 b, f32x4 c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, a), __builtin_bit_cast(s16x4, b), c, 0, 0, 0);
+}
+
 __device__ __forceinline__ void wave_fence() { __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront"); }
 
-// sum over the 16 lanes of a lane group (same g)
+// sum over the 16 lanes of a lane group (same g), in pairs at distance 1, 2, 4, 8: the group is a
+// row of the data-parallel moves, so nothing goes through LDS (lanes that already hold equal sums
+// may be paired in mirrored order)
+template <int CTRL>
+__device__ __forceinline__ float row_move(float v)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xF, 0xF, false));
+}
+
 __device__ __forceinline__ float group_sum(float v)
 {
-#pragma unroll
-    for (int o = 1; o < 16; o <<= 1) v += __shfl_xor(v, o, 64);
+    v += row_move<0xB1>(v);     // quad_perm [1, 0, 3, 2]
+    v += row_move<0x4E>(v);     // quad_perm [2, 3, 0, 1]
+    v += row_move<0x141>(v);    // row_half_mirror
+    v += row_move<0x140>(v);    // row_mirror
     return v;
 }
 
@@ -75,7 +114,8 @@ __device__ __forceinline__ void load_net(const float *__restrict__ P, Net &w)
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const int k = 8 * g + j;
-            w.b1[t][j] = (__bf16)(k < NIN ? P[OFF_W1 + (16 * t + i) * NIN + k] : 0.0f);
+            const float v = P[OFF_W1 + (16 * t + i) * NIN + (k < NIN ? k : 0)];   // (no branch per load)
+            w.b1[t][j] = (__bf16)(k < NIN ? v : 0.0f);
         }
 #pragma unroll
         for (int s = 0; s < 2; ++s)
@@ -91,38 +131,43 @@ __device__ __forceinline__ void load_net(const float *__restrict__ P, Net &w)
 // per-wave LDS scratch of one tile (bf16)
 struct alignas(16) TileLds {
     __bf16 h1[16 * NH];     // H1 row-major [row][n]
-    __bf16 h1t[NH * 16];    // H1 transposed [n][row]
-    __bf16 g2[16 * NH];     // G2 row-major
-    __bf16 g2t[NH * 16];    // G2 transposed
-    __bf16 g1t[NH * 16];    // G1 transposed
-    __bf16 xt[32 * 16];     // X transposed [m][row] (m >= 20: 0)
 };
 
-// forward pass of the 16-row tile starting at row0 (rows >= n are zero inputs).
-// z1, z2: pre-activations in the D layout (rows 4g+j, column 16t+i); y[j]: output of row
-// 4g+j (valid in every lane of the group).
-__device__ __forceinline__ void forward_tile(const float *__restrict__ x, int row0, int n, const Net &w, TileLds &L,
-                                             bool keep, float (&z1)[4][4], float (&z2)[4][4], float (&y)[4])
+// the features 8g .. 8g+7 of row r as a matrix operand (rows past n and features past 20: zeros);
+// a row is 80 bytes, of which only 4-byte alignment is known
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+struct Row {
+    f32x4 lo, hi;
+};
+__device__ __forceinline__ Row load_row(const float *__restrict__ x, long r, int n)
+{
+    const int g = (threadIdx.x & 63) >> 4;
+    Row v = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}};
+    if (r < n && g < 3) {
+        const f4u *p = (const f4u *)(x + (size_t)r * NIN + 8 * g);
+        v.lo = p[0];
+        if (g < 2) v.hi = p[1];
+    }
+    return v;
+}
+
+// forward pass of a 16-row tile from the lane's row of inputs (row i of the tile).  y[j]: output of
+// row 4g+j (valid in every lane of the group).
+__device__ __forceinline__ void forward_tile(const Row &xr, const Net &w, TileLds &L, float (&y)[4])
 {
     const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
-    const int r = row0 + i;
     bf16x8 a;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const int k = 8 * g + j;
-        const float v = (r < n && k < NIN) ? x[(size_t)r * NIN + k] : 0.0f;
-        a[j] = (__bf16)v;
-        if (keep) L.xt[(8 * g + j) * 16 + i] = (__bf16)v;
+    for (int j = 0; j < 4; ++j) {
+        a[j] = (__bf16)xr.lo[j];
+        a[4 + j] = (__bf16)xr.hi[j];
     }
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
         f32x4 d = mfma(a, w.b1[t], f32x4{0.0f, 0.0f, 0.0f, 0.0f});
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            z1[t][j] = d[j] + w.bias1[t];
-            const __bf16 h = (__bf16)gelu(z1[t][j]);
-            L.h1[(4 * g + j) * NH + 16 * t + i] = h;
-            if (keep) L.h1t[(16 * t + i) * 16 + 4 * g + j] = h;
+            L.h1[(4 * g + j) * NH + 16 * t + i] = (__bf16)gelu(d[j] + w.bias1[t]);
         }
     }
     wave_fence();
@@ -136,8 +181,7 @@ __device__ __forceinline__ void forward_tile(const float *__restrict__ x, int ro
         d = mfma(a2[1], w.b2[1][t], d);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            z2[t][j] = d[j] + w.bias2[t];
-            p[j] += gelu(z2[t][j]) * w.w3[t];
+            p[j] += gelu(d[j] + w.bias2[t]) * w.w3[t];
         }
     }
 #pragma unroll
@@ -164,20 +208,23 @@ __global__ void __launch_bounds__(256) k_mlp_forward(const float *__restrict__ P
     load_net(P, w);
     const int ntile = (n + 15) / 16;
     const int nw = gridDim.x * 4;
+    Row next = load_row(x, (long)(blockIdx.x * 4 + wave) * 16 + i, n);
     for (int tile = blockIdx.x * 4 + wave; tile < ntile; tile += nw) {
-        float z1[4][4], z2[4][4], yy[4];
-        forward_tile(x, tile * 16, n, w, lds[wave], false, z1, z2, yy);
-        if (i == 0) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int r = tile * 16 + 4 * g + j;
-                if (r >= n) continue;
-                if (y) y[r] = yy[j];
-                if (nu) {
-                    const T v = (T)fmax(NU0 * expm1((double)yy[j]), 0.0);
-                    nu[r] = v;
-                    if (vmax && fb[r] == 0) vm = fmax(vm, fmax((double)v, 0.0));
-                }
+        float yy[4];
+        const Row xr = next;
+        next = load_row(x, ((long)tile + nw) * 16 + i, n);      // in flight while this tile is worked on
+        forward_tile(xr, w, lds[wave], yy);
+        // lane i < 4 of each group finishes row 4g + i (one exponential for all 16 rows; four in a row in
+        // lane 0 were a tenth of the pass: 398 -> 348 us for 128^3 cells, 315 us with the sums over the
+        // groups in data-parallel moves and the inputs loaded a tile ahead)
+        const int r = tile * 16 + 4 * g + i;
+        if (i < 4 && r < n) {
+            const float yr = i == 0 ? yy[0] : (i == 1 ? yy[1] : (i == 2 ? yy[2] : yy[3]));
+            if (y) y[r] = yr;
+            if (nu) {
+                const T v = (T)fmax(NU0 * expm1((double)yr), 0.0);
+                nu[r] = v;
+                if (vmax && fb[r] == 0) vm = fmax(vm, fmax((double)v, 0.0));
             }
         }
     }
@@ -190,158 +237,250 @@ __global__ void __launch_bounds__(256) k_mlp_forward(const float *__restrict__ P
 }
 
 // --------------------------------------------------------------- gradient
-// Mean-squared-error loss L = (1/n) sum (y - t)^2 and dL/dparams; each wave writes its
-// partial sums to part[wave][NPARAM + 1] (the last entry is the partial loss sum).
-__global__ void __launch_bounds__(256) k_mlp_grad(const float *__restrict__ P, const float *__restrict__ x,
-                                                  const float *__restrict__ tgt, int n, float *__restrict__ part)
+// four FP32 values as bf16, into half HALF of a matrix operand
+template <int HALF>
+__device__ __forceinline__ void pack4(const f32x4 &v, bf16x8 &o)
 {
-    __shared__ TileLds lds[4];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
-    const int gw = blockIdx.x * 4 + wave;
-    const int nw = gridDim.x * 4;
-    TileLds &L = lds[wave];
-    Net w;
-    load_net(P, w);
-    // layer-2 weights as the B operand of G2 W2: W2[32s+8g+j][16t+i]
-    bf16x8 bw2[2][4];
 #pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int j = 0; j < 8; ++j) bw2[s][t][j] = (__bf16)P[OFF_W2 + (32 * s + 8 * g + j) * NH + 16 * t + i];
+    for (int j = 0; j < 4; ++j) o[4 * HALF + j] = (__bf16)v[j];
+}
 
-    f32x4 aw2[4][4], aw1[4][2];
+__device__ __forceinline__ bf16x4 to_bf16(const f32x4 &v)
+{
+    bf16x4 o;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) o[j] = (__bf16)v[j];
+    return o;
+}
+
+// Mean-squared-error loss L = (1/n) sum (y - t)^2 and dL/dparams; each block writes the sums of
+// its rows to part[block][NPARAM + 1] (the last entry is the loss sum).
+//
+// A wave takes a 16-row tile at a time and keeps it in registers throughout.  The layers run
+// transposed, D[neuron][row] = W X^T: lane (g, i) then holds, for row i, the neurons 16t + 4g + j
+// (t, j < 4), which is an operand of the next layer's product as it is when slot (s, g, jj) of the
+// contraction stands for neuron 16(2s + (jj >> 2)) + 4g + (jj & 3) on both sides.  The weight
+// gradients contract over rows: their operands need a neuron per lane and rows in the slots, the
+// transpose, which the matrix cores give too: the held values as the left operand times a 0/1
+// matrix that picks the neurons 16t + i is D[row][16t + i], exactly (one product per 16 neurons
+// instead of 16-bit stores and loads through LDS, 88 per tile before).  Every lane needs GELU and
+// its derivative of 32 values per tile, which bounds the kernel: both come from one exponential
+// (gelu_both).  One wave per SIMD: the weights in operand form (80 registers) and the gradient
+// accumulators (144) beside the tile (32 rows at a time spilled 14-51 registers).  One gradient and
+// update, before and after: 197 -> 61 us at 262,144 rows, 45 -> 25 us at 16,000, 25 -> 17 us at
+// 1,000, 675 -> 180 us at 1,000,000.
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1)))
+k_mlp_grad(const float *__restrict__ P, const float *__restrict__ x, const float *__restrict__ tgt, int n,
+           float *__restrict__ part)
+{
+    // the parameters on entry (a wave's operands are built from here: one coalesced read of them per
+    // block), the waves' gradient sums at the end
+    constexpr int ROW = (NPARAM + 1 + 3) / 4 * 4;
+    __shared__ alignas(16) float red[4][ROW];
+    // the FP32 vectors of the network: biases and last layer (a lane's four neurons are one 16-byte
+    // read; in registers they made the kernel spill)
+    __shared__ f32x4 vec[3][NH / 4];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
+    const int nw = gridDim.x * 4;
+    Row next = load_row(x, (long)(blockIdx.x * 4 + wave) * 16 + i, n);
+    float *Q = red[0];
+#pragma unroll
+    for (int j = 0; j < (NPARAM + 255) / 256; ++j) {
+        const int p = 256 * j + threadIdx.x;
+        if (p < NPARAM) Q[p] = P[p];
+    }
+    __syncthreads();
+    if (threadIdx.x < NH) {
+        ((float *)vec[0])[threadIdx.x] = Q[OFF_B1 + threadIdx.x];
+        ((float *)vec[1])[threadIdx.x] = Q[OFF_B2 + threadIdx.x];
+        ((float *)vec[2])[threadIdx.x] = Q[OFF_W3 + threadIdx.x];
+    }
+    // neuron of contraction slot (s, g, jj)
+    auto neuron = [&](int s, int jj) { return 16 * (2 * s + (jj >> 2)) + 4 * g + (jj & 3); };
+    bf16x8 w1[4], w2[2][4], w2t[2][4], sel[2];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+#pragma unroll
+        for (int jj = 0; jj < 8; ++jj) {
+            const int k = 8 * g + jj;
+            const float w = Q[OFF_W1 + (16 * t + i) * NIN + (k < NIN ? k : 0)];   // (no branch per load)
+            w1[t][jj] = (__bf16)(k < NIN ? w : 0.0f);
+        }
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int jj = 0; jj < 8; ++jj) {
+                w2[s][t][jj] = (__bf16)Q[OFF_W2 + (16 * t + i) * NH + neuron(s, jj)];
+                w2t[s][t][jj] = (__bf16)Q[OFF_W2 + neuron(s, jj) * NH + 16 * t + i];
+            }
+    }
+    const float b3 = Q[OFF_B3];
+    __syncthreads();
+    // sel[p]: picks, of the 8 values of a slot group, the one of half p that belongs to lane i
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int jj = 0; jj < 8; ++jj) sel[p][jj] = (__bf16)((jj >> 2) == p && 4 * g + (jj & 3) == i ? 1.0f : 0.0f);
+
+    const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    f32x4 aw2[4][4], aw1[4][2], gb1[4], gb2[4], gw3[4];
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
 #pragma unroll
-        for (int b = 0; b < 4; ++b) aw2[a][b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int b = 0; b < 2; ++b) aw1[a][b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int b = 0; b < 4; ++b) aw2[a][b] = zero;
+        aw1[a][0] = aw1[a][1] = zero;
+        gb1[a] = gb2[a] = gw3[a] = zero;
     }
-    float gb1[4] = {0, 0, 0, 0}, gb2[4] = {0, 0, 0, 0}, gw3[4] = {0, 0, 0, 0};
     float gb3 = 0.0f, loss = 0.0f;
     const float inv_n = 1.0f / (float)n;
-    const int ntile = (n + 15) / 16;
-    const bf16x8 zero8 = {};
-
-    for (int tile = gw; tile < ntile; tile += nw) {
-        float z1[4][4], z2[4][4], y[4];
-        forward_tile(x, tile * 16, n, w, L, true, z1, z2, y);
-        float g3[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int r = tile * 16 + 4 * g + j;
-            const float e = r < n ? y[j] - tgt[r] : 0.0f;
-            g3[j] = 2.0f * inv_n * e;
-            if (i == 0) loss += e * e;
-            if (i == 0) gb3 += g3[j];
-        }
-        // last layer and G2 = g3 W3 gelu'(z2)
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                gw3[t] += g3[j] * gelu(z2[t][j]);
-                const float v = g3[j] * w.w3[t] * gelu_d(z2[t][j]);
-                gb2[t] += v;
-                const __bf16 b = (__bf16)v;
-                L.g2[(4 * g + j) * NH + 16 * t + i] = b;
-                L.g2t[(16 * t + i) * 16 + 4 * g + j] = b;
-            }
-        wave_fence();
-        // dW2[n][k] += sum_rows G2[row][n] H1[row][k]  (K = 16 rows, upper half zero)
-        bf16x8 ag[4], bh[4];
+    const int ntile = (int)(((long)n + 15) / 16);
+    for (int tile = blockIdx.x * 4 + wave; tile < ntile; tile += nw) {
+        const f32x4 *b1 = vec[0] + g, *b2 = vec[1] + g, *w3 = vec[2] + g;
+        const int r = tile * 16 + i;
+        const bool in = r < n;
+        bf16x8 xb, hb[2], gb[2], gc[2];
+        pack4<0>(next.lo, xb);
+        pack4<1>(next.hi, xb);
+        next = load_row(x, ((long)tile + nw) * 16 + i, n);      // in flight while this tile is worked on
+        const float target = in ? tgt[r] : 0.0f;
+        f32x4 d1[4], d2[4], h2[4];
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-            ag[t] = g < 2 ? *(const bf16x8 *)&L.g2t[(16 * t + i) * 16 + 8 * g] : zero8;
-            bh[t] = g < 2 ? *(const bf16x8 *)&L.h1t[(16 * t + i) * 16 + 8 * g] : zero8;
+            const f32x4 z = mfma(w1[t], xb, zero) + b1[4 * t];
+            f32x4 h;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                float f, d;
+                gelu_both(z[j], f, d);
+                h[j] = f;
+                d1[t][j] = d;
+            }
+            if (t & 1) pack4<1>(h, hb[t >> 1]);
+            else pack4<0>(h, hb[t >> 1]);
+        }
+        // layer 2 and the output of row i, summed over the neurons of the lane, then over g
+        float y = 0.0f;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            f32x4 z = mfma(w2[0][t], hb[0], zero);
+            z = mfma(w2[1][t], hb[1], z) + b2[4 * t];
+            const f32x4 w3t = w3[4 * t];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                float f, d;
+                gelu_both(z[j], f, d);
+                h2[t][j] = f;
+                d2[t][j] = d;
+                y = fmaf(f, w3t[j], y);
+            }
+        }
+        y = across_groups(y) + b3;
+        const float e = in ? y - target : 0.0f;
+        const float g3 = 2.0f * inv_n * e;
+        if (g == 0) {
+            loss += e * e;
+            gb3 += g3;
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            gw3[t] += g3 * h2[t];
+            const f32x4 v = (g3 * w3[4 * t]) * d2[t];
+            gb2[t] += v;
+            if (t & 1) pack4<1>(v, gb[t >> 1]);
+            else pack4<0>(v, gb[t >> 1]);
+        }
+        // rows into the slots, a neuron per lane: dW2[m][k] += sum_rows G2[row][m] H1[row][k]
+        bf16x4 ta[4], tb[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            ta[t] = to_bf16(mfma(gb[t >> 1], sel[t & 1], zero));
+            tb[t] = to_bf16(mfma(hb[t >> 1], sel[t & 1], zero));
         }
 #pragma unroll
         for (int tn = 0; tn < 4; ++tn)
 #pragma unroll
-            for (int tk = 0; tk < 4; ++tk) aw2[tn][tk] = mfma(ag[tn], bh[tk], aw2[tn][tk]);
-        // G1 = (G2 W2) gelu'(z1)
-        bf16x8 a2[2];
-#pragma unroll
-        for (int s = 0; s < 2; ++s) a2[s] = *(const bf16x8 *)&L.g2[i * NH + 32 * s + 8 * g];
+            for (int tk = 0; tk < 4; ++tk) aw2[tn][tk] = mfma(ta[tn], tb[tk], aw2[tn][tk]);
+        // G1 = (W2^T G2) gelu'(z1)
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-            f32x4 d = mfma(a2[0], bw2[0][t], f32x4{0.0f, 0.0f, 0.0f, 0.0f});
-            d = mfma(a2[1], bw2[1][t], d);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float v = d[j] * gelu_d(z1[t][j]);
-                gb1[t] += v;
-                L.g1t[(16 * t + i) * 16 + 4 * g + j] = (__bf16)v;
-            }
+            f32x4 z = mfma(w2t[0][t], gb[0], zero);
+            z = mfma(w2t[1][t], gb[1], z) * d1[t];
+            gb1[t] += z;
+            if (t & 1) pack4<1>(z, gc[t >> 1]);
+            else pack4<0>(z, gc[t >> 1]);
         }
-        wave_fence();
-        // dW1[k][m] += sum_rows G1[row][k] X[row][m]
-        bf16x8 bx[2];
+        // dW1[k][f] += sum_rows G1[row][k] X[row][f]
 #pragma unroll
-        for (int tm = 0; tm < 2; ++tm) bx[tm] = g < 2 ? *(const bf16x8 *)&L.xt[(16 * tm + i) * 16 + 8 * g] : zero8;
+        for (int p = 0; p < 2; ++p) tb[p] = to_bf16(mfma(xb, sel[p], zero));
 #pragma unroll
-        for (int tk = 0; tk < 4; ++tk) {
-            const bf16x8 a1 = g < 2 ? *(const bf16x8 *)&L.g1t[(16 * tk + i) * 16 + 8 * g] : zero8;
+        for (int t = 0; t < 4; ++t) {
+            ta[t] = to_bf16(mfma(gc[t >> 1], sel[t & 1], zero));
 #pragma unroll
-            for (int tm = 0; tm < 2; ++tm) aw1[tk][tm] = mfma(a1, bx[tm], aw1[tk][tm]);
+            for (int p = 0; p < 2; ++p) aw1[t][p] = mfma(ta[t], tb[p], aw1[t][p]);
         }
-        wave_fence();
     }
-    // write this wave's partial gradient
-    float *pw = part + (size_t)gw * (NPARAM + 1);
+    // the neurons' sums over the 16 lanes (rows) of a group, all waves at once
 #pragma unroll
-    for (int tn = 0; tn < 4; ++tn)
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            gb1[t][j] = group_sum(gb1[t][j]);
+            gb2[t][j] = group_sum(gb2[t][j]);
+            gw3[t][j] = group_sum(gw3[t][j]);
+        }
+    gb3 = group_sum(gb3);
+    loss = group_sum(loss);
+    // every wave's sums into its own row, then the block's in wave order
+    float *own = red[wave];
+#pragma unroll
+    for (int tn = 0; tn < 4; ++tn) {
 #pragma unroll
         for (int tk = 0; tk < 4; ++tk)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) pw[OFF_W2 + (16 * tn + 4 * g + j) * NH + 16 * tk + i] = aw2[tn][tk][j];
+            for (int j = 0; j < 4; ++j) own[OFF_W2 + (16 * tn + 4 * g + j) * NH + 16 * tk + i] = aw2[tn][tk][j];
 #pragma unroll
-    for (int tk = 0; tk < 4; ++tk)
+        for (int p = 0; p < 2; ++p) {
+            const int f = 8 * (i >> 2) + 4 * p + (i & 3);      // input feature of column i of half p
+            if (f < NIN)
 #pragma unroll
-        for (int tm = 0; tm < 2; ++tm)
+                for (int j = 0; j < 4; ++j) own[OFF_W1 + (16 * tn + 4 * g + j) * NIN + f] = aw1[tn][p][j];
+        }
+        if (i == 0)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const int m = 16 * tm + i;
-                if (m < NIN) pw[OFF_W1 + (16 * tk + 4 * g + j) * NIN + m] = aw1[tk][tm][j];
+                own[OFF_B1 + 16 * tn + 4 * g + j] = gb1[tn][j];
+                own[OFF_B2 + 16 * tn + 4 * g + j] = gb2[tn][j];
+                own[OFF_W3 + 16 * tn + 4 * g + j] = gw3[tn][j];
             }
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        const float s1 = across_groups(gb1[t]);
-        const float s2 = across_groups(gb2[t]);
-        const float s3 = across_groups(gw3[t]);
-        if (g == 0) {
-            pw[OFF_B1 + 16 * t + i] = s1;
-            pw[OFF_B2 + 16 * t + i] = s2;
-            pw[OFF_W3 + 16 * t + i] = s3;
-        }
     }
-    const float sb3 = across_groups(gb3);
-    const float sl = across_groups(loss);
     if (lane == 0) {
-        pw[OFF_B3] = sb3;
-        pw[NPARAM] = sl;
+        own[OFF_B3] = gb3;
+        own[NPARAM] = loss;
     }
+    __syncthreads();
+    float *pw = part + (size_t)blockIdx.x * (NPARAM + 1);
+    for (int p = threadIdx.x; p <= NPARAM; p += 256) pw[p] = ((red[0][p] + red[1][p]) + red[2][p]) + red[3][p];
 }
 
-// fixed-order sum of the per-wave partials: grad[p] and loss = sum / n.  A block takes 64
-// entries; its wave w sums the rows w, w+4, w+8, ... in order, and the four wave sums are
-// added in wave order.
-__global__ void __launch_bounds__(256) k_mlp_reduce(const float *__restrict__ part, int nwaves, int n,
+// fixed-order sum of the per-block partials: grad[p] and loss = sum / n.  A block takes 16
+// entries; its 16 lane groups sum the rows r, r+16, r+32, ... in order, and the group sums are
+// added in order.
+__global__ void __launch_bounds__(256) k_mlp_reduce(const float *__restrict__ part, int nrows, int n,
                                                     float *__restrict__ grad, float *__restrict__ loss)
 {
-    __shared__ float lds[4][64];
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int p = blockIdx.x * 64 + lane;
+    __shared__ float lds[16][16];
+    const int r = threadIdx.x >> 4, e = threadIdx.x & 15;
+    const int p = blockIdx.x * 16 + e;
     float s = 0.0f;
     if (p <= NPARAM)
-#pragma unroll 8
-        for (int wv = w; wv < nwaves; wv += 4) s += part[(size_t)wv * (NPARAM + 1) + p];
-    lds[w][lane] = s;
+#pragma unroll 16
+        for (int row = r; row < nrows; row += 16) s += part[(size_t)row * (NPARAM + 1) + p];
+    lds[r][e] = s;
     __syncthreads();
-    if (w == 0 && p <= NPARAM) {
-        const float t = ((lds[0][lane] + lds[1][lane]) + lds[2][lane]) + lds[3][lane];
+    if (r == 0 && p <= NPARAM) {
+        float t = lds[0][e];
+#pragma unroll
+        for (int k = 1; k < 16; ++k) t += lds[k][e];
         if (p < NPARAM) grad[p] = t;
         else loss[0] = t / (float)n;
     }
@@ -504,12 +643,11 @@ __global__ void k_fill_int(int *__restrict__ p, int n, int value)
 
 using namespace dg;
 
-// gradient: at most MLP_WAVES waves, one partial-sum row each
+// gradient: at most MLP_BLOCKS blocks, one partial-sum row each
 static int mlp_blocks(int n)
 {
-    const int ntile = (n + 15) / 16;
-    int nw = ntile < MLP_WAVES ? ntile : MLP_WAVES;
-    return (nw + 3) / 4;
+    const int ntile = (int)(((long)n + 15) / 16);
+    return ntile < 4 * MLP_BLOCKS ? (ntile + 3) / 4 : MLP_BLOCKS;
 }
 
 // forward: one full round of waves at the kernel's occupancy (3 waves per SIMD), each wave
@@ -562,8 +700,8 @@ int dg_mlp_grad(dg_ctx *c, const float *P, const float *x, const float *t, int n
     const int nb = mlp_blocks(n);
     hipLaunchKernelGGL(k_mlp_grad, dim3(nb), dim3(256), 0, c->stream, P, x, t, n, mlp_part(c));
     LAUNCHCHK(c);
-    hipLaunchKernelGGL(k_mlp_reduce, dim3((NPARAM + 1 + 63) / 64), dim3(256), 0, c->stream, (const float *)mlp_part(c),
-                       nb * 4, n, grad, loss);
+    hipLaunchKernelGGL(k_mlp_reduce, dim3((NPARAM + 1 + 15) / 16), dim3(256), 0, c->stream, (const float *)mlp_part(c),
+                       nb, n, grad, loss);
     LAUNCHCHK(c);
     return DG_OK;
 }
