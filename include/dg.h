@@ -80,8 +80,9 @@ enum dg_flags {
                                   with mean-free driving on the driving shell, whose mean the split path
                                   sums in modal form).  With neither flag the split is used where it
                                   measured faster (meshes of at least 2^21 cells); FP64 at degree 3
-                                  and DG_VOLUME_MFMA never split.  Both flags together:
-                                  DG_EINVAL */
+                                  and DG_VOLUME_MFMA never split.  (Without either flag meshes of a
+                                  few ten thousand cells add up the right-hand side in another order:
+                                  the same results to rounding.)  Both flags together: DG_EINVAL */
 };
 
 typedef struct dg_config {

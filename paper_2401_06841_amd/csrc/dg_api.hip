@@ -226,6 +226,21 @@ void build_mfma_tables(const std::vector<double> &t, std::vector<float> &mt)
     }
 }
 
+// The largest mesh whose right-hand side shares 64 cells between the four waves of a block (k_rhs
+// with WSPLIT).  A block of 256 cells there leaves most SIMDs with one wave or none, and the kernel
+// takes as long as one wave's chain of loads and arithmetic; with 64 cells per block each wave has a
+// quarter of that chain, and what it costs (both sides' fluxes on the shared faces, the sums through
+// LDS) pays until the blocks fill the chip's 256 compute units about three (FP64) or four (FP32)
+// times.  Driven steps, 256 cells per block -> 64, us:
+//   cells     FP64: degree 1    degree 2    degree 3     FP32: degree 1    degree 2    degree 3
+//   4096         89 ->  75   172 -> 121   378 -> 216         76 -> 66   129 ->  91   245 -> 148
+//   16250       102 ->  75   204 -> 125   441 -> 230         85 -> 65   155 ->  94   283 -> 153
+//   32768        99 ->  80   203 -> 145   436 -> 341         81 -> 67   150 ->  98   272 -> 167
+//   46656       105 -> 100   217 -> 191   467 -> 437         86 -> 70   161 -> 107   294 -> 221
+//   64000       107 -> 110   223 -> 214   499 -> 553         86 -> 75   164 -> 140   301 -> 247
+//   85184       130 -> 144   294 -> 298   817 -> 770         94 -> 97   182 -> 161   347 -> 322
+constexpr int shared_cells_max(size_t es) { return es == 8 ? 49152 : 65536; }
+
 size_t align_up(size_t x) { return (x + 255) & ~size_t(255); }
 
 }  // namespace
@@ -260,8 +275,8 @@ static void layout(dg_ctx *c, size_t *total)
     c->off.feat = o; o += learned ? align_up(nc * DG_MLP_NIN * 4) : 0;
     c->off.lab = o; o += learned ? align_up(nc * 8) : 0;
     c->off.mlp = o; o += align_up((size_t)MLP_PART_ROWS * (DG_MLP_NPARAM + 1) * 4);   // per-wave network gradients
-    // per-block partials
-    c->off.part = o; o += align_up((size_t)c->nblk * 4 * 8);
+    // per-block partials (small meshes: a right-hand-side block may hold 64 cells)
+    c->off.part = o; o += align_up((size_t)c->nblk * (c->nc <= shared_cells_max(c->es) ? BLOCK / 64 : 1) * 4 * 8);
     // the step's last stage: per-block time-step maxima (apart from the right-hand side's
     // partials, which the same stage reads)
     c->off.spart = o; o += align_up((size_t)c->nblk * 2 * 8);
@@ -620,6 +635,15 @@ constexpr bool may_split() { return !(sizeof(T) == 8 && K == 3); }
 // FP64 34.6 -> 33.1 / 32.5 / 32.6 ms; 64^3 unchanged up to 8 and slower at 16
 constexpr int RHS_ZTILE = 8;
 
+// Whether the four waves of a block share 64 cells: on small meshes (shared_cells_max), where the
+// caller has not named the form of the stages (the two forms share the sums of k_rhs bit for bit)
+// or the matrix-core volume integral; a driving evaluated mode by mode keeps the general kernel.
+static bool shared_cells(const dg_ctx *c, bool direct)
+{
+    return !direct && c->nc <= shared_cells_max(c->es) &&
+           !(c->cfg.flags & (DG_VOLUME_MFMA | DG_SEPARATE_STAGE | DG_SPLIT_STAGE));
+}
+
 // st: the split stage whose combination the right-hand-side kernel forms, or NULL:
 // the right-hand side is stored into out
 template <typename T, int K>
@@ -666,8 +690,9 @@ static int launch_rhs(dg_ctx *c, const void *u, const void *vh, void *out, doubl
     const StageArgs st0{};
     if (st) a.part = nullptr;   // a split stage's kernel reads the partials of its input
     // sweep order: tiles of planes when whole blocks make up a plane
+    const long long plane = (long long)c->cfg.nx * c->cfg.ny;
+    c->rhs_nblk = c->nblk;
     {
-        const long long plane = (long long)c->cfg.nx * c->cfg.ny;
         a.bpp = plane % BLOCK == 0 ? (int)(plane / BLOCK) : 0;
         a.zt = RHS_ZTILE;
     }
@@ -694,6 +719,12 @@ static int launch_rhs(dg_ctx *c, const void *u, const void *vh, void *out, doubl
             done = true;
         }
     }
+    if (!done && shared_cells(c, direct)) {
+        c->rhs_nblk = (c->nc + 63) / 64;
+        a.bpp = plane % 64 == 0 ? (int)(plane / 64) : 0;
+        hipLaunchKernelGGL((k_rhs<T, K, false, false, 0, true>), dim3(c->rhs_nblk), bl, 0, c->stream, a, st0);
+        done = true;
+    }
     if (!done) {
         if (direct) hipLaunchKernelGGL((k_rhs<T, K, true>), gr, bl, 0, c->stream, a, st0);
         else hipLaunchKernelGGL((k_rhs<T, K, false>), gr, bl, 0, c->stream, a, st0);
@@ -715,7 +746,7 @@ static int launch_abar(dg_ctx *c, const double *part = nullptr, int np = 0)
 {
     if (!part) {
         part = (const double *)c->wp(c->off.part);
-        np = c->nblk;
+        np = c->rhs_nblk;
     }
     hipLaunchKernelGGL(k_final, dim3(1), dim3(BLOCK), 0, c->stream, part, np, 1, 1.0, 0.0, c->abar(),
                        (const int *)nullptr, (volatile long long *)nullptr, 0LL, (const double *)nullptr, 0);
@@ -744,7 +775,7 @@ static StageArgs stage_args(dg_ctx *c, const void *ui, const void *un, const voi
     const bool mf = (L || split) && use_meanfree(c);
     a.abar = mf && !c->abar_in_stage ? c->abar() : nullptr;
     a.abar_part = mf && c->abar_in_stage ? (const double *)c->wp(split ? c->off.dpart : c->off.part) : nullptr;
-    a.abar_np = c->nblk;
+    a.abar_np = split ? c->nblk : c->rhs_nblk;
     a.fail = c->fail();
     a.nlim = nlim;
     a.part = part;
@@ -1057,7 +1088,7 @@ static int launch_step_stage(dg_ctx *c, void *u, int s, double dt, bool reset_fa
     // mean-free driving: with few right-hand-side blocks every stage block reduces their
     // partials itself (at most 32 KB of reads per block, no reduction kernel); with more, one
     // k_final reduces them once, as the repeated reads would grow with the square of the mesh
-    const bool in_stage = c->nblk <= ABAR_IN_STAGE_BLOCKS;
+    const bool in_stage = c->rhs_nblk <= ABAR_IN_STAGE_BLOCKS;
     if (use_meanfree(c) && !in_stage) {
         rc = launch_abar(c);
         if (rc) return rc;

@@ -1158,16 +1158,19 @@ __device__ __forceinline__ void volume_mfma(const RhsArgs &a, ctab<float> *tab, 
 // 128^3 right-hand side.  Two lanes per cell at two waves per SIMD, which was the better form while
 // every point was evaluated from all modes (5.9 ms), took 5.4 ms line by line (256 registers and
 // spills, every line's moments swapped between the lanes).
-template <typename T, int K, bool VMFMA = false>
-constexpr int rhs_waves() { return VMFMA ? MFMA_WAVES : (sizeof(T) == 8 ? (K <= 2 ? 2 : 1) : (K <= 2 ? 4 : 2)); }
+template <typename T, int K, bool VMFMA = false, bool WSPLIT = false>
+constexpr int rhs_waves()
+{
+    return VMFMA ? MFMA_WAVES : (sizeof(T) == 8 ? (K <= 2 ? 2 : 1) : (K <= 2 && !WSPLIT ? 4 : 2));
+}
 
 // How many variables' weights (the last ones) wait in the block's LDS (the face columns, unused
 // until the surface integral) during the volume integral instead of in registers: at degree 2 one
 // in FP64 (256 registers for 2 waves; 9 spilled without, 567 -> 552 us per 64^3 step; two: 560 us)
 // and three in FP32 (128 registers for 4 waves; 2.58 ms per 128^3 learned step against 2.64 ms
 // with two; 3 waves without spills 2.79 against 2.71 ms in an earlier form); the others fit.
-template <typename T, int K>
-constexpr int volume_lds_vars() { return K == 2 ? (sizeof(T) == 8 ? 1 : 3) : 0; }
+template <typename T, int K, bool WSPLIT = false>
+constexpr int volume_lds_vars() { return K == 2 ? (sizeof(T) == 8 ? 1 : (WSPLIT ? 0 : 3)) : 0; }
 
 // a lane's column of LDS values, stride ST
 template <typename T, int ST>
@@ -1183,24 +1186,34 @@ __device__ __forceinline__ void rhs_combination(const void *ui, T (&L)[4][Shape<
 // COMB: 0 stores the right-hand side (and the mean-acceleration partials); 1 and 2 go on with
 // the combination of the stage st of a Runge-Kutta step for the cell (rhs_combination; 2: u^n
 // enters) and store nothing of the right-hand side
-template <typename T, int K, bool FDIRECT, bool VMFMA = false, int COMB = 0>
-__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(rhs_waves<T, K, VMFMA>())))
+// WSPLIT: the four waves of a block share 64 cells instead of taking 64 each.  On a mesh that leaves
+// the SIMDs a wave or less each, nothing hides the latencies of a wave's chain of loads and
+// arithmetic, which is what the kernel takes; here the chain is cut in four: waves 0 and 1 take half
+// of the volume lines each (wave 1, with the smaller half, the density row too), waves 2 and 3 three
+// faces each.  Their sums meet in LDS, where wave v adds up variable v in wave order.  A step at
+// 33x20x27 cells, degree 2, FP32: 157 -> 101 us; at 16^3, degree 1, FP64: 62 -> 53 us.
+template <typename T, int K, bool FDIRECT, bool VMFMA = false, int COMB = 0, bool WSPLIT = false>
+__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(rhs_waves<T, K, VMFMA, WSPLIT>())))
 k_rhs(RhsArgs a, StageArgs st)
 {
     static_assert(!(COMB && VMFMA), "split stages: vector volume integral only");
+    static_assert(!(WSPLIT && (VMFMA || COMB)), "shared cells: stored right-hand side, vector volume integral only");
+    constexpr int CPB = WSPLIT ? 64 : BLOCK;       // cells per block
     using S = Shape<K>;
     using TL = TabLayout<K>;
     constexpr Modes<K> M = make_modes<K>();
     constexpr int NB = S::NB;
-    constexpr int LV0 = VMFMA ? 4 : 4 - volume_lds_vars<T, K>();    // variables LV0.. wait in LDS
+    constexpr int LV0 = VMFMA ? 4 : 4 - volume_lds_vars<T, K, WSPLIT>();    // variables LV0.. wait in LDS
     __shared__ double lds[4 * 4];
     __shared__ T fsh[S::NF * 4 * BLOCK];        // face moments, a column per cell (face_slot)
     ctab<T> *tab = as_tab<T>(a.tab);
     const int nc = a.g.nc;
     const int blk = plane_tiled(xcd_remap(blockIdx.x, gridDim.x), a.bpp, a.g.nz, a.zt);
-    const int c0 = blk * BLOCK + threadIdx.x;
+    const int c0 = blk * CPB + (WSPLIT ? (int)(threadIdx.x & 63) : (int)threadIdx.x);
     const bool active = c0 < nc;
     const int c = active ? c0 : 0;
+    const int role = WSPLIT ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
+    const bool does_volume = !WSPLIT || role < 2;
     if (a.fail_reset && blockIdx.x == 0 && threadIdx.x == 0) *a.fail_reset = 0;
 
     const bool av = a.flags & F_AV;
@@ -1222,7 +1235,8 @@ k_rhs(RhsArgs a, StageArgs st)
     // non-temporal, like the right-hand side written at the end
     T W[4][NB];
     if constexpr (!VMFMA) {
-        if (prim) {
+        if (!does_volume) {
+        } else if (prim) {
 #pragma unroll
             for (int v = 0; v < 4; ++v)
 #pragma unroll
@@ -1234,7 +1248,7 @@ k_rhs(RhsArgs a, StageArgs st)
         W[0][0] = U.get(0, 0, bo);
     }
 
-    if constexpr (LV0 < 4)
+    if (LV0 < 4 && does_volume)
 #pragma unroll
         for (int v = LV0; v < 4; ++v)
 #pragma unroll
@@ -1252,7 +1266,7 @@ k_rhs(RhsArgs a, StageArgs st)
     // viscosity of a compressed point, nu0 + nu1 s capped at numax (Sec. 3.1)
     T nu1 = alpha * hp * hp, nu0 = beta * cs * hp;
     const T numax = T(0.5) * hp * hp * inv_dt;
-    if (av && !VMFMA) {
+    if (av && !VMFMA && does_volume) {
 #pragma unroll
         for (int d = 0; d < 3; ++d)
 #pragma unroll
@@ -1291,8 +1305,9 @@ k_rhs(RhsArgs a, StageArgs st)
         constexpr int FM = decltype(form)::value;
         constexpr int N1 = S::N1, NL = TL::NL;
         ctab<T> *g = ft + PencilLayout<K>::HDR + (size_t)pen * PencilLayout<K>::STRIDE;
+        const int r0 = WSPLIT && role == 1 ? (S::NF + 1) / 2 : 0, r1 = WSPLIT && role == 0 ? (S::NF + 1) / 2 : S::NF;
 #pragma unroll 1
-        for (int r = 0; r < S::NF; ++r) {
+        for (int r = r0; r < r1; ++r) {
             ctab<T> *phi2 = tab + TL::F2 + r * S::NB2;
             T x[4][N1], c[N1];
             // (the offset is opaque, or the compiler would keep the loop-invariant weights in
@@ -1406,6 +1421,7 @@ k_rhs(RhsArgs a, StageArgs st)
         }
         // the density row, sum_q w_q d_d(phi_l) m_d, is linear in the momentum and the quadrature
         // exact for it: 8 sum_t sqrt(f_t) W_{1+d, m_t} by the derivative identity
+        if (!WSPLIT || role == 1)
 #pragma unroll
         for (int d = 0; d < 3; ++d)
 #pragma unroll
@@ -1421,6 +1437,7 @@ k_rhs(RhsArgs a, StageArgs st)
     if constexpr (VMFMA) {
         static_assert(sizeof(T) == 4 && K == 2 && !FDIRECT, "matrix-core volume integral: FP32, degree 2");
         volume_mfma(a, tab, (float *)fsh, blk, active, pencil, L, fs0, fs1, fs2);
+    } else if (!does_volume) {
     } else if constexpr (FDIRECT) {
         volume(std::integral_constant<int, FM_DIRECT>{}, 0);
     } else {
@@ -1431,51 +1448,108 @@ k_rhs(RhsArgs a, StageArgs st)
         else
             volume(std::integral_constant<int, FM_LANE>{}, pencil);
     }
-    const T mass0 = W[0][0];
+    const T mass0 = does_volume ? W[0][0] : T(0);
 
     // ---- surface integral (traces: rho and either the projected velocity or m)
     int nbr[6], ijk[3];
     neighbours(a.g, c, nbr, ijk);
     const Field<T, 4> SRC = prim ? Field<T, 4>(a.u, a.vh, NB, nc) : U;
     // Each face flux is needed by both cells.  Every cell computes its low x and y faces
-    // and leaves the point fluxes in LDS; a wave whose high-side neighbours all belong to
+    // and leaves the fluxes' line moments in LDS; a wave whose high-side neighbours all belong to
     // this block (whole x lines per block, and y lines of the block but the last) lifts
     // those instead of recomputing the face.  The decision is a wave vote, so the branch
     // is uniform; the stored values are exactly those the cell would compute itself.
     const int base = blk * BLOCK;
     const bool xsh = __all((unsigned)(nbr[1] - base) < (unsigned)BLOCK);
     const bool ysh = __all((unsigned)(nbr[3] - base) < (unsigned)BLOCK);
-    // Every face leaves its point fluxes in the cell's LDS column and lifts them from there.
-    // A wave whose high neighbours all lie in the block lifts their low-face fluxes (between
+    // Every face leaves its moments in the cell's LDS column and lifts them from there.
+    // A wave whose high neighbours all lie in the block lifts their low-face moments (between
     // two barriers) instead of computing its high face; a high face that is computed is
     // stored only after the second barrier, when no other wave reads the columns any more.
     T *col = fsh + threadIdx.x;
+    if constexpr (WSPLIT) {
+        // wave 2: both x faces and the low y face; wave 3: the others
+        if (role >= 2) {
 #pragma unroll 1
-    for (int s = 0; s < 2; ++s) {
-        if (s == 1) {
-            __syncthreads();
-            if (xsh) lift<T, K, 0>(fsh + (nbr[1] - base), 1, tab, L);
-            __syncthreads();
-            if (xsh) break;
+            for (int s = 0; s < 2; ++s) {
+                if (role == 2)
+                    face<T, K, 0>(SRC, bo, (unsigned)(s ? nbr[1] : nbr[0]) * sizeof(T), s, tab, prim, use_hllc, cs, cs2, L,
+                                  col);
+                else
+                    face<T, K, 2>(SRC, bo, (unsigned)(s ? nbr[5] : nbr[4]) * sizeof(T), s, tab, prim, use_hllc, cs, cs2, L,
+                                  col);
+            }
+            const int s = role - 2;
+            face<T, K, 1>(SRC, bo, (unsigned)(s ? nbr[3] : nbr[2]) * sizeof(T), s, tab, prim, use_hllc, cs, cs2, L, col);
         }
-        face<T, K, 0>(SRC, bo, (unsigned)(s ? nbr[1] : nbr[0]) * sizeof(T), s, tab, prim, use_hllc, cs, cs2, L, col);
-    }
-#pragma unroll 1
-    for (int s = 0; s < 2; ++s) {
-        if (s == 1) {
-            __syncthreads();
-            if (ysh) lift<T, K, 1>(fsh + (nbr[3] - base), 1, tab, L);
-            __syncthreads();
-            if (ysh) break;
+        // every wave leaves the three variables it does not finish in its column
+        static_assert(3 * NB <= S::NF * 4, "the column holds three variables' sums");
+        const T scale = (T)(0.25 / a.h);
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (v != role)
+#pragma unroll
+                for (int l = 0; l < NB; ++l) col[((v - (v > role)) * NB + l) * BLOCK] = L[v][l];
+        __builtin_amdgcn_sched_barrier(0);
+        __syncthreads();
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (v == role) {
+                const Field<T, 4> O(a.out, NB, nc);
+#pragma unroll
+                for (int l = 0; l < NB; ++l) {
+                    T sum = T(0);
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) {
+                        const T x = w == v ? L[v][l] : fsh[((v - (v > w)) * NB + l) * BLOCK + 64 * w + (threadIdx.x & 63)];
+                        sum = w ? sum + x : x;
+                    }
+                    sum *= scale;
+                    if (active) O.put_nt(v, l, bo, sum);
+                    if (v == 0 && l == 0 && active && a.pred_fail) predict_failure<T>(a, dt, c, U.get(0, 0, bo), sum);
+                    if (l % 5 == 4) __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        if (force && a.part) {
+            const double fsc = 0.125 / (double)half_h;
+            const bool mine = active && role < 2;
+            double acc[4] = {mine ? fsc * (double)fs0 : 0.0, mine ? fsc * (double)fs1 : 0.0, mine ? fsc * (double)fs2 : 0.0,
+                             active && role == 0 ? (double)mass0 : 0.0};
+            block_sum<4>(acc, lds);
+            if (threadIdx.x == 0)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) a.part[blk * 4 + i] = acc[i];
         }
-        face<T, K, 1>(SRC, bo, (unsigned)(s ? nbr[3] : nbr[2]) * sizeof(T), s, tab, prim, use_hllc, cs, cs2, L, col);
-    }
+    } else {
 #pragma unroll 1
-    for (int s = 0; s < 2; ++s)
-        face<T, K, 2>(SRC, bo, (unsigned)(s ? nbr[5] : nbr[4]) * sizeof(T), s, tab, prim, use_hllc, cs, cs2, L, col);
+        for (int s = 0; s < 2; ++s) {
+            if (s == 1) {
+                __syncthreads();
+                if (xsh) lift<T, K, 0>(fsh + (nbr[1] - base), 1, tab, L);
+                __syncthreads();
+                if (xsh) break;
+            }
+            face<T, K, 0>(SRC, bo, (unsigned)(s ? nbr[1] : nbr[0]) * sizeof(T), s, tab, prim, use_hllc, cs, cs2, L, col);
+        }
+#pragma unroll 1
+        for (int s = 0; s < 2; ++s) {
+            if (s == 1) {
+                __syncthreads();
+                if (ysh) lift<T, K, 1>(fsh + (nbr[3] - base), 1, tab, L);
+                __syncthreads();
+                if (ysh) break;
+            }
+            face<T, K, 1>(SRC, bo, (unsigned)(s ? nbr[3] : nbr[2]) * sizeof(T), s, tab, prim, use_hllc, cs, cs2, L, col);
+        }
+#pragma unroll 1
+        for (int s = 0; s < 2; ++s)
+            face<T, K, 2>(SRC, bo, (unsigned)(s ? nbr[5] : nbr[4]) * sizeof(T), s, tab, prim, use_hllc, cs, cs2, L, col);
+    }
 
     const T inv4h = (T)(0.25 / a.h);
-    if constexpr (COMB != 0) {
+    if constexpr (WSPLIT) {
+        (void)st;
+    } else if constexpr (COMB != 0) {
         (void)mass0;
         __shared__ double lds_st[20];
         rhs_combination<T, K, COMB == 2>(a.u, L, inv4h, dt, st, active, bo, lds_st);
