@@ -378,7 +378,8 @@ int dg_spectrum_nshell(const dg_ctx *ctx, int p);
  * (sub-points xi_s = -1 + (2s+1)/p): e_host[K] = sum over wave vectors kappa (box units)
  * with round(|kappa|) = K of 1/2 |v_hat(kappa)|^2, v_hat = the discrete Fourier transform
  * divided by the number of grid points, so that sum_K e_host[K] = 1/2 <|v|^2> over the grid.
- * FP64 grid and FFT (hipFFT, double precision real-to-complex).  e_host has
+ * FP64 grid and FFT (own kernels for sides of up to 512 points without a prime factor above 5, else
+ * hipFFT, double precision real-to-complex).  e_host has
  * dg_spectrum_nshell(p) entries (host memory).
  * Errors: DG_EINVAL (bad pointer, p < 1, fewer than 2 grid points along an axis),
  * DG_EUNSUPPORTED (more than 4096 shells), DG_ENOMEM (scratch too small), DG_EHIP. */

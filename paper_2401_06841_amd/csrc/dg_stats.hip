@@ -22,16 +22,19 @@
 // (rho, m_x then m_y, m_z) so that 20 KB of LDS per wave keeps two waves per SIMD.  Sums are
 // per lane, per wave (fixed tree) and over blocks in a fixed order, so the structure
 // function is deterministic.  The spectrum bins shell energies with LDS atomics inside a block (the
-// order of additions inside a block is not fixed; blocks are summed in a fixed order).
+// order of additions inside a block is not fixed; blocks are summed in a fixed order).  Its
+// transform is that of dg_fft.hpp where the grid's sides allow it, else the library's.
 #include <hip/hip_runtime.h>
 #include <hipfft/hipfft.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <vector>
 
 #include "dg.h"
 #include "dg_ctx.hpp"
+#include "dg_fft.hpp"
 #include "dg_kernels.hpp"
 
 namespace dg {
@@ -409,6 +412,58 @@ int launch_grid(dg_ctx *c, const void *u, int p, double *grid, long long npts)
     return DG_OK;
 }
 
+// The spectrum of a grid whose sides are lines of dg_fft.hpp, in the scratch of the grid and its
+// half spectrum (which the lines' tables and the rounded-up x frequencies have to fit; grids of a
+// few points a side may not).  The shell histograms of nblk blocks go to part; nblk = 0: not such a
+// grid.  Against the grid kernel, the library's transforms and the shell kernel, which such grids
+// took before, us: 128^3 cells, degree 2, FP32, on 384^3 points 3860 -> 1910 (and 7 -> 2 ms with the
+// library's plan to make); degree 3 on 512^3 8800 -> 4460; 128^3, degree 1, FP64, on 256^3 1010 ->
+// 520; 64^3, degree 2, on 192^3 500 -> 264; 16^3, degree 1, on 32^3 74 -> 46.  Every size measured
+// is faster, so there is no lower bound.
+template <typename T, int K>
+int launch_lines(dg_ctx *c, const void *u, int p, const SpLayout &s, char *scr, int *nblk)
+{
+    *nblk = 0;
+    FftAxis ax[3];
+    if (!fft_axis(s.X, &ax[0]) || !fft_axis(s.Y, &ax[1]) || !fft_axis(s.Z, &ax[2])) return DG_OK;
+    const int ntile = (int)((s.X / 2 + 1 + FFT_COLS - 1) / FFT_COLS);
+    size_t o = s.grid;
+    double2 *F = (double2 *)(scr + o);
+    o += up256((size_t)3 * ntile * FFT_COLS * s.Y * s.Z * sizeof(double2));
+    FftTables tb;
+    for (int a = 0; a < 3; ++a) {
+        tb.tw[a] = (double2 *)(scr + o); o += up256(ax[a].n * sizeof(double2));
+        tb.freq[a] = (int *)(scr + o); o += up256(ax[a].n * sizeof(int));
+        tb.pos[a] = (int *)(scr + o); o += up256(ax[a].n * sizeof(int));
+    }
+    tb.leg = (double *)(scr + o); o += up256((size_t)p * 4 * sizeof(double));
+    if (o > s.part) return DG_OK;
+    const int nx = c->cfg.nx, ny = c->cfg.ny, nz = c->cfg.nz;
+    // as many of a cell's p lines as a block's LDS holds with the twiddles
+    int yl = p;
+    auto bytes = [&](int n) { return ((size_t)((3 * n + 1) / 2) * fft_pad((int)s.X) + s.X) * sizeof(double2); };
+    while (bytes(yl) > 65536) --yl;
+    const long long nbx = (long long)((p + yl - 1) / yl) * p * ny * nz;
+    hipLaunchKernelGGL(k_fft_tables, dim3(1), dim3(BLOCK), 0, c->stream, ax[0], ax[1], ax[2], p, tb);
+    hipLaunchKernelGGL((k_fft_x<T, K>), dim3((unsigned)nbx), dim3(fft_threads(std::min(nx * yl, BLOCK))), bytes(yl), c->stream, u, nx, ny, nz,
+                       c->cfg.rho_floor, p, yl, ax[0], tb, ntile, F);
+    const dim3 gy((unsigned)(3 * ntile * s.Z)), ty(fft_threads(ax[1].n));
+    if (s.Y <= 256) hipLaunchKernelGGL(k_fft_y<256>, gy, ty, 0, c->stream, ax[1], tb, F);
+    else if (s.Y <= 384) hipLaunchKernelGGL(k_fft_y<384>, gy, ty, 0, c->stream, ax[1], tb, F);
+    else hipLaunchKernelGGL(k_fft_y<512>, gy, ty, 0, c->stream, ax[1], tb, F);
+    *nblk = (int)(ntile * s.Y < SP_BLOCKS ? ntile * s.Y : SP_BLOCKS);
+    const dim3 gz(*nblk), tz(fft_threads(ax[2].n));
+    double *part = (double *)(scr + s.part);
+    if (s.Z <= 256)
+        hipLaunchKernelGGL(k_fft_z<256>, gz, tz, 0, c->stream, ax[2], tb, F, (int)s.X, (int)s.Y, ntile, s.nshell, part);
+    else if (s.Z <= 384)
+        hipLaunchKernelGGL(k_fft_z<384>, gz, tz, 0, c->stream, ax[2], tb, F, (int)s.X, (int)s.Y, ntile, s.nshell, part);
+    else
+        hipLaunchKernelGGL(k_fft_z<512>, gz, tz, 0, c->stream, ax[2], tb, F, (int)s.X, (int)s.Y, ntile, s.nshell, part);
+    LAUNCHCHK(c);
+    return DG_OK;
+}
+
 #define STATS_DISPATCH(c, FN, ...)                                                  \
     ((c)->es == 8 ? ((c)->k == 1   ? FN<double, 1>(__VA_ARGS__)                     \
                      : (c)->k == 2 ? FN<double, 2>(__VA_ARGS__)                     \
@@ -521,21 +576,25 @@ int dg_velocity_spectrum(dg_ctx *c, const void *u, int p, void *scratch, size_t 
     double2 *cplx = (double2 *)(scr + s.cplx);
     double *part = (double *)(scr + s.part);
     double *out = (double *)(scr + s.out);
-    rc = STATS_DISPATCH(c, launch_grid, c, u, p, grid, s.npts);
-    if (rc) return rc;
-    hipfftHandle plan;
-    if ((rc = fft_plan(c, s, &plan))) return rc;
-    hipfftResult fr = hipfftSetStream(plan, c->stream);
-    for (int d = 0; d < 3 && fr == HIPFFT_SUCCESS; ++d)
-        fr = hipfftExecD2Z(plan, grid + (size_t)d * s.npts, (hipfftDoubleComplex *)(cplx + (size_t)d * s.M));
-    if (fr != HIPFFT_SUCCESS) {
-        stats_release(c);
-        return fft_fail(c, "hipfftExecD2Z", fr);
+    int nblk = 0;
+    if ((rc = STATS_DISPATCH(c, launch_lines, c, u, p, s, scr, &nblk))) return rc;
+    if (!nblk) {
+        rc = STATS_DISPATCH(c, launch_grid, c, u, p, grid, s.npts);
+        if (rc) return rc;
+        hipfftHandle plan;
+        if ((rc = fft_plan(c, s, &plan))) return rc;
+        hipfftResult fr = hipfftSetStream(plan, c->stream);
+        for (int d = 0; d < 3 && fr == HIPFFT_SUCCESS; ++d)
+            fr = hipfftExecD2Z(plan, grid + (size_t)d * s.npts, (hipfftDoubleComplex *)(cplx + (size_t)d * s.M));
+        if (fr != HIPFFT_SUCCESS) {
+            stats_release(c);
+            return fft_fail(c, "hipfftExecD2Z", fr);
+        }
+        const long long need = (s.M + BLOCK - 1) / BLOCK;
+        nblk = (int)(need < SP_BLOCKS ? need : SP_BLOCKS);
+        hipLaunchKernelGGL(k_shells, dim3(nblk), dim3(BLOCK), (size_t)s.nshell * sizeof(double), c->stream,
+                           (const double2 *)cplx, s.X, s.Y, s.Z, s.nshell, part);
     }
-    const long long need = (s.M + BLOCK - 1) / BLOCK;
-    const int nblk = (int)(need < SP_BLOCKS ? need : SP_BLOCKS);
-    hipLaunchKernelGGL(k_shells, dim3(nblk), dim3(BLOCK), (size_t)s.nshell * sizeof(double), c->stream,
-                       (const double2 *)cplx, s.X, s.Y, s.Z, s.nshell, part);
     hipError_t le = hipGetLastError();
     if (le == hipSuccess) {
         hipLaunchKernelGGL(k_shells_final, dim3(s.nshell), dim3(BLOCK), 0, c->stream, (const double *)part, nblk,
