@@ -274,7 +274,7 @@ static void layout(dg_ctx *c, size_t *total)
     c->off.fb = o; o += align_up(nc * 4);
     c->off.feat = o; o += learned ? align_up(nc * DG_MLP_NIN * 4) : 0;
     c->off.lab = o; o += learned ? align_up(nc * 8) : 0;
-    c->off.mlp = o; o += align_up((size_t)MLP_PART_ROWS * (DG_MLP_NPARAM + 1) * 4);   // per-wave network gradients
+    c->off.mlp = o; o += align_up((size_t)MLP_PART_ROWS * (DG_MLP_NPARAM + 1) * 4);   // per-block network gradients
     // per-block partials (small meshes: a right-hand-side block may hold 64 cells)
     c->off.part = o; o += align_up((size_t)c->nblk * (c->nc <= shared_cells_max(c->es) ? BLOCK / 64 : 1) * 4 * 8);
     // the step's last stage: per-block time-step maxima (apart from the right-hand side's

@@ -7,7 +7,8 @@
 
 #include "dg.h"
 
-// rows of per-wave partial network gradients in the workspace (waves of the gradient kernel)
+// rows of partial network gradients in the workspace (the gradient kernel, whose blocks of four waves
+// write a row each, uses a quarter of them)
 constexpr int MLP_PART_ROWS = 1024;
 
 struct dg_offsets {
