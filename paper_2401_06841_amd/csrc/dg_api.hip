@@ -241,6 +241,17 @@ void build_mfma_tables(const std::vector<double> &t, std::vector<float> &mt)
 //   85184       130 -> 144   294 -> 298   817 -> 770         94 -> 97   182 -> 161   347 -> 322
 constexpr int shared_cells_max(size_t es) { return es == 8 ? 49152 : 65536; }
 
+// The largest mesh whose stage kernel does the same (k_stage_shared); every wave holds the new weights
+// of all four variables, which costs more where the general kernel has waves to overlap.  Driven
+// steps with the shared right-hand side, general stage kernel -> shared, us:
+//   cells     FP64: degree 1    degree 2    degree 3     FP32: degree 1    degree 2    degree 3
+//   4096         77 ->  70   121 ->  98   216 -> 171         68 -> 65    92 ->  82   147 -> 126
+//   16250        75 ->  67   126 -> 103   231 -> 185         66 -> 62    95 ->  84   153 -> 132
+//   32768        80 ->  76   145 -> 132   340 -> 302         68 -> 65    98 ->  93   167 -> 154
+//   46656       100 -> 100   191 -> 182   437 -> 458         71 -> 71   107 -> 105   221 -> 212
+//   64000       (general: 49152 is the limit of FP64)        76 -> 79   140 -> 145   247 -> 250
+constexpr int shared_stage_max(size_t es, int k) { return es == 8 && k == 3 ? 32768 : 49152; }
+
 size_t align_up(size_t x) { return (x + 255) & ~size_t(255); }
 
 }  // namespace
@@ -279,7 +290,7 @@ static void layout(dg_ctx *c, size_t *total)
     c->off.part = o; o += align_up((size_t)c->nblk * (c->nc <= shared_cells_max(c->es) ? BLOCK / 64 : 1) * 4 * 8);
     // the step's last stage: per-block time-step maxima (apart from the right-hand side's
     // partials, which the same stage reads)
-    c->off.spart = o; o += align_up((size_t)c->nblk * 2 * 8);
+    c->off.spart = o; o += align_up((size_t)c->nblk * (c->nc <= shared_cells_max(c->es) ? BLOCK / 64 : 1) * 2 * 8);
     // mean-acceleration partials of a stage's input formed before its right-hand side (split
     // stages), apart from the right-hand side's own
     c->off.dpart = o; o += align_up((size_t)c->nblk * 4 * 8);
@@ -813,9 +824,15 @@ static int launch_stage(dg_ctx *c, const void *ui, const void *un, const void *L
     if (rc) return rc;
     // u^n enters when its coefficient is not zero; the side combination when it has an output
     const bool unv = a.L && a.ca != 0.0, side = a.L && a.w_out;
+    c->stage_nblk = c->nblk;
     if (side) {
         if (unv) hipLaunchKernelGGL((k_stage<T, K, true, true>), dim3(c->nblk), dim3(BLOCK), 0, c->stream, a);
         else hipLaunchKernelGGL((k_stage<T, K, false, true>), dim3(c->nblk), dim3(BLOCK), 0, c->stream, a);
+    } else if (a.L && shared_cells(c, false) && c->nc <= shared_stage_max(sizeof(T), K)) {
+        c->stage_nblk = (c->nc + 63) / 64;
+        const dim3 gr(c->stage_nblk);
+        if (unv) hipLaunchKernelGGL((k_stage_shared<T, K, true>), gr, dim3(BLOCK), 0, c->stream, a);
+        else hipLaunchKernelGGL((k_stage_shared<T, K, false>), gr, dim3(BLOCK), 0, c->stream, a);
     } else {
         if (unv) hipLaunchKernelGGL((k_stage<T, K, true, false>), dim3(c->nblk), dim3(BLOCK), 0, c->stream, a);
         else hipLaunchKernelGGL((k_stage<T, K, false, false>), dim3(c->nblk), dim3(BLOCK), 0, c->stream, a);
@@ -845,11 +862,11 @@ static int do_rhs(dg_ctx *c, const void *u, void *dudt, double dt)
 // vmax: np2 further partial maxima of the viscosity (the learned cells'), or NULL
 template <typename T, int K>
 static int launch_dt_final(dg_ctx *c, const double *src, double *dst, long long seq = 0, const double *vmax = nullptr,
-                           int np2 = 0)
+                           int np2 = 0, int np = 0)
 {
     const double hp = c->cfg.h / (K + 1);
     volatile long long *pub = seq > 0 ? (volatile long long *)(c->pinned + dg_ctx::PUB) : nullptr;
-    hipLaunchKernelGGL(k_final, dim3(1), dim3(BLOCK), 0, c->stream, src, c->nblk, 2,
+    hipLaunchKernelGGL(k_final, dim3(1), dim3(BLOCK), 0, c->stream, src, np ? np : c->nblk, 2,
                        c->cfg.cfl * c->cfg.h / (K + 1), c->cfg.cfl_visc > 0.0 ? c->cfg.cfl_visc * hp * hp : 0.0,
                        dst, (const int *)(pub ? c->fail() : nullptr), pub, seq, vmax, np2);
     LAUNCHCHK(c);
@@ -1144,7 +1161,7 @@ static int do_step(dg_ctx *c, void *u, double dt, int *status_host, bool reuse, 
             if (proj_args(c).visc) vmax = (const double *)c->wp(c->off.mlp);
         }
         const long long seq = ++c->pub_seq;
-        rc = launch_dt_final<T, K>(c, (const double *)c->wp(c->off.spart), c->scal() + 8, seq, vmax, nvmax);
+        rc = launch_dt_final<T, K>(c, (const double *)c->wp(c->off.spart), c->scal() + 8, seq, vmax, nvmax, c->stage_nblk);
         if (rc) return rc;
         if (ahead) {
             // from u^(n+1) with the time step k_final has just stored; written only into

@@ -1576,6 +1576,45 @@ k_rhs(RhsArgs a, StageArgs st)
     }
 }
 
+// the projected velocity's component d, V, into the modal coefficients of its divergence (a
+// degree-(K-1) polynomial, on the reference cell)
+template <typename T, int K>
+__device__ __forceinline__ void fold_divergence(int d, const T (&V)[Shape<K>::NB], T (&Dv)[DivMap<K>::NDIV])
+{
+    constexpr Modes<K> M = make_modes<K>();
+    constexpr DivMap<K> DM = make_divmap<K>();
+#pragma unroll
+    for (int l = 0; l < Shape<K>::NB; ++l)
+        if (M.e[l][d] >= 1)
+#pragma unroll
+            for (int t = 0; t < DivMap<K>::MAXT; ++t)
+                if (DM.m[d][l][t] >= 0) Dv[DM.m[d][l][t]] += V[l] * T(__builtin_sqrt(double(DM.f[d][l][t])));
+}
+
+// the largest bulk viscosity of a cell, from the most negative divergence of the projected velocity
+// over the interior points
+template <typename T, int K>
+__device__ __forceinline__ double viscous_bound(const T (&Dv)[DivMap<K>::NDIV], ctab<T> *tab, const ProjArgs &pa, int c)
+{
+    using S = Shape<K>;
+    using TL = TabLayout<K>;
+    double nm = 0.0;
+    const double hp = pa.h / (K + 1);
+    double smin = 0.0;
+#pragma unroll 1
+    for (int r = 0; r < S::NF; ++r) {
+        T cd[K], div[S::N1];
+        line_coefficients<T, K, K>(Dv, tab + TL::F2 + r * S::NB2, cd);
+        line_eval<K>(cd, div);
+#pragma unroll
+        for (int t = 0; t < S::N1; ++t) smin = fmin(smin, (double)div[t]);
+    }
+    const double s = -smin * (2.0 / pa.h);
+    if (s > 0.0) nm = pa.alpha * hp * hp * s + pa.beta * pa.cs * hp;
+    if (pa.fb && pa.fb[c] == 0) nm = pa.nu ? fmax((double)((const T *)pa.nu)[c], 0.0) : 0.0;
+    return nm;
+}
+
 // Projected velocity of one cell (Sec. 3.2; stored when vh is not null) and, when part is
 // not null, the per-block maxima for the time step: signal speed sum_d |v_d| + cs over the
 // interior points, and bulk viscosity alpha (h/p)^2 |div v| + beta cs h/p at compressing
@@ -1586,10 +1625,7 @@ __device__ __forceinline__ void project_and_bounds(const T (&W)[4][Shape<K>::NB]
                                                    unsigned bo, int c, bool active, const ProjArgs &pa,
                                                    double *part, int blk, double *lds)
 {
-    using S = Shape<K>;
-    using TL = TabLayout<K>;
-    constexpr Modes<K> M = make_modes<K>();
-    constexpr int NB = S::NB;
+    constexpr int NB = Shape<K>::NB;
     double sm = 0.0;
     // the projection takes the signal speed along from its own point values
     const bool speed_in_projection = vh || (part && pa.visc);
@@ -1600,7 +1636,6 @@ __device__ __forceinline__ void project_and_bounds(const T (&W)[4][Shape<K>::NB]
     }
     // projected velocity, component by component: stored, and folded into the modal
     // coefficients of its divergence (a degree-(K-1) polynomial) for the viscous bound
-    constexpr DivMap<K> DM = make_divmap<K>();
     constexpr int NDIV = DivMap<K>::NDIV;
     const bool visc = part && pa.visc;
     T Dv[NDIV];
@@ -1608,14 +1643,6 @@ __device__ __forceinline__ void project_and_bounds(const T (&W)[4][Shape<K>::NB]
     for (int m = 0; m < NDIV; ++m) Dv[m] = T(0);
     if (vh || visc) {
         const Field<T, 3> VO(vh ? vh : (const void *)tab, NB, nc);
-        auto fold = [&](int d, const T (&V)[NB]) {
-#pragma unroll
-            for (int l = 0; l < NB; ++l)
-                if (M.e[l][d] >= 1)
-#pragma unroll
-                    for (int t = 0; t < DivMap<K>::MAXT; ++t)
-                        if (DM.m[d][l][t] >= 0) Dv[DM.m[d][l][t]] += V[l] * T(__builtin_sqrt(double(DM.f[d][l][t])));
-        };
         if constexpr (SPLIT) {
             auto component = [&](auto dc, auto speed) {
                 constexpr int d = decltype(dc)::value;
@@ -1624,7 +1651,7 @@ __device__ __forceinline__ void project_and_bounds(const T (&W)[4][Shape<K>::NB]
                 if (vh && active)
 #pragma unroll
                     for (int l = 0; l < NB; ++l) VO.put(d, l, bo, V[0][l]);
-                if (visc) fold(d, V[0]);
+                if (visc) fold_divergence<T, K>(d, V[0], Dv);
             };
             if (part) component(std::integral_constant<int, 0>{}, std::true_type{});
             else component(std::integral_constant<int, 0>{}, std::false_type{});
@@ -1639,27 +1666,11 @@ __device__ __forceinline__ void project_and_bounds(const T (&W)[4][Shape<K>::NB]
             if (vh && active) store_field<T, K, 3>(VO, bo, V);
             if (visc)
 #pragma unroll
-                for (int d = 0; d < 3; ++d) fold(d, V[d]);
+                for (int d = 0; d < 3; ++d) fold_divergence<T, K>(d, V[d], Dv);
         }
     }
     if (part) {
-        double nm = 0.0;
-        if (visc) {
-            // most negative divergence of the projected velocity over the interior points
-            const double hp = pa.h / (K + 1);
-            double smin = 0.0;
-#pragma unroll 1
-            for (int r = 0; r < S::NF; ++r) {
-                T cd[K], div[S::N1];
-                line_coefficients<T, K, K>(Dv, tab + TL::F2 + r * S::NB2, cd);
-                line_eval<K>(cd, div);
-#pragma unroll
-                for (int t = 0; t < S::N1; ++t) smin = fmin(smin, (double)div[t]);
-            }
-            const double s = -smin * (2.0 / pa.h);
-            if (s > 0.0) nm = pa.alpha * hp * hp * s + pa.beta * pa.cs * hp;
-            if (pa.fb && pa.fb[c] == 0) nm = pa.nu ? fmax((double)((const T *)pa.nu)[c], 0.0) : 0.0;
-        }
+        double nm = visc ? viscous_bound<T, K>(Dv, tab, pa, c) : 0.0;
         __syncthreads();
         sm = block_max(active ? sm : 0.0, lds);
         __syncthreads();
@@ -1954,6 +1965,117 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(stag
         }
     }
     stage_finish<T, K>(U, tab, a, bo, c, active, blk, lds);
+}
+
+// k_stage on small meshes, the four waves of a block on the same 64 cells (as k_rhs with WSPLIT, for
+// the same reason): wave v loads and combines variable v, all waves share the new weights through
+// LDS and check the limiter, wave v stores variable v, and waves 1 to 3 project one velocity
+// component each while wave 0 takes the signal speeds.  The arithmetic of every value is
+// k_stage's: the same bits.  A driven step at 33x20x27 cells, degree 2, FP32: 97 -> 89 us, at 16^3,
+// degree 1, FP64: 53 -> 46 us, at 16^3, degree 3, FP64: 216 -> 171 us.
+template <typename T, int K, bool UNV>
+__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(rhs_waves<T, K, false, true>())))
+k_stage_shared(StageArgs a)
+{
+    using S = Shape<K>;
+    constexpr int NB = S::NB;
+    __shared__ double lds[4];
+    __shared__ double lds_ab[20];
+    __shared__ T sh[4 * NB * 64];
+    const int nc = a.g.nc;
+    const int blk = xcd_remap(blockIdx.x, gridDim.x);
+    const int lane = threadIdx.x & 63, role = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int c0 = blk * 64 + lane;
+    const bool active = c0 < nc;
+    const int c = active ? c0 : 0;
+    const unsigned bo = (unsigned)c * sizeof(T);
+    ctab<T> *tab = as_tab<T>(a.tab);
+    if (a.skip_flag && *a.skip_flag) return;
+    const Field<T, 4> UI(a.ui, NB, nc), LF(a.L, NB, nc), UN(a.un, NB, nc);
+    T u0[NB], uv[NB], rl[NB], nl[UNV ? NB : 1];
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+        if (v == role)
+#pragma unroll
+            for (int l = 0; l < NB; ++l) {
+                u0[l] = UI.get(0, l, bo);
+                uv[l] = UI.get(v, l, bo);
+                rl[l] = LF.get_nt(v, l, bo);
+                if constexpr (UNV) nl[l] = UN.get_nt(v, l, bo);
+            }
+    const double dt = a.dt_dev ? *a.dt_dev : a.dt;
+    const T ca = (T)a.ca, cb = (T)a.cb, cdt = (T)(a.cc * dt);
+    T ab[3];
+    stage_abar<T>(a, ab, lds_ab);
+    const T abv = role == 1 ? ab[0] : (role == 2 ? ab[1] : ab[2]);
+#pragma unroll
+    for (int l = 0; l < NB; ++l) {
+        T rhs = rl[l];
+        if (role > 0) rhs = fma(-abv, u0[l], rhs);
+        T x = fma(cdt, rhs, cb * uv[l]);
+        if constexpr (UNV) x = fma(ca, nl[l], x);
+        sh[(role * NB + l) * 64 + lane] = x;
+    }
+    __syncthreads();
+    T U[4][NB];
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int l = 0; l < NB; ++l) U[v][l] = sh[(v * NB + l) * 64 + lane];
+    // (every wave finds the same limiter factor; a cell below the floor raises the flag four times)
+    if (a.flags & F_LIMIT) stage_limit<T, K>(U, tab, a, active, lds);
+    const Field<T, 4> O(a.out, NB, nc);
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+        if (v == role && active)
+#pragma unroll
+            for (int l = 0; l < NB; ++l) O.put(v, l, bo, U[v][l]);
+    if (!a.vh_out) return;
+    const bool visc = a.part && a.pa.visc;
+    double sm = 0.0;
+    __syncthreads();        // sh is read
+    auto component = [&](auto dc) {
+        constexpr int D = decltype(dc)::value;
+        T V[1][NB];
+        project_lines<T, K, D, 1, false>(U, tab, V, 0.0, sm);
+        const Field<T, 3> VO(a.vh_out, NB, nc);
+#pragma unroll
+        for (int l = 0; l < NB; ++l) {
+            if (active) VO.put(D, l, bo, V[0][l]);
+            if (visc) sh[(D * NB + l) * 64 + lane] = V[0][l];
+        }
+    };
+    if (role == 1) component(std::integral_constant<int, 0>{});
+    else if (role == 2) component(std::integral_constant<int, 1>{});
+    else if (role == 3) component(std::integral_constant<int, 2>{});
+    else if (a.part) {
+        T none[1][NB];
+        project_lines<T, K, 3, 1, true>(U, tab, none, a.pa.cs, sm);
+    }
+    if (!a.part) return;
+    __syncthreads();
+    double nm = 0.0;
+    if (visc && role == 0) {
+        T Dv[DivMap<K>::NDIV];
+#pragma unroll
+        for (int m = 0; m < DivMap<K>::NDIV; ++m) Dv[m] = T(0);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            T V[NB];
+#pragma unroll
+            for (int l = 0; l < NB; ++l) V[l] = sh[(d * NB + l) * 64 + lane];
+            fold_divergence<T, K>(d, V, Dv);
+        }
+        nm = viscous_bound<T, K>(Dv, tab, a.pa, c);
+    }
+    const bool mine = active && role == 0;
+    sm = block_max(mine ? sm : 0.0, lds);
+    __syncthreads();
+    nm = block_max(mine ? nm : 0.0, lds);
+    if (threadIdx.x == 0) {
+        a.part[2 * blk] = sm;
+        a.part[2 * blk + 1] = nm;
+    }
 }
 
 // The combination of a stage formed in the right-hand-side kernel (k_rhs with COMB): k_stage's

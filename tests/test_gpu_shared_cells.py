@@ -68,14 +68,26 @@ def test_against_oracle_and_general(shape, flags, k, precision):
 
 
 @pytest.mark.parametrize("shape,precision,shared", [
-    ((64, 32, 24), dg.DG_FP64, True), ((199, 19, 13), dg.DG_FP64, False),
-    ((64, 32, 32), dg.DG_FP32, True), ((65537, 1, 1), dg.DG_FP32, False)])
+    ((64, 32, 24), dg.DG_FP64, True), ((199, 19, 13), dg.DG_FP64, False), ((64, 32, 24), dg.DG_FP32, True),
+    ((199, 19, 13), dg.DG_FP32, True), ((64, 32, 32), dg.DG_FP32, True), ((65537, 1, 1), dg.DG_FP32, False)])
 def test_edges_of_the_rule(shape, precision, shared):
     print(f"rule edge {shape} precision={precision}", flush=True)
     k = 1
-    u = synthetic.turbulent_like(*shape, k, mach=3.0, seed=3)
+    u = synthetic.turbulent_like(*shape, k, mach=3.0, seed=3, high_amp=0.02, kmax_frac=0.125)
+    if precision == dg.DG_FP32:
+        u = u.astype(np.float32).astype(np.float64)
     ctxs = _contexts(shape, k, FORCE, precision, synthetic.forcing_table(5, amp=5.0))
     dt = dg.dg_dt_max(ctxs[1], dev(u, ctxs[1]))
+    states = [dev(u, c) for c in ctxs]
+    nexts = [dg.dg_rk_step_next(c, x, 0.5 * dt, False) for c, x in zip(ctxs, states)]
+    assert all(status == dg.DG_OK for status, _ in nexts)
+    if shared:
+        assert max(field_rel(host(states[0]), host(states[1]), u)) < TOL[precision]
+        assert nexts[0][1] == pytest.approx(nexts[1][1], rel=10 * TOL[precision])
+    else:
+        assert torch.equal(states[0], states[1]) and nexts[0][1] == nexts[1][1]
+    # the time step of the kept projection is the one of the state
+    assert nexts[0][1] == dg.dg_dt_max(ctxs[0], states[0])
     got, gen = (_rhs(c, u, dt) for c in ctxs)
     if shared:
         assert max(field_rel(dt * got, dt * gen, u)) < TOL[precision]
