@@ -1832,8 +1832,8 @@ __device__ __forceinline__ bool stage_limit(T (&U)[4][Shape<K>::NB], ctab<T> *ta
     return changed;
 }
 
-// What follows the combination in every stage: the limiter, the new weights, their density
-// copy and their projected velocity (with the time-step maxima when a.part is set).  SPLIT:
+// What follows the combination in every stage: the limiter, the new weights and their
+// projected velocity (with the time-step maxima when a.part is set).  SPLIT:
 // project one velocity component at a time (fewer live registers; the same bits).
 template <typename T, int K, bool SPLIT = split_projection<T>()>
 __device__ __forceinline__ void stage_finish(T (&U)[4][Shape<K>::NB], ctab<T> *tab, const StageArgs &a, unsigned bo,
