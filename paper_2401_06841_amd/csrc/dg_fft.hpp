@@ -227,8 +227,9 @@ static __global__ void __launch_bounds__(BLOCK) k_fft_tables(FftAxis x, FftAxis 
 // points of a line in LDS, whole groups of 8
 __host__ __device__ inline int fft_pad(int n) { return (n + 7) / 8 * 8; }
 
-// x lines: the velocities of the points of up to yl of a cell row's lines of one z (three real lines
-// each, two real lines a complex one) and their transforms, F[d][tile of 8 x frequencies][z][y][8].
+// x lines: the velocities of the points of yl lines of one z and their transforms,
+// F[d][tile of 8 x frequencies][z][y][8].  Two real lines of one component, neighbours in y, make a
+// complex line (of two components, the larger one's rounding would pass into the smaller).
 // Bound about half by the vector units (some 250 instructions a point: the three FP64 quotients, the
 // collapse of the weights, the transform) and half by the writes of 128-byte pieces: 0.77 ms on 384^3
 // points (1.4 GB written, 0.34 GB read), where the evaluation alone took 0.78 ms with the grid written
@@ -241,24 +242,22 @@ __global__ void __launch_bounds__(BLOCK) k_fft_x(const void *u_, int nx, int ny,
     constexpr int NB = Shape<K>::NB, N1 = K + 1, NXY = Shape<K>::NB2;
     const int X = nx * p, Y = ny * p, Z = nz * p;
     const int nt = blockDim.x;
-    const int nch = (p + yl - 1) / yl;
-    // a cell row's points of all z and y chunks in neighbouring blocks of one XCD: its weights are
-    // read from memory once
+    const int nch = (Y + yl - 1) / yl;
+    // a cell row's points of all z and y in neighbouring blocks of one XCD: its weights are read from
+    // memory once
     int b = xcd_remap(blockIdx.x, gridDim.x);
-    const int ch = b % nch; b /= nch;
     const int iz = b % p; b /= p;
-    const int cj = b % ny, ck = b / ny;
-    const int y0 = ch * yl, nyl = min(yl, p - y0);      // the cell's y sub-points y0 .. y0 + nyl - 1
-    const int nl = (3 * nyl + 1) / 2;
+    const int ck = b / nch, y0 = (b - ck * nch) * yl, nyl = min(yl, Y - y0);     // lines y0 .. y0 + nyl - 1
+    const int nlc = (nyl + 1) / 2, nl = 3 * nlc;                                  // complex lines
     double2 *tw = shx, *line = shx + X;
     // point x of line l: every group of 8 points in an order of its own, so that points 4 or 8 apart
     // (neighbouring cells', the last stage's butterflies) lie in different LDS banks
     const int XP = fft_pad(X);
     auto at = [&](int x, int l) { return l * XP + (x ^ ((x >> 3) & 7)); };
-    double *re = (double *)line;                        // real line r: part r % 2 of line r / 2
+    double *re = (double *)line;                        // line iy of component d: part iy % 2 of line d nlc + iy / 2
     for (int t = threadIdx.x; t < X; t += nt) tw[t] = tb.tw[0][t];
     const size_t nc = (size_t)nx * ny * nz;
-    const T *u = (const T *)u_ + (size_t)nx * (cj + (size_t)ny * ck);
+    const T *u = (const T *)u_ + (size_t)nx * ny * ck;
     const double *lz = tb.leg + 4 * iz;
     // a cell's points on one line from the line's Legendre coefficients
     auto points = [&](int i, int iy, const double (&c)[4][N1]) {
@@ -274,12 +273,10 @@ __global__ void __launch_bounds__(BLOCK) k_fft_x(const void *u_, int nx, int ny,
             const double rho = fmax(w[0], floor_);
             const int x = i * p + a;
 #pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                const int r = d * nyl + iy;
-                re[2 * at(x, r >> 1) + (r & 1)] = w[1 + d] / rho;
-            }
+            for (int d = 0; d < 3; ++d) re[2 * at(x, d * nlc + (iy >> 1)) + (iy & 1)] = w[1 + d] / rho;
         }
     };
+    // weight of cell i of the plane (i < nx ny)
     auto weight = [&](int v, int l, int i) {
         return *(const T *)((const char *)(u + (size_t)(v * NB + l) * nc) + (unsigned)i * sizeof(T));
     };
@@ -289,25 +286,39 @@ __global__ void __launch_bounds__(BLOCK) k_fft_x(const void *u_, int nx, int ny,
     // first, on 512^3 points, degree 3, 3.1 against 2.1 ms.
     if constexpr (K < 3) {
         for (int it = threadIdx.x; it < nx * nyl; it += nt) {
-            const int i = it % nx, iy = it / nx;
-            const double *ly = tb.leg + 4 * (y0 + iy);
+            const int i = it % nx, iy = it / nx, cj = (y0 + iy) / p;
+            const double *ly = tb.leg + 4 * (y0 + iy - cj * p);
             double c[4][N1], lyz[NXY];
 #pragma unroll
             for (int l = 0; l < NB; ++l)
                 if (M.e[l][0] == 0) lyz[M.d2[0][l]] = ly[M.e[l][1]] * lz[M.e[l][2]];
+            // (all loads first where the compiler would otherwise send them one at a time: 256^3 cells
+            // on 512^3 points 6.7 -> 5.2 ms)
+            constexpr bool AHEAD = sizeof(T) == 8 && K == 2;
+            T w[4][NB];
+            if constexpr (AHEAD) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+#pragma unroll
+                    for (int l = 0; l < NB; ++l) w[v][l] = weight(v, l, cj * nx + i);
+                __builtin_amdgcn_sched_barrier(0);
+            }
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
 #pragma unroll
                 for (int a = 0; a < N1; ++a) c[v][a] = 0.0;
 #pragma unroll
-                for (int l = 0; l < NB; ++l) c[v][M.e[l][0]] = fma((double)weight(v, l, i), lyz[M.d2[0][l]], c[v][M.e[l][0]]);
+                for (int l = 0; l < NB; ++l)
+                    c[v][M.e[l][0]] = fma((double)(AHEAD ? w[v][l] : weight(v, l, cj * nx + i)), lyz[M.d2[0][l]], c[v][M.e[l][0]]);
             }
             points(i, iy, c);
         }
     } else {
-        const int ng = max(1, min(nyl, nt / nx));
-        for (int it = threadIdx.x; it < nx * ng; it += nt) {
-            const int i = it % nx;
+        const int cj0 = y0 / p, nrow = (y0 + nyl - 1) / p - cj0 + 1;       // the lines' cell rows
+        const int ng = max(1, min(min(p, nyl), nt / (nx * nrow)));
+        for (int it = threadIdx.x; it < nx * nrow * ng; it += nt) {
+            const int i = it % nx, q = it / nx, g = q / nrow, cj = cj0 + q - g * nrow;
+            const int ya = max(cj * p, y0) - y0, yb = min((cj + 1) * p, y0 + nyl) - y0;
             double cz[4][NXY];
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
@@ -315,12 +326,14 @@ __global__ void __launch_bounds__(BLOCK) k_fft_x(const void *u_, int nx, int ny,
                 for (int l = 0; l < NXY; ++l) cz[v][l] = 0.0;
                 T w[NB];
 #pragma unroll
-                for (int l = 0; l < NB; ++l) w[l] = weight(v, l, i);
+                for (int l = 0; l < NB; ++l) w[l] = weight(v, l, cj * nx + i);
+                // (FP64 is faster with the compiler's order on all grids below 512^3, 7 % on 256^3, and 5 % slower there)
+                if constexpr (sizeof(T) == 4) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int l = 0; l < NB; ++l) cz[v][M.d2[2][l]] = fma((double)w[l], lz[M.e[l][2]], cz[v][M.d2[2][l]]);
             }
-            for (int iy = it / nx; iy < nyl; iy += ng) {
-                const double *ly = tb.leg + 4 * (y0 + iy);
+            for (int iy = ya + g; iy < yb; iy += ng) {
+                const double *ly = tb.leg + 4 * (y0 + iy - cj * p);
                 double c[4][N1];
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
@@ -335,7 +348,9 @@ __global__ void __launch_bounds__(BLOCK) k_fft_x(const void *u_, int nx, int ny,
         }
     }
     if (nyl & 1)
-        for (int x = threadIdx.x; x < X; x += nt) re[2 * at(x, nl - 1) + 1] = 0.0;
+        for (int x = threadIdx.x; x < X; x += nt)
+#pragma unroll
+            for (int d = 0; d < 3; ++d) re[2 * at(x, d * nlc + nlc - 1) + 1] = 0.0;
     __syncthreads();
     for (int s = 0; s < ax.nst; ++s) {
         fft_any<0>(ax, s, tw, nl, nt, [&](int pos, int cc) { return line[at(pos, cc)]; },
@@ -344,21 +359,17 @@ __global__ void __launch_bounds__(BLOCK) k_fft_x(const void *u_, int nx, int ny,
     }
     // the transforms of the two real lines of a complex one, from frequencies f and X - f
     const int Xh = X / 2 + 1;
-    const int zz = ck * p + iz, yy = cj * p + y0;
+    const int zz = ck * p + iz;
     const size_t tstr = (size_t)Z * Y * FFT_COLS;       // between tiles of x frequencies
     for (int f = threadIdx.x; f < Xh; f += nt) {
         const int t = f / FFT_COLS, pf = tb.pos[0][f], pb = tb.pos[0][f ? X - f : 0];
-        double2 *G = F + t * tstr + ((size_t)zz * Y + yy) * FFT_COLS + (f - t * FFT_COLS);
-        for (int l = 0; l < nl; ++l) {
-            const double2 g = line[at(pf, l)], h = line[at(pb, l)];
-            const int r = 2 * l, d = r / nyl;
-            G[d * ntile * tstr + (r - d * nyl) * FFT_COLS] = make_double2(0.5 * (g.x + h.x), 0.5 * (g.y - h.y));
-            if (r + 1 < 3 * nyl) {
-                const int d1 = (r + 1) / nyl;
-                G[d1 * ntile * tstr + (r + 1 - d1 * nyl) * FFT_COLS] =
-                    make_double2(0.5 * (g.y + h.y), 0.5 * (h.x - g.x));
+        double2 *G = F + t * tstr + ((size_t)zz * Y + y0) * FFT_COLS + (f - t * FFT_COLS);
+        for (int d = 0; d < 3; ++d, G += ntile * tstr)
+            for (int j = 0; j < nlc; ++j) {
+                const double2 g = line[at(pf, d * nlc + j)], h = line[at(pb, d * nlc + j)];
+                G[2 * j * FFT_COLS] = make_double2(0.5 * (g.x + h.x), 0.5 * (g.y - h.y));
+                if (2 * j + 1 < nyl) G[(2 * j + 1) * FFT_COLS] = make_double2(0.5 * (g.y + h.y), 0.5 * (h.x - g.x));
             }
-        }
     }
 }
 

@@ -439,11 +439,11 @@ int launch_lines(dg_ctx *c, const void *u, int p, const SpLayout &s, char *scr, 
     tb.leg = (double *)(scr + o); o += up256((size_t)p * 4 * sizeof(double));
     if (o > s.part) return DG_OK;
     const int nx = c->cfg.nx, ny = c->cfg.ny, nz = c->cfg.nz;
-    // as many of a cell's p lines as a block's LDS holds with the twiddles
-    int yl = p;
-    auto bytes = [&](int n) { return ((size_t)((3 * n + 1) / 2) * fft_pad((int)s.X) + s.X) * sizeof(double2); };
-    while (bytes(yl) > 65536) --yl;
-    const long long nbx = (long long)((p + yl - 1) / yl) * p * ny * nz;
+    // lines of a block: whole pairs, about a cell's p, as many as its LDS holds with the twiddles
+    int yl = (p + 1) / 2 * 2;
+    auto bytes = [&](int n) { return ((size_t)3 * (n / 2) * fft_pad((int)s.X) + s.X) * sizeof(double2); };
+    while (bytes(yl) > 65536) yl -= 2;
+    const long long nbx = (s.Y + yl - 1) / yl * p * nz;
     hipLaunchKernelGGL(k_fft_tables, dim3(1), dim3(BLOCK), 0, c->stream, ax[0], ax[1], ax[2], p, tb);
     hipLaunchKernelGGL((k_fft_x<T, K>), dim3((unsigned)nbx), dim3(fft_threads(std::min(nx * yl, BLOCK))), bytes(yl), c->stream, u, nx, ny, nz,
                        c->cfg.rho_floor, p, yl, ax[0], tb, ntile, F);
