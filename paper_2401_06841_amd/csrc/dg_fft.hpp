@@ -232,8 +232,9 @@ __host__ __device__ inline int fft_pad(int n) { return (n + 7) / 8 * 8; }
 // complex line (of two components, the larger one's rounding would pass into the smaller).
 // Bound about half by the vector units (some 250 instructions a point: the three FP64 quotients, the
 // collapse of the weights, the transform) and half by the writes of 128-byte pieces: 0.77 ms on 384^3
-// points (1.4 GB written, 0.34 GB read), where the evaluation alone took 0.78 ms with the grid written
-template <typename T, int K>
+// points (1.4 GB written, 0.34 GB read), where the evaluation alone took 0.78 ms with the grid written.
+// SPLIT: the points of a cell's line are shared by as many threads as the block has for it
+template <typename T, int K, bool SPLIT>
 __global__ void __launch_bounds__(BLOCK) k_fft_x(const void *u_, int nx, int ny, int nz, double floor_, int p, int yl,
                                                  FftAxis ax, FftTables tb, int ntile, double2 *F)
 {
@@ -259,9 +260,9 @@ __global__ void __launch_bounds__(BLOCK) k_fft_x(const void *u_, int nx, int ny,
     const size_t nc = (size_t)nx * ny * nz;
     const T *u = (const T *)u_ + (size_t)nx * ny * ck;
     const double *lz = tb.leg + 4 * iz;
-    // a cell's points on one line from the line's Legendre coefficients
-    auto points = [&](int i, int iy, const double (&c)[4][N1]) {
-        for (int a = 0; a < p; ++a) {
+    // a cell's points a0, a0 + na, .. of one line from the line's Legendre coefficients
+    auto points = [&](int i, int iy, int a0, int na, const double (&c)[4][N1]) {
+        for (int a = a0; a < p; a += na) {
             const double *lx = tb.leg + 4 * a;
             double w[4];
 #pragma unroll
@@ -285,8 +286,9 @@ __global__ void __launch_bounds__(BLOCK) k_fft_x(const void *u_, int nx, int ny,
     // On 384^3 points, degree 2, FP32, this pass takes 0.78 ms against 0.85 ms with the sums over z
     // first, on 512^3 points, degree 3, 3.1 against 2.1 ms.
     if constexpr (K < 3) {
-        for (int it = threadIdx.x; it < nx * nyl; it += nt) {
-            const int i = it % nx, iy = it / nx, cj = (y0 + iy) / p;
+        const int na = SPLIT ? max(1, nt / (nx * nyl)) : 1;
+        for (int it = threadIdx.x; it < nx * nyl * na; it += nt) {
+            const int i = it % nx, q = it / nx, a0 = SPLIT ? q / nyl : 0, iy = q - a0 * nyl, cj = (y0 + iy) / p;
             const double *ly = tb.leg + 4 * (y0 + iy - cj * p);
             double c[4][N1], lyz[NXY];
 #pragma unroll
@@ -311,13 +313,15 @@ __global__ void __launch_bounds__(BLOCK) k_fft_x(const void *u_, int nx, int ny,
                 for (int l = 0; l < NB; ++l)
                     c[v][M.e[l][0]] = fma((double)(AHEAD ? w[v][l] : weight(v, l, cj * nx + i)), lyz[M.d2[0][l]], c[v][M.e[l][0]]);
             }
-            points(i, iy, c);
+            points(i, iy, a0, na, c);
         }
     } else {
         const int cj0 = y0 / p, nrow = (y0 + nyl - 1) / p - cj0 + 1;       // the lines' cell rows
         const int ng = max(1, min(min(p, nyl), nt / (nx * nrow)));
-        for (int it = threadIdx.x; it < nx * nrow * ng; it += nt) {
-            const int i = it % nx, q = it / nx, g = q / nrow, cj = cj0 + q - g * nrow;
+        const int na = SPLIT ? max(1, nt / (nx * nrow * ng)) : 1;
+        for (int it = threadIdx.x; it < nx * nrow * ng * na; it += nt) {
+            const int i = it % nx, q = it / nx, h = q / nrow, cj = cj0 + q - h * nrow;
+            const int a0 = SPLIT ? h / ng : 0, g = h - a0 * ng;
             const int ya = max(cj * p, y0) - y0, yb = min((cj + 1) * p, y0 + nyl) - y0;
             double cz[4][NXY];
 #pragma unroll
@@ -343,7 +347,7 @@ __global__ void __launch_bounds__(BLOCK) k_fft_x(const void *u_, int nx, int ny,
                     for (int l = 0; l < NB; ++l)
                         if (M.e[l][2] == 0) c[v][M.e[l][0]] = fma(cz[v][M.d2[2][l]], ly[M.e[l][1]], c[v][M.e[l][0]]);
                 }
-                points(i, iy, c);
+                points(i, iy, a0, na, c);
             }
         }
     }

@@ -439,14 +439,27 @@ int launch_lines(dg_ctx *c, const void *u, int p, const SpLayout &s, char *scr, 
     tb.leg = (double *)(scr + o); o += up256((size_t)p * 4 * sizeof(double));
     if (o > s.part) return DG_OK;
     const int nx = c->cfg.nx, ny = c->cfg.ny, nz = c->cfg.nz;
-    // lines of a block: whole pairs, about a cell's p, as many as its LDS holds with the twiddles
+    // lines of a block: whole pairs, about a cell's p, more where the lines are short (a block of a few
+    // points is all start and end: 4x96x96 cells at p = 4, degree 3, 257 -> 188 us), and as many as its LDS
+    // holds with the twiddles
     int yl = (p + 1) / 2 * 2;
+    while (s.X * yl < BLOCK && s.Y * s.Z > 2048ll * yl) yl *= 2;
     auto bytes = [&](int n) { return ((size_t)3 * (n / 2) * fft_pad((int)s.X) + s.X) * sizeof(double2); };
     while (bytes(yl) > 65536) yl -= 2;
     const long long nbx = (s.Y + yl - 1) / yl * p * nz;
     hipLaunchKernelGGL(k_fft_tables, dim3(1), dim3(BLOCK), 0, c->stream, ax[0], ax[1], ax[2], p, tb);
-    hipLaunchKernelGGL((k_fft_x<T, K>), dim3((unsigned)nbx), dim3(fft_threads(std::min(nx * yl, BLOCK))), bytes(yl), c->stream, u, nx, ny, nz,
-                       c->cfg.rho_floor, p, yl, ax[0], tb, ntile, F);
+    // From 16 points per cell and axis on the block has more threads than cell lines, and they share the
+    // points of a line (512^3 points of one cell, degree 1: 16.4 -> 3.8 ms, of 8^3 cells 6.1 -> 3.8 ms);
+    // with fewer points the weights' sums that the threads repeat cost more (8: 2x64x64 cells, degree 2,
+    // 253 -> 275 us; 2 to 4: 2 to 10 % on ordinary meshes).
+    const bool split = p >= 16;
+    const dim3 tx(fft_threads(split ? (int)std::min<long long>(s.X * yl, BLOCK) : std::min(nx * yl, BLOCK)));
+    auto launch_x = [&](auto sp) {
+        hipLaunchKernelGGL((k_fft_x<T, K, decltype(sp)::value>), dim3((unsigned)nbx), tx, bytes(yl), c->stream, u, nx, ny, nz,
+                           c->cfg.rho_floor, p, yl, ax[0], tb, ntile, F);
+    };
+    if (split) launch_x(std::true_type{});
+    else launch_x(std::false_type{});
     const dim3 gy((unsigned)(3 * ntile * s.Z)), ty(fft_threads(ax[1].n));
     if (s.Y <= 256) hipLaunchKernelGGL(k_fft_y<256>, gy, ty, 0, c->stream, ax[1], tb, F);
     else if (s.Y <= 384) hipLaunchKernelGGL(k_fft_y<384>, gy, ty, 0, c->stream, ax[1], tb, F);
