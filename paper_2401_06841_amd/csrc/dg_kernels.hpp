@@ -399,48 +399,77 @@ constexpr bool split_projection() { return sizeof(T) == 8; }
 
 // The face flux at one point, in two parts, so that a face's tangential traces need not be held
 // beside the normal ones (Sec. 2.2 numerical flux; all values are twice the flux's): from the
-// density r and normal velocity v of the cell (o) and its neighbour (n), the mass flux F0, the
+// density r and normal trace t of the cell (o) and its neighbour (n), the mass flux F0, the
 // normal momentum flux Fn, and the factors go, gn that give each tangential momentum flux as
-// go v_t,o + gn v_t,n.  sg = 1 when the cell is the low side of the face, else -1: written in the
+// go t_t,o + gn t_t,n from the tangential traces t_t.  The traces are velocities (PRIM) or
+// momenta, which enter as they are: r (t / r) in their place is one rounding more.  sg = 1
+// when the cell is the low side of the face, else -1: written in the
 // cell and its neighbour, with no choice of a low and a high side (the compiler turned that branch
 // into moves, a quarter of a face's instructions).
-//
-// Isothermal Rusanov flux: m_j v_n +- lambda m_j of a side is r (v_n +- lambda) times v_j, so
-// the factors are g = r (v_n +- lambda); the mass flux keeps the difference form.
-template <typename T>
-__device__ __forceinline__ void rusanov2(T cs, T cs2, T sg, T ro, T vo, T rn, T vn, T &F0, T &Fn, T &go, T &gn)
+template <bool PRIM, typename T>
+__device__ __forceinline__ void normal_trace(T r, T t, T &v, T &m, T &ir)
+{
+#pragma clang fp contract(off)
+    ir = PRIM ? T(0) : rcp(r);
+    v = PRIM ? t : t * ir;
+    m = PRIM ? r * t : t;
+}
+
+// Isothermal Rusanov flux: m_j v_n +- lambda m_j of a side is (v_n +- lambda) times m_j, so
+// the factors are v_n +- lambda, times r for velocities; the mass flux keeps the difference form.
+template <bool PRIM, typename T>
+__device__ __forceinline__ void rusanov2(T cs, T cs2, T sg, T ro, T to, T rn, T tn, T &F0, T &Fn, T &go, T &gn)
 {
     // products of the two sides rounded alike and no contraction left to the compiler: the flux of a
     // face is then the same bits whichever of its two cells computes it
 #pragma clang fp contract(off)
+    T vo, vn, mo, mn, io, in;
+    normal_trace<PRIM>(ro, to, vo, mo, io);
+    normal_trace<PRIM>(rn, tn, vn, mn, in);
     const T lam = sg * (fmax(fabs(vo), fabs(vn)) + cs);
-    F0 = fma(lam, ro - rn, ro * vo + rn * vn);
-    go = ro * (vo + lam);
-    gn = rn * (vn - lam);
-    Fn = fma(cs2, ro + rn, go * vo + gn * vn);
+    F0 = fma(lam, ro - rn, mo + mn);
+    go = vo + lam;
+    gn = vn - lam;
+    if (PRIM) {
+        go *= ro;
+        gn *= rn;
+    }
+    Fn = fma(cs2, ro + rn, go * to + gn * tn);
 }
 
 // Isothermal HLLC-type flux (the counterpart of the HLLC solver of Sec. 2.2 for isothermal gas):
 // wave speeds S_L = min(v_L, v_R) - cs and S_R = max(v_L, v_R) + cs of the normal velocities;
 // density and normal momentum take the HLL flux, each tangential momentum is the mass flux times
-// the upwind tangential velocity.  With S_L clipped to at most 0 and S_R to at least 0 the HLL
-// flux is the low (high) side's where all waves move one way.  In the cell and its neighbour: with
-// a = S_R and b = S_L when the cell is the low side, else a = S_L and b = S_R, it is
-// (a f_o - b f_n + a b (u_n - u_o)) / (a - b) either way.
-template <typename T>
-__device__ __forceinline__ void hllc2(T cs, T cs2, T sg, T ro, T vo, T rn, T vn, T &F0, T &Fn, T &go, T &gn)
+// the upwind tangential velocity.  Where all waves move one way the HLL flux is that side's, as it
+// is.  In the cell and its neighbour: with a = S_R and b = S_L when the cell is the low side, else
+// a = S_L and b = S_R, it is (a f_o - b f_n + a b (u_n - u_o)) / (a - b) either way, the cell's f_o
+// when b does not move towards it (sg b >= 0), the neighbour's when a does (sg a <= 0).
+// (The difference a f_o - b f_n is rounded product by product, for the same bits on both sides:
+// at subsonic faces an rms error of 6.7e-8 of the flux in FP32 against 6.4e-8 with a fused product.)
+template <bool PRIM, typename T>
+__device__ __forceinline__ void hllc2(T cs, T cs2, T sg, T ro, T to, T rn, T tn, T &F0, T &Fn, T &go, T &gn)
 {
 #pragma clang fp contract(off)
-    const T no = ro * vo, nn = rn * vn;
-    const T SL = fmin(fmin(vo, vn) - cs, T(0)), SR = fmax(fmax(vo, vn) + cs, T(0));
+    T vo, vn, mo, mn, io, in;
+    normal_trace<PRIM>(ro, to, vo, mo, io);
+    normal_trace<PRIM>(rn, tn, vn, mn, in);
+    const T SL = fmin(vo, vn) - cs, SR = fmax(vo, vn) + cs;
     const bool low = sg > T(0);
     const T a = low ? SR : SL, b = low ? SL : SR;
     const T iw = (sg + sg) * rcp(SR - SL), ab = SL * SR;
-    F0 = fma(ab, rn - ro, a * no - b * nn) * iw;
-    Fn = fma(ab, nn - no, a * fma(no, vo, cs2 * ro) - b * fma(nn, vn, cs2 * rn)) * iw;
+    const T fo = fma(mo, vo, cs2 * ro), fn = fma(mn, vn, cs2 * rn);
+    const bool own = sg * b >= T(0), nbr = sg * a <= T(0);
+    F0 = fma(ab, rn - ro, a * mo - b * mn) * iw;
+    Fn = fma(ab, mn - mo, a * fo - b * fn) * iw;
+    F0 = own ? mo + mo : (nbr ? mn + mn : F0);
+    Fn = own ? fo + fo : (nbr ? fn + fn : Fn);
     const bool up = (F0 >= T(0)) == low;   // the cell is upwind
     go = up ? F0 : T(0);
     gn = up ? T(0) : F0;
+    if (!PRIM) {
+        go *= io;
+        gn *= in;
+    }
 }
 
 // von Neumann-Richtmyer viscous pressure at one point (Sec. 3.1)
@@ -574,19 +603,11 @@ __device__ __forceinline__ void face_line_normal(const T (&Co)[2][Shape<K>::NB2]
     auto fluxes = [&](auto pr, auto hl) {
 #pragma unroll
         for (int r = 0; r < N1; ++r) {
-            T io, in;
-            if constexpr (!decltype(pr)::value) {
-                io = rcp(ro[r]);
-                in = rcp(rn[r]);
-                vo[r] *= io;
-                vn[r] *= in;
-            }
-            if constexpr (decltype(hl)::value) hllc2(cs, cs2, sg, ro[r], vo[r], rn[r], vn[r], F0[r], Fn[r], go[r], gn[r]);
-            else rusanov2(cs, cs2, sg, ro[r], vo[r], rn[r], vn[r], F0[r], Fn[r], go[r], gn[r]);
-            if constexpr (!decltype(pr)::value) {
-                go[r] *= io;
-                gn[r] *= in;
-            }
+            constexpr bool PRIM = decltype(pr)::value;
+            if constexpr (decltype(hl)::value)
+                hllc2<PRIM>(cs, cs2, sg, ro[r], vo[r], rn[r], vn[r], F0[r], Fn[r], go[r], gn[r]);
+            else
+                rusanov2<PRIM>(cs, cs2, sg, ro[r], vo[r], rn[r], vn[r], F0[r], Fn[r], go[r], gn[r]);
         }
     };
     if (prim) {
