@@ -707,17 +707,26 @@ static int launch_rhs(dg_ctx *c, const void *u, const void *vh, void *out, doubl
         a.bpp = plane % BLOCK == 0 ? (int)(plane / BLOCK) : 0;
         a.zt = RHS_ZTILE;
     }
-    const dim3 gr(c->nblk), bl(BLOCK);
+    // the forms of the kernel: direct driving, volume integral on the matrix cores, combination
+    // (rhs_combination), shared cells
+    using std::false_type;
+    using std::true_type;
+    constexpr std::integral_constant<int, 0> store{};
+    auto launch = [&](auto fd, auto vm, auto comb, auto ws, int nblk, const StageArgs &s) {
+        constexpr bool FD = decltype(fd)::value, VM = decltype(vm)::value, WS = decltype(ws)::value;
+        constexpr int CB = decltype(comb)::value;
+        if (a.flags & DG_HLLC) hipLaunchKernelGGL((k_rhs<T, K, FD, VM, CB, WS, true>), dim3(nblk), dim3(BLOCK), 0, c->stream, a, s);
+        else hipLaunchKernelGGL((k_rhs<T, K, FD, VM, CB, WS, false>), dim3(nblk), dim3(BLOCK), 0, c->stream, a, s);
+    };
     if constexpr (may_split<T, K>()) {
         if (st) {
+            auto split = [&](auto comb) {
+                if (direct) launch(true_type{}, false_type{}, comb, false_type{}, c->nblk, *st);
+                else launch(false_type{}, false_type{}, comb, false_type{}, c->nblk, *st);
+            };
             // u^n enters the combination when its coefficient is not zero
-            if (st->ca != 0.0) {
-                if (direct) hipLaunchKernelGGL((k_rhs<T, K, true, false, 2>), gr, bl, 0, c->stream, a, *st);
-                else hipLaunchKernelGGL((k_rhs<T, K, false, false, 2>), gr, bl, 0, c->stream, a, *st);
-            } else {
-                if (direct) hipLaunchKernelGGL((k_rhs<T, K, true, false, 1>), gr, bl, 0, c->stream, a, *st);
-                else hipLaunchKernelGGL((k_rhs<T, K, false, false, 1>), gr, bl, 0, c->stream, a, *st);
-            }
+            if (st->ca != 0.0) split(std::integral_constant<int, 2>{});
+            else split(std::integral_constant<int, 1>{});
             LAUNCHCHK(c);
             return prof_mark(c, 0, 1);
         }
@@ -726,19 +735,19 @@ static int launch_rhs(dg_ctx *c, const void *u, const void *vh, void *out, doubl
     if constexpr (sizeof(T) == 4 && K == 2) {
         // volume integral on the matrix cores (tables in the pencil form or no driving)
         if ((c->cfg.flags & DG_VOLUME_MFMA) && !direct) {
-            hipLaunchKernelGGL((k_rhs<T, K, false, true>), gr, bl, 0, c->stream, a, st0);
+            launch(false_type{}, true_type{}, store, false_type{}, c->nblk, st0);
             done = true;
         }
     }
     if (!done && shared_cells(c, direct)) {
         c->rhs_nblk = (c->nc + 63) / 64;
         a.bpp = plane % 64 == 0 ? (int)(plane / 64) : 0;
-        hipLaunchKernelGGL((k_rhs<T, K, false, false, 0, true>), dim3(c->rhs_nblk), bl, 0, c->stream, a, st0);
+        launch(false_type{}, false_type{}, store, true_type{}, c->rhs_nblk, st0);
         done = true;
     }
     if (!done) {
-        if (direct) hipLaunchKernelGGL((k_rhs<T, K, true>), gr, bl, 0, c->stream, a, st0);
-        else hipLaunchKernelGGL((k_rhs<T, K, false>), gr, bl, 0, c->stream, a, st0);
+        if (direct) launch(true_type{}, false_type{}, store, false_type{}, c->nblk, st0);
+        else launch(false_type{}, false_type{}, store, false_type{}, c->nblk, st0);
     }
     LAUNCHCHK(c);
     return prof_mark(c, 0, 1);

@@ -18,7 +18,7 @@
 
 namespace dg {
 
-enum : int { F_AV = 1, F_PRIM = 2, F_FORCE = 4, F_LIMIT = 8, F_LEARNED = 16, F_MEANFREE = 32, F_HLLC = 64,
+enum : int { F_AV = 1, F_PRIM = 2, F_FORCE = 4, F_LIMIT = 8, F_LEARNED = 16, F_MEANFREE = 32,
              F_VOLUME_MFMA = 256 };
 
 constexpr int BLOCK = 256;
@@ -464,12 +464,8 @@ __device__ __forceinline__ void hllc2(T cs, T cs2, T sg, T ro, T to, T rn, T tn,
     F0 = own ? mo + mo : (nbr ? mn + mn : F0);
     Fn = own ? fo + fo : (nbr ? fn + fn : Fn);
     const bool up = (F0 >= T(0)) == low;   // the cell is upwind
-    go = up ? F0 : T(0);
-    gn = up ? T(0) : F0;
-    if (!PRIM) {
-        go *= io;
-        gn *= in;
-    }
+    go = up ? (PRIM ? F0 : F0 * io) : T(0);
+    gn = up ? T(0) : (PRIM ? F0 : F0 * in);
 }
 
 // von Neumann-Richtmyer viscous pressure at one point (Sec. 3.1)
@@ -583,9 +579,9 @@ __device__ __forceinline__ void collapse(const T (&w)[Shape<K>::NB], int s, ctab
 // mass and normal momentum flux, F0 and Fn, and the factors of the tangential velocities (of
 // the tangential momenta with prim off) of the two sides, go and gn.  s: 1 the cell is the low side.
 // p1: the basis values of the line's second tangential point.
-template <typename T, int K, typename B>
+template <typename T, int K, bool HLLC, typename B>
 __device__ __forceinline__ void face_line_normal(const T (&Co)[2][Shape<K>::NB2], const T (&Cn)[2][Shape<K>::NB2],
-                                                 const B &p1, int s, bool prim, bool use_hllc, T cs, T cs2,
+                                                 const B &p1, int s, bool prim, T cs, T cs2,
                                                  T (&F0)[K + 1], T (&Fn)[K + 1], T (&go)[K + 1], T (&gn)[K + 1])
 {
     constexpr int N1 = K + 1;
@@ -598,30 +594,24 @@ __device__ __forceinline__ void face_line_normal(const T (&Co)[2][Shape<K>::NB2]
     line_eval<K>(c, vo);
     face_line_coefficients<T, K>(Cn[1], p1, c);
     line_eval<K>(c, vn);
-    // one branch per line and combination of options, each with its own straight code
+    // one branch per line, each form with its own straight code
     const T sg = s ? T(1) : T(-1);
-    auto fluxes = [&](auto pr, auto hl) {
+    auto fluxes = [&](auto pr) {
+        constexpr bool PRIM = decltype(pr)::value;
 #pragma unroll
         for (int r = 0; r < N1; ++r) {
-            constexpr bool PRIM = decltype(pr)::value;
-            if constexpr (decltype(hl)::value)
-                hllc2<PRIM>(cs, cs2, sg, ro[r], vo[r], rn[r], vn[r], F0[r], Fn[r], go[r], gn[r]);
-            else
-                rusanov2<PRIM>(cs, cs2, sg, ro[r], vo[r], rn[r], vn[r], F0[r], Fn[r], go[r], gn[r]);
+            if constexpr (HLLC) hllc2<PRIM>(cs, cs2, sg, ro[r], vo[r], rn[r], vn[r], F0[r], Fn[r], go[r], gn[r]);
+            else rusanov2<PRIM>(cs, cs2, sg, ro[r], vo[r], rn[r], vn[r], F0[r], Fn[r], go[r], gn[r]);
         }
     };
-    if (prim) {
-        if (use_hllc) fluxes(std::true_type{}, std::true_type{});
-        else fluxes(std::true_type{}, std::false_type{});
-    } else {
-        if (use_hllc) fluxes(std::false_type{}, std::true_type{});
-        else fluxes(std::false_type{}, std::false_type{});
-    }
+    if (prim) fluxes(std::true_type{});
+    else fluxes(std::false_type{});
 }
 
 // The flux of one tangential momentum along a line from its 2D coefficients of both sides and
-// the line's factors
-template <typename T, int K, typename B>
+// the line's factors.  HLLC: one factor is zero and the other side's trace is taken alone, as a
+// trace that is not finite must not pass through the zero
+template <typename T, int K, bool HLLC, typename B>
 __device__ __forceinline__ void face_line_tangential(const T (&Co)[Shape<K>::NB2], const T (&Cn)[Shape<K>::NB2],
                                                      const B &p1, const T (&go)[K + 1], const T (&gn)[K + 1],
                                                      T (&F)[K + 1])
@@ -633,12 +623,13 @@ __device__ __forceinline__ void face_line_tangential(const T (&Co)[Shape<K>::NB2
     face_line_coefficients<T, K>(Cn, p1, c);
     line_eval<K>(c, vn);
 #pragma unroll
-    for (int r = 0; r <= K; ++r) F[r] = go[r] * F[r] + gn[r] * vn[r];
+    for (int r = 0; r <= K; ++r)
+        F[r] = HLLC ? (go[r] + gn[r]) * (gn[r] == T(0) ? F[r] : vn[r]) : go[r] * F[r] + gn[r] * vn[r];
 }
 
 // 2D moments M of one tangential momentum's flux from its 2D coefficients of both sides and the
 // factors in the column
-template <typename T, int K, int D>
+template <typename T, int K, int D, bool HLLC>
 __device__ __forceinline__ void face_tangential(const T (&Co)[Shape<K>::NB2], const T (&Cn)[Shape<K>::NB2],
                                                 ctab<T> *tab, const T *col, T (&M2)[Shape<K>::NB2])
 {
@@ -655,7 +646,7 @@ __device__ __forceinline__ void face_tangential(const T (&Co)[Shape<K>::NB2], co
             go[r] = col[face_slot<T, K>(t, 1 + tan1(D), r)];
             gn[r] = col[face_slot<T, K>(t, 1 + tan2(D), r)];
         }
-        face_line_tangential<T, K>(Co, Cn, tab + TL::P1 + t * N1, go, gn, F);
+        face_line_tangential<T, K, HLLC>(Co, Cn, tab + TL::P1 + t * N1, go, gn, F);
         line_moments<K>(F, m);
         add_line<T, K>(m, tab + TL::WLT + t * N1, M2);
     }
@@ -672,9 +663,9 @@ __device__ __forceinline__ void face_tangential(const T (&Co)[Shape<K>::NB2], co
 // accumulators, 0.74 -> 0.90 ms per 64^3 step).  What remains is the latency of the trace loads:
 // the density's and the normal velocity's go out together, each tangential velocity's while the
 // variables before it are worked on.
-template <typename T, int K, int D>
+template <typename T, int K, int D, bool HLLC>
 __device__ __forceinline__ void face(const Field<T, 4> &src, unsigned bo, unsigned bn, int s, ctab<T> *tab, bool prim,
-                                     bool use_hllc, T cs, T cs2, T (&L)[4][Shape<K>::NB], T *col)
+                                     T cs, T cs2, T (&L)[4][Shape<K>::NB], T *col)
 {
     using S = Shape<K>;
     using TL = TabLayout<K>;
@@ -705,7 +696,7 @@ __device__ __forceinline__ void face(const Field<T, 4> &src, unsigned bo, unsign
 #pragma unroll 1
         for (int t = 0; t < N1; ++t) {
             T F0[N1], Fn[N1], go[N1], gn[N1], m[N1];
-            face_line_normal<T, K>(Co, Cn, tab + TL::P1 + t * N1, s, prim, use_hllc, cs, cs2, F0, Fn, go, gn);
+            face_line_normal<T, K, HLLC>(Co, Cn, tab + TL::P1 + t * N1, s, prim, cs, cs2, F0, Fn, go, gn);
             line_moments<K>(F0, m);
 #pragma unroll
             for (int p = 0; p < N1; ++p) col[face_slot<T, K>(t, 0, p)] = m[p];
@@ -731,12 +722,12 @@ __device__ __forceinline__ void face(const Field<T, 4> &src, unsigned bo, unsign
     load_modes<T, K>(src.r[T2], src.pstride, bo, wo);
     load_modes<T, K>(src.r[T2], src.pstride, bn, wn);
     __builtin_amdgcn_sched_barrier(0);
-    face_tangential<T, K, D>(Co, Cn, tab, col, M1);
+    face_tangential<T, K, D, HLLC>(Co, Cn, tab, col, M1);
     lift_moments<T, K, D>(M1, s, tab, L[T1]);
     collapse<T, K, D>(wo, s, tab, Co);
     collapse<T, K, D>(wn, 1 - s, tab, Cn);
     __builtin_amdgcn_sched_barrier(0);
-    face_tangential<T, K, D>(Co, Cn, tab, col, M2);
+    face_tangential<T, K, D, HLLC>(Co, Cn, tab, col, M2);
     lift_moments<T, K, D>(M2, s, tab, L[T2]);
     // (only the low x and y faces are read by a neighbour)
     if constexpr (D < 2)
@@ -1213,7 +1204,9 @@ __device__ __forceinline__ void rhs_combination(const void *ui, T (&L)[4][Shape<
 // of the volume lines each (wave 1, with the smaller half, the density row too), waves 2 and 3 three
 // faces each.  Their sums meet in LDS, where wave v adds up variable v in wave order.  A step at
 // 33x20x27 cells, degree 2, FP32: 157 -> 101 us; at 16^3, degree 1, FP64: 62 -> 53 us.
-template <typename T, int K, bool FDIRECT, bool VMFMA = false, int COMB = 0, bool WSPLIT = false>
+// HLLC: the interface flux, a kernel of its own (the two fluxes' tangential momenta differ in form, and
+// a branch per line cost 2 % of the degree-3 FP64 kernel)
+template <typename T, int K, bool FDIRECT, bool VMFMA = false, int COMB = 0, bool WSPLIT = false, bool HLLC = false>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(rhs_waves<T, K, VMFMA, WSPLIT>())))
 k_rhs(RhsArgs a, StageArgs st)
 {
@@ -1240,7 +1233,6 @@ k_rhs(RhsArgs a, StageArgs st)
     const bool av = a.flags & F_AV;
     const bool prim = a.flags & F_PRIM;
     const bool force = a.flags & F_FORCE;
-    const bool use_hllc = a.flags & F_HLLC;
     const T cs = (T)a.cs, cs2 = (T)(a.cs * a.cs);
     const T hp = (T)(a.h / (K + 1));
     const double dt = a.dt_dev ? *a.dt_dev : a.dt;
@@ -1507,14 +1499,14 @@ k_rhs(RhsArgs a, StageArgs st)
 #pragma unroll 1
             for (int s = 0; s < 2; ++s) {
                 if (role == 2)
-                    face<T, K, 0>(SRC, bo, (unsigned)(s ? nbr[1] : nbr[0]) * sizeof(T), s, tab, prim, use_hllc, cs, cs2, L,
+                    face<T, K, 0, HLLC>(SRC, bo, (unsigned)(s ? nbr[1] : nbr[0]) * sizeof(T), s, tab, prim, cs, cs2, L,
                                   col);
                 else
-                    face<T, K, 2>(SRC, bo, (unsigned)(s ? nbr[5] : nbr[4]) * sizeof(T), s, tab, prim, use_hllc, cs, cs2, L,
+                    face<T, K, 2, HLLC>(SRC, bo, (unsigned)(s ? nbr[5] : nbr[4]) * sizeof(T), s, tab, prim, cs, cs2, L,
                                   col);
             }
             const int s = role - 2;
-            face<T, K, 1>(SRC, bo, (unsigned)(s ? nbr[3] : nbr[2]) * sizeof(T), s, tab, prim, use_hllc, cs, cs2, L, col);
+            face<T, K, 1, HLLC>(SRC, bo, (unsigned)(s ? nbr[3] : nbr[2]) * sizeof(T), s, tab, prim, cs, cs2, L, col);
         }
         // every wave leaves the three variables it does not finish in its column
         static_assert(3 * NB <= S::NF * 4, "the column holds three variables' sums");
@@ -1563,7 +1555,7 @@ k_rhs(RhsArgs a, StageArgs st)
                 __syncthreads();
                 if (xsh) break;
             }
-            face<T, K, 0>(SRC, bo, (unsigned)(s ? nbr[1] : nbr[0]) * sizeof(T), s, tab, prim, use_hllc, cs, cs2, L, col);
+            face<T, K, 0, HLLC>(SRC, bo, (unsigned)(s ? nbr[1] : nbr[0]) * sizeof(T), s, tab, prim, cs, cs2, L, col);
         }
 #pragma unroll 1
         for (int s = 0; s < 2; ++s) {
@@ -1573,11 +1565,11 @@ k_rhs(RhsArgs a, StageArgs st)
                 __syncthreads();
                 if (ysh) break;
             }
-            face<T, K, 1>(SRC, bo, (unsigned)(s ? nbr[3] : nbr[2]) * sizeof(T), s, tab, prim, use_hllc, cs, cs2, L, col);
+            face<T, K, 1, HLLC>(SRC, bo, (unsigned)(s ? nbr[3] : nbr[2]) * sizeof(T), s, tab, prim, cs, cs2, L, col);
         }
 #pragma unroll 1
         for (int s = 0; s < 2; ++s)
-            face<T, K, 2>(SRC, bo, (unsigned)(s ? nbr[5] : nbr[4]) * sizeof(T), s, tab, prim, use_hllc, cs, cs2, L, col);
+            face<T, K, 2, HLLC>(SRC, bo, (unsigned)(s ? nbr[5] : nbr[4]) * sizeof(T), s, tab, prim, cs, cs2, L, col);
     }
 
     const T inv4h = (T)(0.25 / a.h);
