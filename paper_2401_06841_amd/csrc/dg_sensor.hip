@@ -31,27 +31,29 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ float gelu(float z) { return 0.5f * z * (1.0f + erff(z * 0.70710678118654752f)); }
 
 // GELU and its derivative from one exponential: gelu = z Phi(z), gelu' = Phi(z) + z phi(z).  The
-// tail q = Phi(-|z|) = exp(-z^2/2) erfcx(|z|/sqrt 2)/2 is the same exponential times a polynomial
-// of degree 9 in t = 1/(1 + 0.33 |z|) (no constant term: q ~ t for large |z|), a weighted
-// least-squares fit of that quotient on 0 <= |z| <= 14 whose largest relative error is 5.5e-8.
-// Against 64 bits over |z| <= 8 the largest errors are 3.8e-7 (gelu) and 2.0e-7 (gelu'); with the
-// library's erff and expf 4.5e-7 and 1.4e-7, at three times the instructions, and the relative
-// error of gelu's negative tail (2.7e-6) there is 1, from 1 + erf.
+// tail q = Phi(-|z|) = exp(-z^2/2) erfcx(|z|/sqrt 2)/2 is the same exponential times 1/2 plus a
+// polynomial of degree 9 without a constant term in w = 0.36 |z|/(1 + 0.36 |z|), a weighted fit of that
+// quotient on 0 <= |z| <= 14 (largest relative error 2.4e-7, times the exponential 2.4e-9; the
+// reciprocal is the hardware's, to 1 ulp, which counts for little in w).  Largest errors against
+// 64 bits over |z| <= 8, measured: 3.8e-7 (gelu) and 1.1e-7 (gelu', rms 2.4e-8); with the library's erff
+// and expf 4.4e-7 and 1.3e-7 (rms 2.6e-8) at three times the instructions, and the relative error of
+// gelu's negative tail (4e-6) there is 1, from 1 + erf.  (A polynomial in 1 - w, whose terms have to
+// add up to 1/2 at z = 0: 2.0e-7 in gelu' there, at the same speed.)
 __device__ __forceinline__ void gelu_both(float z, float &f, float &d)
 {
-    const float a = fabsf(z);
+    const float b = 0.36f * fabsf(z);
     const float e = __builtin_amdgcn_exp2f(z * z * -0.72134752044448170f);
-    const float t = rcp(fmaf(0.33f, a, 1.0f));
-    float p = -0.0208073827f;
-    p = fmaf(p, t, 0.123079021f);
-    p = fmaf(p, t, -0.267184559f);
-    p = fmaf(p, t, 0.224629068f);
-    p = fmaf(p, t, -0.0565259163f);
-    p = fmaf(p, t, 0.121818947f);
-    p = fmaf(p, t, 0.111065914f);
-    p = fmaf(p, t, 0.132302778f);
-    p = fmaf(p, t, 0.131622159f);
-    const float q = p * t * e;
+    const float w = b * __builtin_amdgcn_rcpf(1.0f + b);
+    float p = 0.0159039553f;
+    p = fmaf(p, w, -0.0774657652f);
+    p = fmaf(p, w, 0.107688867f);
+    p = fmaf(p, w, -0.0153067438f);
+    p = fmaf(p, w, 0.011065728f);
+    p = fmaf(p, w, -0.154588133f);
+    p = fmaf(p, w, -0.0999606401f);
+    p = fmaf(p, w, 0.820816517f);
+    p = fmaf(p, w, -1.10817254f);
+    const float q = fmaf(p, w, 0.5f) * e;
     const float cdf = z < 0.0f ? q : 1.0f - q;
     f = z * cdf;
     d = fmaf(z, 0.39894228040143268f * e, cdf);
