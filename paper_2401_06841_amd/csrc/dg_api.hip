@@ -134,16 +134,6 @@ void build_tables(std::vector<double> &t)
                 const double xi[3] = {g[qx], g[qy], g[qz]};
                 t[TL::VW + q] = w[qx] * w[qy] * w[qz];
                 for (int a = 0; a < 3; ++a) t[TL::VXI + 3 * q + a] = xi[a];
-                for (int l = 0; l < S::NB; ++l) {
-                    const int *e = M.e[l];
-                    t[TL::VPHI + q * S::NB + l] = lt(e[0], xi[0]) * lt(e[1], xi[1]) * lt(e[2], xi[2]);
-                    for (int d = 0; d < 3; ++d) {
-                        if (M.dj[d][l] < 0) continue;
-                        double v = 1.0;
-                        for (int a = 0; a < 3; ++a) v *= (a == d) ? dlt(e[a], xi[a]) : lt(e[a], xi[a]);
-                        t[TL::VDPHI + (q * 3 + d) * S::ND + M.dj[d][l]] = v;
-                    }
-                }
             }
     for (int r2 = 0; r2 < S::N1; ++r2)
         for (int r1 = 0; r1 < S::N1; ++r1) {
@@ -172,38 +162,27 @@ void build_tables(std::vector<double> &t)
                 if (b >= 1) t[TL::LWY + r * TL::NL + line_dy(a, b)] = wr * lt(a, g[tx]) * dlt(b, g[ty]);
             }
         }
-    // basis values on the faces: the face point r = r1 + (k+1) r2 has the tangential
-    // coordinates (g[r1], g[r2]) along the axes tan1(d) < tan2(d), and xi_d = -1 or +1
-    for (int d = 0; d < 3; ++d)
-        for (int s = 0; s < 2; ++s)
-            for (int r2 = 0; r2 < S::N1; ++r2)
-                for (int r1 = 0; r1 < S::N1; ++r1) {
-                    const int r = r1 + S::N1 * r2;
-                    double xi[3];
-                    xi[d] = s ? 1.0 : -1.0;
-                    xi[tan1(d)] = g[r1];
-                    xi[tan2(d)] = g[r2];
-                    for (int l = 0; l < S::NB; ++l) {
-                        const int *e = M.e[l];
-                        t[TL::PLIFT + ((d * 2 + s) * S::NF + r) * S::NB + l] =
-                            lt(e[0], xi[0]) * lt(e[1], xi[1]) * lt(e[2], xi[2]);
-                    }
-                }
 }
 
-// A-operand tables of the matrix-core volume integral at degree 2 (MfmaTab) from the host
-// tables t: lane = 16 g + j; padded points take point 0's values for evaluations and zero
-// weights for the contractions; padded modes are zero.
-void build_mfma_tables(const std::vector<double> &t, std::vector<float> &mt)
+// A-operand tables of the matrix-core volume integral at degree 2 (MfmaTab): lane = 16 g + j;
+// padded points take point 0's values for evaluations and zero weights for the contractions;
+// padded modes are zero.
+void build_mfma_tables(std::vector<float> &mt)
 {
     using S = Shape<2>;
-    using TL = TabLayout<2>;
     constexpr Modes<2> M = make_modes<2>();
     mt.assign(MfmaTab::SIZE, 0.0f);
-    auto phi = [&](int q, int l) { return t[TL::VPHI + q * S::NB + l]; };
-    auto dphi = [&](int q, int d, int l) {
-        return M.dj[d][l] < 0 ? 0.0 : t[TL::VDPHI + (q * 3 + d) * S::ND + M.dj[d][l]];
+    double x[3], wx[3];
+    gauss_host(3, x, wx);
+    // phi_l at volume point q, or with d < 3 its derivative along axis d
+    auto basis = [&](int q, int l, int d) {
+        const int p[3] = {q % 3, q / 3 % 3, q / 9};
+        double v = 1.0;
+        for (int a = 0; a < 3; ++a) v *= a == d ? dlt(M.e[l][a], x[p[a]]) : lt(M.e[l][a], x[p[a]]);
+        return v;
     };
+    auto phi = [&](int q, int l) { return basis(q, l, 3); };
+    auto weight = [&](int q) { return wx[q % 3] * wx[q / 3 % 3] * wx[q / 9]; };
     for (int lane = 0; lane < 64; ++lane) {
         const int g = lane / 16, j = lane % 16;
         for (int P = 0; P < 2; ++P) {
@@ -216,9 +195,9 @@ void build_mfma_tables(const std::vector<double> &t, std::vector<float> &mt)
             for (int r = 0; r < 4; ++r) {
                 const int q = 16 * P + 4 * g + r;
                 const bool ok = q < S::NQ && j < S::NB;
-                const double w = q < S::NQ ? t[TL::VW + q] : 0.0;
+                const double w = q < S::NQ ? weight(q) : 0.0;
                 for (int d = 0; d < 3; ++d)
-                    mt[MfmaTab::CT + ((d * 2 + P) * 4 + r) * 64 + lane] = ok ? (float)(w * dphi(q, d, j)) : 0.0f;
+                    mt[MfmaTab::CT + ((d * 2 + P) * 4 + r) * 64 + lane] = ok ? (float)(w * basis(q, j, d)) : 0.0f;
                 mt[MfmaTab::FT + (P * 4 + r) * 64 + lane] = ok ? (float)(w * phi(q, j)) : 0.0f;
                 mt[MfmaTab::WQ + (P * 4 + r) * 64 + lane] = (float)w;
             }
@@ -391,7 +370,7 @@ int dg_init(const dg_config *cfg, dg_ctx **out)
     if (e == hipSuccess) e = hipMalloc((void **)&c->mlp_bf16, 8 * DG_MLP_NPARAM);
     if (e == hipSuccess && (c->cfg.flags & DG_VOLUME_MFMA)) {
         std::vector<float> mt;
-        build_mfma_tables(t, mt);
+        build_mfma_tables(mt);
         e = hipMalloc((void **)&c->mfma_tab, mt.size() * sizeof(float));
         if (e == hipSuccess) e = hipMemcpy(c->mfma_tab, mt.data(), mt.size() * sizeof(float), hipMemcpyHostToDevice);
     }

@@ -17,7 +17,6 @@ struct Shape {
     static constexpr int NF = N1 * N1;
     static constexpr int NB = (K + 1) * (K + 2) * (K + 3) / 6;
     static constexpr int NB2 = (K + 1) * (K + 2) / 2;   // modes of the 2D face basis
-    static constexpr int ND = NB - NB2;                  // modes with a positive exponent along an axis
 };
 
 // tangential axes of a face normal to d (increasing order)
@@ -31,7 +30,6 @@ template <int K>
 struct Modes {
     int e[Shape<K>::NB][3];     // exponents (a, b, c) of every mode
     int d2[3][Shape<K>::NB];    // 2D index of the tangential exponents on a face normal to d
-    int dj[3][Shape<K>::NB];    // index among the modes with e[d] >= 1, or -1
     int p2[Shape<K>::NB2][2];   // exponent pair of every 2D mode
 };
 
@@ -48,13 +46,8 @@ constexpr Modes<K> make_modes()
                 M.e[m][2] = n - a - b;
                 ++m;
             }
-    for (int d = 0; d < 3; ++d) {
-        int j = 0;
-        for (int l = 0; l < Shape<K>::NB; ++l) {
-            M.d2[d][l] = idx2(M.e[l][tan1(d)], M.e[l][tan2(d)]);
-            M.dj[d][l] = M.e[l][d] >= 1 ? j++ : -1;
-        }
-    }
+    for (int d = 0; d < 3; ++d)
+        for (int l = 0; l < Shape<K>::NB; ++l) M.d2[d][l] = idx2(M.e[l][tan1(d)], M.e[l][tan2(d)]);
     for (int n = 0; n <= K; ++n)
         for (int p = n; p >= 0; --p) {
             M.p2[idx2(p, n - p)][0] = p;
@@ -114,16 +107,12 @@ constexpr DivMap<K> make_divmap()
 template <int K>
 struct TabLayout {
     using S = Shape<K>;
-    static constexpr int VPHI = 0;                          // [NQ][NB]   phi_l at volume points
-    static constexpr int VDPHI = VPHI + S::NQ * S::NB;      // [NQ][3][ND] dphi_l/dxi_d, modes with e_d >= 1
-    static constexpr int VW = VDPHI + S::NQ * 3 * S::ND;    // [NQ]       product Gauss weights
+    static constexpr int VW = 0;                            // [NQ]       product Gauss weights
     static constexpr int F2 = VW + S::NQ;                   // [NF][NB2]  2D basis at face points
     static constexpr int FW = F2 + S::NF * S::NB2;          // [NF]       face weights
     static constexpr int LEND = FW + S::NF;                 // [K+1][2]   Lt_n(-1), Lt_n(+1)
     static constexpr int VXI = LEND + 2 * (K + 1);          // [NQ][3]    reference coordinates
-    static constexpr int PLIFT = VXI + 3 * S::NQ;           // [3][2][NF][NB] phi_l at the face points of
-                                                            //   face (normal d, side s: 0 low, 1 high)
-    static constexpr int WLT = PLIFT + 3 * 2 * S::NF * S::NB;  // [K+1][K+1] w_t Lt_a(xi_t): 1D weight times
+    static constexpr int WLT = VXI + 3 * S::NQ;             // [K+1][K+1] w_t Lt_a(xi_t): 1D weight times
                                                             //   the 1D basis of degree a at 1D point t
     static constexpr int P1 = WLT + (K + 1) * (K + 1);     // [K+1][K+1] Lt_a(xi_t) at 1D point t
     // per line of volume points along z, r = t_x + (K+1) t_y: the weighted 2D basis

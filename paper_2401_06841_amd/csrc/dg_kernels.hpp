@@ -778,29 +778,10 @@ struct PencilLayout {
     __host__ __device__ static size_t size(int nx, int ny, int nz) { return moments(nx, ny, nz) + (size_t)ny * nz * MST; }
 };
 
-// a at volume point q (q = t_x + N1 (t_y + N1 t_z)) from the pencil table: g = this pencil's
-// block, (pr, pi) = the cell's phase P
-// (roundings fixed by explicit fused multiply-adds: every kernel that evaluates the field gets
-// the same bits)
-template <typename T, int K>
-__device__ __forceinline__ void pencil_accel(ctab<T> *ft, ctab<T> *g, int q, T pr, T pim, T (&acc)[3])
-{
-#pragma clang fp contract(off)
-    using PL = PencilLayout<K>;
-    const int tx = q % PL::N1, tt = q / PL::N1;
-    const T er = ft[2 * tx], ei = ft[2 * tx + 1];
-    const T xr = fma(pr, er, -(pim * ei));
-    const T xi = fma(pr, ei, pim * er);
-    const T x2r = fma(xr, xr, -(xi * xi));
-    const T x2i = (T(2) * xr) * xi;
-    ctab<T> *e = g + tt * PL::ENT;
-#pragma unroll
-    for (int d = 0; d < 3; ++d)
-        acc[d] = fma(-e[5 * d + 4], x2i, fma(e[5 * d + 3], x2r, fma(-e[5 * d + 2], xi, fma(e[5 * d + 1], xr, e[5 * d]))));
-}
-
-// the same for the points of a line along z, which share t_x: the phase X and its square once,
-// then a at the point pair tt = t_y + N1 t_z
+// a at the points of a line along z (which share t_x) from the pencil table: the phase X and its square
+// once, from the cell's phase (pr, pim), then a at the point pair tt = t_y + N1 t_z from this pencil's
+// block g.  (Roundings fixed by explicit fused multiply-adds: every kernel that evaluates the field
+// gets the same bits.)
 template <typename T, int K>
 __device__ __forceinline__ void line_phase(ctab<T> *ft, int tx, T pr, T pim, T &xr, T &xi, T &x2r, T &x2i)
 {
@@ -886,22 +867,6 @@ __device__ __forceinline__ void cell_phase(ctab<T> *px, int i, T &pr, T &pim)
 {
     pr = px[2 * i];
     pim = px[2 * i + 1];
-}
-
-// The driving source of one volume point, s = (rho w_q) a, and the running sums of the
-// cell's source for the removed mean acceleration, every rounding fixed (no contraction):
-// the sums come out the same in every kernel that forms them.
-template <typename T>
-__device__ __forceinline__ void drive_point(T rho, T wq, const T (&ac)[3], T (&s)[3], T &fs0, T &fs1, T &fs2)
-{
-#pragma clang fp contract(off)
-    const T rw = rho * wq;
-    s[0] = rw * ac[0];
-    s[1] = rw * ac[1];
-    s[2] = rw * ac[2];
-    fs0 = fs0 + s[0];
-    fs1 = fs1 + s[1];
-    fs2 = fs2 + s[2];
 }
 
 // The cell's driving source summed over its volume points, from its density weights W0 and
@@ -1511,9 +1476,6 @@ k_rhs(RhsArgs a, StageArgs st)
     // this block (whole x lines per block, and y lines of the block but the last) lifts
     // those instead of recomputing the face.  The decision is a wave vote, so the branch
     // is uniform; the stored values are exactly those the cell would compute itself.
-    const int base = blk * BLOCK;
-    const bool xsh = __all((unsigned)(nbr[1] - base) < (unsigned)BLOCK);
-    const bool ysh = __all((unsigned)(nbr[3] - base) < (unsigned)BLOCK);
     // Every face leaves its moments in the cell's LDS column and lifts them from there.
     // A wave whose high neighbours all lie in the block lifts their low-face moments (between
     // two barriers) instead of computing its high face; a high face that is computed is
@@ -1573,6 +1535,9 @@ k_rhs(RhsArgs a, StageArgs st)
                 for (int i = 0; i < 4; ++i) a.part[blk * 4 + i] = acc[i];
         }
     } else {
+        const int base = blk * BLOCK;
+        const bool xsh = __all((unsigned)(nbr[1] - base) < (unsigned)BLOCK);
+        const bool ysh = __all((unsigned)(nbr[3] - base) < (unsigned)BLOCK);
 #pragma unroll 1
         for (int s = 0; s < 2; ++s) {
             if (s == 1) {
