@@ -20,7 +20,8 @@ Comparison legs, from the same state and driving, timed the same way:
   * the other precision with the plain sensor (FP32 bulk mode for the FP64 workloads);
   * FP32 with the learned sensor (degree 2), whose network is trained by the library's
     kernels on sensor snapshots taken during the warm-up (at least its last state).
-Each leg reports its throughput, its k_rhs roofline and the difference of its final state
+Each leg reports its throughput, its k_rhs roofline (executed operations and HBM bytes from the
+committed counters, over the live launch time) and the difference of its final state
 from the main run's: per-field relative L2, density-PDF L1 distance and velocity-spectrum
 log distance (the FP32 legs' statistics error against the FP64 path).
 
@@ -45,6 +46,7 @@ PEAK_FP64_TFLOPS = 78.6      # MI355X vector = matrix FP64 peak
 PEAK_FP32_TFLOPS = 157.3     # MI355X published FP32 vector peak (packed issue)
 FP32_UNPACKED_TFLOPS = 78.6  # issue limit without packed FP32, which the library's kernels do not emit
 PEAK_HBM_TBPS = 8.0          # MI355X HBM3E
+COPY_HBM_TBPS = 4.4          # a large device copy on the card (read + written)
 
 WORKLOADS = {
     # name: (N, degree, default precision, target Mach, driving sigma, spin-up steps from rest)
@@ -106,7 +108,7 @@ def _profile_record(kernel, workload, precision, what):
     return rec
 
 
-def traffic_from_profiles(kernel, workload, precision, launches_unit=1):
+def traffic_from_profiles(kernel, workload, precision):
     """HBM bytes per launch (FETCH_SIZE and WRITE_SIZE, calibrated with a plain copy)."""
     rec = _profile_record(kernel, workload, precision, "traffic")
     return rec.get("bytes_per_launch") if rec else None
@@ -123,6 +125,32 @@ def executed_flops_from_profiles(kernel, workload, precision):
 def _log(msg):
     """Progress on stderr (the JSON line is the only output on stdout)."""
     print(f"[bench {time.strftime('%H:%M:%S')}] {msg}", file=sys.stderr, flush=True)
+
+
+def roofline(workload, precision, kernel, avg_ms, least_bytes):
+    """The dominant kernel's place under the roofline, from the operations it executes and the bytes it
+    moves through HBM (counted with rocprofv3, profiles/) over the live launch time avg_ms.  The bound
+    is the resource it uses the larger part of: the memory, or the vector units (FP32: against the
+    issue rate without packed instructions).  Without valid counters (other workloads, changed
+    sources) the bytes are the least the kernel has to move, each array once, and the fraction a lower
+    bound of the memory's."""
+    t = avg_ms * 1e-3
+    traffic = traffic_from_profiles("k_rhs", workload, precision)
+    executed = executed_flops_from_profiles("k_rhs", workload, precision)
+    tbps = (traffic or least_bytes) / t / 1e12
+    out = {"bound": "hbm", "achieved": tbps, "peak": PEAK_HBM_TBPS, "unit": "TB/s", "frac": tbps / PEAK_HBM_TBPS,
+           "frac_of_large_copy": tbps / COPY_HBM_TBPS, "kernel": kernel, "traffic": traffic,
+           "counted": bool(traffic), "least_bytes_per_launch": least_bytes}
+    if executed:
+        tf = executed / t / 1e12
+        peak, issue = (PEAK_FP64_TFLOPS,) * 2 if precision == "fp64" else (PEAK_FP32_TFLOPS, FP32_UNPACKED_TFLOPS)
+        out.update(executed_flops_per_launch=executed, executed_TFLOP_s=tf, executed_frac=tf / peak)
+        if precision == "fp32":
+            out["executed_frac_of_unpacked_fp32"] = tf / issue
+        if tf / issue > out["frac"]:
+            out.update(bound="alu", achieved=tf, peak=peak, unit="TFLOP/s", frac=tf / peak,
+                       hbm_TB_per_s=tbps, hbm_frac=tbps / PEAK_HBM_TBPS)
+    return out
 
 
 def _timed(sim, steps, measure_profile):
@@ -158,46 +186,31 @@ def _summary(args, sim, precision, wall, prof, retries, dt_min):
         rhs_ms, rhs_n, st_ms, st_n = prof
         avg = rhs_ms / max(rhs_n, 1)
         fl = cfg.flags
-        rhs_flops = model.rhs_flops_per_cell(k, av=bool(fl & dg.DG_AV), proj=bool(fl & dg.DG_PRIM_PROJ),
-                                             forcing=bool(fl & dg.DG_FORCING)) * cfg.ncell
+        model_flops = model.rhs_flops_per_cell(k, av=bool(fl & dg.DG_AV), proj=bool(fl & dg.DG_PRIM_PROJ),
+                                               forcing=bool(fl & dg.DG_FORCING)) * cfg.ncell
         # with split stages the timed kernel (the first stage's right-hand side) also forms the
         # stage's combination
         split = dg.dg_split_stages(sim.ctx)
-        flops = rhs_flops + (model.combination_flops_per_cell(k) * cfg.ncell if split else 0)
-        achieved = flops / (avg * 1e-3) / 1e12
-        peak = PEAK_FP64_TFLOPS if precision == "fp64" else PEAK_FP32_TFLOPS
         out["kernels"] = {"k_rhs_avg_ms": avg, "k_rhs_launches": rhs_n,
                           "k_rhs_forms_stage_combination": split,
                           "k_stage_avg_ms": st_ms / st_n if st_n else None, "k_stage_launches": st_n}
         if not split:
             out["kernels"]["k_rhs_share_of_step"] = avg * 3 * args.steps / (1e3 * wall)
-        out["roofline"] = {"bound": "alu", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
-                           "frac": achieved / peak,
-                           "kernel": "k_rhs: right-hand side and stage combination" if split else "k_rhs",
-                           "traffic": traffic_from_profiles("k_rhs", args.workload, precision, 1)}
-        if precision == "fp32":
-            out["roofline"]["frac_of_unpacked_fp32"] = achieved / FP32_UNPACKED_TFLOPS
-        executed = executed_flops_from_profiles("k_rhs", args.workload, precision)
-        if executed:
-            # the flops the kernel issues (counted), beside the model count of Sec. 7
-            out["roofline"]["executed_flops_per_launch"] = executed
-            out["roofline"]["executed_TFLOP_s"] = executed / (avg * 1e-3) / 1e12
-            out["roofline"]["executed_frac"] = out["roofline"]["executed_TFLOP_s"] / peak
-        traffic = out["roofline"]["traffic"]
-        if traffic:
-            # HBM rate implied by the counted bytes per launch over the live launch time
-            gbps = traffic / (avg * 1e-3) / 1e9
-            out["roofline"]["traffic_GB_per_s"] = gbps
-            out["roofline"]["traffic_frac_of_hbm"] = gbps / (PEAK_HBM_TBPS * 1e3)
-        out["algorithmic_flops_per_launch"] = flops
-        out["rhs_flops_per_launch"] = rhs_flops
+        es = 8 if precision == "fp64" else 4
+        out["roofline"] = roofline(args.workload, precision,
+                                   "k_rhs: right-hand side and stage combination" if split else "k_rhs", avg,
+                                   model.rhs_bytes_per_cell(k, es, bool(fl & (dg.DG_AV | dg.DG_PRIM_PROJ))) * cfg.ncell)
+        # the paper's operation count (every mode at every point) per second: how fast the right-hand
+        # side is, not how busy the units are
+        out["paper_model_flops_per_launch"] = model_flops
+        out["paper_model_TFLOP_s"] = model_flops / (avg * 1e-3) / 1e12
     return out
 
 
 def _rhs_alone(sim, calls, summary):
     """With split stages every stage's right-hand-side kernel also forms the stage's
     combination: the right-hand side alone (stored, dg_rhs on the run's final state) timed over
-    a few calls, its roofline beside the dominant kernel's."""
+    a few calls, beside the dominant kernel."""
     import torch
 
     from paper_2401_06841_amd import dg
@@ -212,18 +225,17 @@ def _rhs_alone(sim, calls, summary):
     ms, n, _, _ = dg.dg_profile_read(sim.ctx)
     dg.dg_profile(sim.ctx, False)
     avg = ms / max(n, 1)
-    rf = summary["roofline"]
-    achieved = summary["rhs_flops_per_launch"] / (avg * 1e-3) / 1e12
     summary["kernels"]["k_rhs_stored_avg_ms"] = avg
-    rf["rhs_alone"] = {"kernel": "k_rhs alone (right-hand side stored, dg_rhs)", "avg_ms": avg,
-                       "achieved": achieved, "frac": achieved / rf["peak"], "launches": n}
+    summary["roofline"]["rhs_alone"] = {"kernel": "k_rhs alone (right-hand side stored, dg_rhs)", "avg_ms": avg,
+                                        "paper_model_TFLOP_s": summary["paper_model_flops_per_launch"] / (avg * 1e-3) / 1e12,
+                                        "launches": n}
 
 
 def _statistics(sim):
     """Flow statistics of the final state on the GPU (Sec. 4.3), timed: the structure
     function with 100 bins of 1e5 pairs and the spectrum on the N p grid (p = k+1).  Each
-    is run once untimed (hipFFT plan set-up) and then timed on the host clock around the
-    synchronising call.  The pair kernel reads two cell records of 4 nb doubles per pair."""
+    is run once untimed (hipFFT's plan, for grids that take it) and then timed on the host
+    clock around the synchronising call.  The pair kernel reads two cell records of 4 nb doubles per pair."""
     import numpy as np
     import torch
 

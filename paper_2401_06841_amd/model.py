@@ -1,4 +1,4 @@
-"""Algorithmic work counts of the DG stage (used for roofline fractions).
+"""Work counts of the DG stage: the paper's operation model and the bytes a stage cannot do without.
 
 The paper's operation-count model (Sec. 7, "Discussion on computational cost") per cell
 and per evaluation of the weight derivative:
@@ -11,8 +11,9 @@ pieces this method runs beside it, counted the same way (one multiply-add = 2):
     driving source        12 b v        (Sec. 4.2: rho a at v points projected on 3 rows)
     positivity limiter    2 b (v + 6 s) (Sec. 3.1: density at every volume and face point)
     stage combination     5 per DOF     (Sec. 2.2 / 7: SSP Runge-Kutta)
-Kernels that do fewer operations (e.g. exploiting zero derivative entries) are still
-measured against these counts.
+The model counts every mode at every point.  The kernels evaluate and contract line by line and
+execute about a third of it, so a rate in these counts says how fast a kernel is, not what part
+of the units it uses (that takes the counted operations in profiles/).
 """
 
 
@@ -61,10 +62,11 @@ def rhs_flops_per_cell(k: int, av: bool = True, proj: bool = True, forcing: bool
     return n
 
 
-def combination_flops_per_cell(k: int) -> int:
-    """The stage combination alone (5 per DOF, f = 4): the extra work of a right-hand-side
-    kernel that forms its stage's combination (split stages)."""
-    return 5 * 4 * nbasis(k)
+def rhs_bytes_per_cell(k: int, elem_bytes: int, vhat: bool = True) -> int:
+    """Least HBM bytes of the right-hand-side kernel: the state and (vhat: with the projection or the
+    viscosity) the projected velocity read once, a state (the right-hand side, or the stage's
+    combination) written once."""
+    return (11 if vhat else 8) * nbasis(k) * elem_bytes
 
 
 def stage_bytes_per_cell(k: int, elem_bytes: int) -> float:
