@@ -328,7 +328,9 @@ int dg_sensor_set_nu(dg_ctx *ctx, const void *nu_dev, const int32_t *fallback_de
 int dg_mlp_forward(dg_ctx *ctx, const float *params_dev, const float *x_dev, int n, float *y_dev);
 
 /* Mean-squared-error loss and its gradient with respect to the parameters for n rows:
- * grad_dev[DG_MLP_NPARAM] float (overwritten), loss_dev[1] float (device). */
+ * grad_dev[DG_MLP_NPARAM] float (overwritten), loss_dev[1] float (device).  Its GELU and that of
+ * dg_mlp_forward are two FP32 evaluations, each within 4.5e-7 of the function: the loss of the
+ * outputs dg_mlp_forward gives for the same rows agrees to the network's rounding, not to the bit. */
 int dg_mlp_grad(dg_ctx *ctx, const float *params_dev, const float *x_dev, const float *t_dev,
                 int n, float *grad_dev, float *loss_dev);
 

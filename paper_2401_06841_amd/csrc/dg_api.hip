@@ -943,8 +943,7 @@ static const Scheme &scheme_of(const dg_ctx *c)
 
 // Whether a stage is split between its right-hand-side kernel, which forms the stage's
 // combination (k_rhs with COMB), and k_limit_project, which limits and projects it, instead of
-// storing the right-hand side for a stage kernel: the one-lane kernel with the vector volume
-// integral, a stage without a side combination that writes a workspace buffer other than its
+// storing the right-hand side for a stage kernel: the vector volume integral, a stage without a side combination that writes a workspace buffer other than its
 // input, and not turned off by DG_SEPARATE_STAGE.  The last stage writes the caller's array,
 // which must keep u^n when the step fails: split, it stores its combination into a free
 // workspace buffer (raising the failure flag from the combination's mean density) and k_stage
@@ -953,7 +952,10 @@ static const Scheme &scheme_of(const dg_ctx *c)
 // The split pays where the mesh takes many rounds of blocks: measured on one MI355X (split
 // against separate, alternated in one call, degree 2, driven, mean-free): 256^3 FP64 42.7 vs
 // 43.8 ms per step, 256^3 FP32 21.5 vs 22.2 ms, 128^3 FP64 5.43 vs 5.52 ms, 128^3 FP32 2.76 vs
-// 2.79 ms; slower at 64^3 FP64 (0.81-0.82 vs 0.78 ms).
+// 2.79 ms; slower at 64^3 FP64 (0.81-0.82 vs 0.78 ms).  That was with point-by-point kernels, and the
+// line is where they put it; with the present ones the split gains more and earlier (150x91x121:
+// degree 2 FP64 3.66 vs 4.17 ms, FP32 1.78 vs 2.15, degree 3 FP32 4.25 vs 4.73, degree 1 FP64 1.34 vs
+// 1.43; 64^3 degree 2 FP64 0.533 vs 0.539 ms, degree 3 FP32 0.663 vs 0.648).
 constexpr long long SPLIT_MIN_CELLS = 1LL << 21;
 
 // (The split last stage: 256^3 FP64 39.19 against 39.83 ms per step, FP32 20.22 against 20.71

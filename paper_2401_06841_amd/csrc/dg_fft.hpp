@@ -231,8 +231,9 @@ __host__ __device__ inline int fft_pad(int n) { return (n + 7) / 8 * 8; }
 // F[d][tile of 8 x frequencies][z][y][8].  Two real lines of one component, neighbours in y, make a
 // complex line (of two components, the larger one's rounding would pass into the smaller).
 // Bound about half by the vector units (some 250 instructions a point: the three FP64 quotients, the
-// collapse of the weights, the transform) and half by the writes of 128-byte pieces: 0.77 ms on 384^3
-// points (1.4 GB written, 0.34 GB read), where the evaluation alone took 0.78 ms with the grid written.
+// collapse of the weights, the transform) and half by the writes of 128-byte pieces: on 384^3 points
+// 0.745 ms (1.37 GB written, 0.34 GB read; averages of one trace, like the two other passes': 1.92 ms
+// the whole call), where the evaluation alone took 0.78 ms with the grid written.
 // SPLIT: the points of a cell's line are shared by as many threads as the block has for it
 template <typename T, int K, bool SPLIT>
 __global__ void __launch_bounds__(BLOCK) k_fft_x(const void *u_, int nx, int ny, int nz, double floor_, int p, int yl,
@@ -283,8 +284,8 @@ __global__ void __launch_bounds__(BLOCK) k_fft_x(const void *u_, int nx, int ny,
     };
     // A thread takes one line of a cell, and reads the cell's weights for it; with the 80 weights of
     // degree 3 (at most nt / nx threads a cell) it first sums them over z, for all of its lines.
-    // On 384^3 points, degree 2, FP32, this pass takes 0.78 ms against 0.85 ms with the sums over z
-    // first, on 512^3 points, degree 3, 3.1 against 2.1 ms.
+    // Forms of a thread's work compared, a line at a time against the sums over z first: on 384^3 points,
+    // degree 2, FP32, 0.78 and 0.85 ms, on 512^3 points, degree 3, 3.1 and 2.1 ms.
     if constexpr (K < 3) {
         const int na = SPLIT ? max(1, nt / (nx * nyl)) : 1;
         for (int it = threadIdx.x; it < nx * nyl * na; it += nt) {
@@ -380,7 +381,7 @@ __global__ void __launch_bounds__(BLOCK) k_fft_x(const void *u_, int nx, int ny,
 // the block's threads for lines of n points: n, rounded up to whole waves
 __host__ __device__ inline int fft_threads(int n) { return (n + 63) / 64 * 64; }
 
-// y lines, in place: one tile of 8 columns, contiguous, a block.  Bound by memory: 2.8 GB in 0.60 ms
+// y lines, in place: one tile of 8 columns, contiguous, a block.  Bound by memory: 2.83 GB in 0.606 ms
 // on 384^3 points (4.7 TB/s; a large copy runs at 4.4)
 template <int TN>
 __global__ void __launch_bounds__(TN) k_fft_y(FftAxis ax, FftTables tb, double2 *F)
@@ -415,7 +416,7 @@ __device__ __forceinline__ int shell_of(int s)
 
 // z lines and the shell sums of 1/2 |F / npts|^2 (the x frequencies 0 < f < X / 2 stand for
 // themselves and their mirror images): one (tile, y) after another, the three components' squares
-// added in registers before the one addition to the block's histogram in LDS.  1.4 GB in 0.61 ms on
+// added in registers before the one addition to the block's histogram in LDS.  1.42 GB in 0.603 ms on
 // 384^3 points and 3.3 GB in 0.85 ms on 512^3; without the histogram 0.61 and 0.83, with three
 // resident blocks a compute unit instead of two (twiddles read from memory) 0.62 and 0.98, with the
 // next lines fetched ahead in registers 0.54 and 1.07

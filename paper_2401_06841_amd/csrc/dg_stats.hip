@@ -416,10 +416,11 @@ int launch_grid(dg_ctx *c, const void *u, int p, double *grid, long long npts)
 // half spectrum (which the lines' tables and the rounded-up x frequencies have to fit; grids of a
 // few points a side may not).  The shell histograms of nblk blocks go to part; nblk = 0: not such a
 // grid.  Against the grid kernel, the library's transforms and the shell kernel, which such grids
-// took before, us: 128^3 cells, degree 2, FP32, on 384^3 points 3860 -> 1910 (and 7 -> 2 ms with the
-// library's plan to make); degree 3 on 512^3 8800 -> 4460; 128^3, degree 1, FP64, on 256^3 1010 ->
-// 520; 64^3, degree 2, on 192^3 500 -> 264; 16^3, degree 1, on 32^3 74 -> 46.  Every size measured
-// is faster, so there is no lower bound.
+// took before, us: 128^3 cells, degree 2, FP32, on 384^3 points 3860 -> 1917 (and 7 -> 2 ms with the
+// library's plan to make); degree 3 on 512^3 8830 -> 4150; 128^3, degree 1, FP64, on 256^3 1010 ->
+// 515; 64^3, degree 2, on 192^3 515 -> 250; 16^3, degree 1, on 32^3 74 -> 50; one cell of 512^3 points
+// 7420 -> 3790, 512x4x4 cells of one point each 80 -> 56.  Every size measured is faster, so there is
+// no lower bound.
 template <typename T, int K>
 int launch_lines(dg_ctx *c, const void *u, int p, const SpLayout &s, char *scr, int *nblk)
 {
