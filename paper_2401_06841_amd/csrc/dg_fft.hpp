@@ -431,7 +431,6 @@ __global__ void __launch_bounds__(TN) k_fft_z(FftAxis ax, FftTables tb, const do
     for (int t = threadIdx.x; t < Z; t += nt) tw[t] = tb.tw[2][t];
     for (int s = threadIdx.x; s < nshell; s += nt) hist[s] = 0.0;
     const int Xh = X / 2 + 1, ntiles = ntile * Y;
-    const double inv = 1.0 / ((double)X * (double)Y * (double)Z);
     auto lds = [&](int pos, int c) { return tile[pos * FFT_COLS + c]; };
     auto sts = [&](int, int, int pos, int c, double2 v) { tile[pos * FFT_COLS + c] = v; };
     constexpr int NE = 12;      // squares of a thread: at most ceil(8 / R) R
@@ -484,7 +483,7 @@ __global__ void __launch_bounds__(TN) k_fft_z(FftAxis ax, FftTables tb, const do
                         // the last stage's sub-lines are single points
                         const int iz = tb.freq[2][q / FFT_COLS * R + p], fz = iz < (Z + 1) / 2 ? iz : iz - Z;
                         const int shell = shell_of(ix * ix + fy * fy + fz * fz);
-                        atomicAdd(&hist[shell], w * e[i * R + p] * inv * inv);
+                        atomicAdd(&hist[shell], w * e[i * R + p]);
                     }
                 }
             }
@@ -499,7 +498,10 @@ __global__ void __launch_bounds__(TN) k_fft_z(FftAxis ax, FftTables tb, const do
         }
     }
     __syncthreads();
-    for (int s = threadIdx.x; s < nshell; s += nt) part[(size_t)blockIdx.x * nshell + s] = hist[s];
+    // (the sums by the square of the point count, at once: its reciprocal's rounding, squared, would
+    // stand in every shell)
+    const double npts = (double)X * (double)Y * (double)Z;
+    for (int s = threadIdx.x; s < nshell; s += nt) part[(size_t)blockIdx.x * nshell + s] = hist[s] / (npts * npts);
 }
 
 // The fewest stages of radices 8 6 5 4 3 2 for a line of n points, largest last (the last stage has

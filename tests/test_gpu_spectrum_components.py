@@ -19,6 +19,20 @@ from paper_2401_06841_amd import dg
 pytestmark = pytest.mark.gpu
 
 
+@pytest.mark.parametrize("shape,p", [((24, 24, 24), 1), ((16, 12, 20), 1), ((18, 15, 10), 2), ((16, 9, 6), 3), ((40, 3, 5), 5)])
+def test_uniform_flow_is_exact(shape, p):
+    """v = (1, 2, 2) everywhere: every sum of the transform is a whole number, and the energy of shell 0
+    is 4.5 to the bit when nothing but the squared point count divides it."""
+    print(f"spectrum of a uniform flow {shape} p={p}", flush=True)
+    ctx = make(*shape, 1, 0)
+    u = ctx.empty_state()
+    u.zero_()
+    for v, x in enumerate((1.0, 1.0, 2.0, 2.0)):
+        u[v, 0] = x
+    e = dg.dg_velocity_spectrum(ctx, u, p)
+    assert e[0] == 4.5 and np.abs(e[1:]).max() < 1e-28
+
+
 @pytest.mark.parametrize("big", [0, 1, 2])
 @pytest.mark.parametrize("small", [1, 2])       # axes after the large one
 @pytest.mark.parametrize("n,p,k", [(24, 1, 1), (25, 1, 3), (20, 3, 2), (20, 2, 1), (12, 5, 3)])
